@@ -24,9 +24,6 @@
 #ifndef ZPP_ADAM_RESIDENCY
 #define ZPP_ADAM_RESIDENCY 11
 #endif
-#ifndef ZPP_ADAM_MAX_GRID
-#define ZPP_ADAM_MAX_GRID (1u << 20)
-#endif
 
 namespace zpp {
 namespace {
@@ -41,59 +38,37 @@ struct AdamArgs {
 
 constexpr int kAdamThreads = ZPP_ADAM_THREADS;
 
-template <bool ADAMW, int U>
-__global__ __launch_bounds__(kAdamThreads) void adam_vec_kernel(AdamArgs a) {
-    constexpr size_t kTile = (size_t)kAdamThreads * 4 * U;
-    const size_t ntiles = (a.n + kTile - 1) / kTile;
-    for (size_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const size_t base = t * kTile + (size_t)threadIdx.x * 4;
-        if ((t + 1) * kTile <= a.n) {
-            f32x4 P[U], M[U], V[U], G[U];
+template <bool ADAMW, int U, bool WHOLE>
+__device__ __forceinline__ void adam_tile(const AdamArgs &a, size_t base, uint32_t rest) {
+    f32x4 P[U], M[U], V[U], G[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const size_t i = base + (size_t)u * kAdamThreads * 4;
-                P[u] = ld_nt(reinterpret_cast<const f32x4 *>(a.p + i));
-                M[u] = ld_nt(reinterpret_cast<const f32x4 *>(a.m + i));
-                V[u] = ld_nt(reinterpret_cast<const f32x4 *>(a.v + i));
-                G[u] = ld_nt(reinterpret_cast<const f32x4 *>(a.g + i));
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const size_t i = base + (size_t)u * kAdamThreads * 4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float p = P[u][e], m = M[u][e], v = V[u][e];
-                    adam_update<ADAMW>(p, m, v, G[u][e], a.c);
-                    P[u][e] = p;
-                    M[u][e] = m;
-                    V[u][e] = v;
-                }
-                st_nt(reinterpret_cast<f32x4 *>(a.p + i), P[u]);
-                st_nt(reinterpret_cast<f32x4 *>(a.m + i), M[u]);
-                st_nt(reinterpret_cast<f32x4 *>(a.v + i), V[u]);
-                u32x2 o;
-                o.x = pack_bf16x2(P[u].x, P[u].y);
-                o.y = pack_bf16x2(P[u].z, P[u].w);
-                st_nt(reinterpret_cast<u32x2 *>(a.out + i), o);
-            }
-        } else {
-            // the last, partial tile: element by element
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                for (int e = 0; e < 4; ++e) {
-                    const size_t i = base + (size_t)u * kAdamThreads * 4 + e;
-                    if (i < a.n) {
-                        float p = a.p[i], m = a.m[i], v = a.v[i];
-                        adam_update<ADAMW>(p, m, v, a.g[i], a.c);
-                        a.p[i] = p;
-                        a.m[i] = m;
-                        a.v[i] = v;
-                        a.out[i] = (uint16_t)bf16_rne_bits(p);
-                    }
-                }
-            }
-        }
+    for (int u = 0; u < U; ++u) {
+        const uint32_t i = (u * kAdamThreads + threadIdx.x) * 4;
+        P[u] = load4<WHOLE>(a.p + base, i, rest);
+        M[u] = load4<WHOLE>(a.m + base, i, rest);
+        V[u] = load4<WHOLE>(a.v + base, i, rest);
+        G[u] = load4<WHOLE>(a.g + base, i, rest);
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t i = (u * kAdamThreads + threadIdx.x) * 4;
+        adam_update4<ADAMW>(P[u], M[u], V[u], G[u], a.c);
+        store4<WHOLE>(a.p + base, i, rest, P[u]);
+        store4<WHOLE>(a.m + base, i, rest, M[u]);
+        store4<WHOLE>(a.v + base, i, rest, V[u]);
+        store4_bf16<WHOLE>(a.out + base, i, rest,
+                           u32x2{pack_bf16x2(P[u].x, P[u].y), pack_bf16x2(P[u].z, P[u].w)});
+    }
+}
+
+template <bool ADAMW, int U>
+__global__ __launch_bounds__(kAdamThreads) void adam_vec_kernel(AdamArgs a, TileSpan tiles) {
+    constexpr uint32_t kTile = kAdamThreads * 4 * U;
+    const size_t base = (tiles.first + blockIdx.x) * kTile;
+    if (__builtin_expect(blockIdx.x < tiles.whole, 1))
+        adam_tile<ADAMW, U, true>(a, base, kTile);
+    else
+        adam_tile<ADAMW, U, false>(a, base, tiles.tail);
 }
 
 // Any alignment: one element per thread, grid-stride.
@@ -116,16 +91,16 @@ hipError_t launch_adam(float *p, float *m, float *v, const float *g, uint16_t *o
                        const AdamConsts &c, bool vector_path, hipStream_t stream) {
     AdamArgs a{p, m, v, g, out, n, c};
     if (vector_path) {
-        constexpr size_t kTile = (size_t)kAdamThreads * 4 * ZPP_ADAM_UNROLL;
-        size_t tiles = (n + kTile - 1) / kTile;
-        const unsigned grid = (unsigned)(tiles < ZPP_ADAM_MAX_GRID ? tiles : ZPP_ADAM_MAX_GRID);
+        constexpr uint32_t kTile = kAdamThreads * 4 * ZPP_ADAM_UNROLL;
         constexpr size_t lds = residency_lds(ZPP_ADAM_RESIDENCY);
-        if (c.adamw)
-            hipLaunchKernelGGL((adam_vec_kernel<true, ZPP_ADAM_UNROLL>), dim3(grid),
-                               dim3(kAdamThreads), lds, stream, a);
-        else
-            hipLaunchKernelGGL((adam_vec_kernel<false, ZPP_ADAM_UNROLL>), dim3(grid),
-                               dim3(kAdamThreads), lds, stream, a);
+        for_tiles(n, kTile, 1, kAdamThreads, [&](const TileSpan &tiles, unsigned grid) {
+            if (c.adamw)
+                hipLaunchKernelGGL((adam_vec_kernel<true, ZPP_ADAM_UNROLL>), dim3(grid),
+                                   dim3(kAdamThreads), lds, stream, a, tiles);
+            else
+                hipLaunchKernelGGL((adam_vec_kernel<false, ZPP_ADAM_UNROLL>), dim3(grid),
+                                   dim3(kAdamThreads), lds, stream, a, tiles);
+        });
     } else {
         size_t blocks = (n + kThreads - 1) / kThreads;
         const unsigned grid = (unsigned)(blocks < (1u << 20) ? blocks : (1u << 20));

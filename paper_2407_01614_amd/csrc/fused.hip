@@ -51,9 +51,6 @@
 #ifndef ZPP_FUSED_RECV_IL_RESIDENCY
 #define ZPP_FUSED_RECV_IL_RESIDENCY 14
 #endif
-#ifndef ZPP_FUSED_MAX_GRID
-#define ZPP_FUSED_MAX_GRID (1u << 30)
-#endif
 
 namespace zpp {
 namespace {
@@ -73,91 +70,72 @@ struct FusedArgs {
 template <class GS> constexpr size_t fused_xcd_run() { return 0; }
 template <> constexpr size_t fused_xcd_run<I4Grad>() { return kSeparateXcdRun; }
 
+// One chunk of C consecutive elements from `base` on, `rest` of which lie
+// inside the arrays.  WHOLE: all of them; otherwise (the launch's last,
+// partial chunk) the absent elements hold bf16 zero, which no absmax can see.
+template <bool ADAMW, int B, bool QUANT, bool WHOLE, class GS>
+__device__ __forceinline__ void fused_chunk(const FusedArgs &a, const GS &gs, size_t base,
+                                            uint32_t rest) {
+    constexpr int C = B > 256 ? B : 256;  // elements per chunk (one wave)
+    constexpr int W = C / 256;            // float4 groups per lane
+    static_assert(W <= 2, "blocks of 64 to 512");
+    constexpr int L = B < 256 ? B / 4 : kWave;  // lanes per quant block
+    const uint32_t lane = threadIdx.x;
+    u32x2 pk[W];
+    u16x2 m2 = {0, 0};
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const uint32_t i = w * 256 + lane * 4;
+        f32x4 P = load4<WHOLE>(a.p + base, i, rest);
+        f32x4 M = load4<WHOLE>(a.m + base, i, rest);
+        f32x4 V = load4<WHOLE>(a.v + base, i, rest);
+        const f32x4 G = grad_load4<WHOLE>(gs, base, i, rest);
+        adam_update4<ADAMW>(P, M, V, G, a.c);
+        store4<WHOLE>(a.p + base, i, rest, P);
+        store4<WHOLE>(a.m + base, i, rest, M);
+        store4<WHOLE>(a.v + base, i, rest, V);
+        pk[w] = u32x2{pack_bf16x2(P.x, P.y), pack_bf16x2(P.z, P.w)};
+        if constexpr (!WHOLE) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (i + e >= rest)
+                    pk[w][e / 2] &= e % 2 ? 0x0000FFFFu : 0xFFFF0000u;
+        }
+        store4_bf16<WHOLE>(a.primary + base, i, rest, pk[w]);
+        if (a.secondary)
+            store4_bf16<WHOLE>(a.secondary + base, i, rest, pk[w]);
+        m2 = __builtin_elementwise_max(
+            m2, __builtin_elementwise_max(absbits2(pk[w].x), absbits2(pk[w].y)));
+    }
+    if constexpr (QUANT) {
+        uint32_t mx = max((uint32_t)m2.x, (uint32_t)m2.y);
+#pragma unroll
+        for (int off = L / 2; off >= 1; off >>= 1)
+            mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
+        const BlockQuant q = block_params(mx);
+        // no loop: its one store would be hoisted out of it as a plain,
+        // temporal one
+        store4_i8<WHOLE>(a.codes + base, lane * 4, rest, quant_word(pk[0].x, pk[0].y, q));
+        if constexpr (W == 2)
+            store4_i8<WHOLE>(a.codes + base, 256 + lane * 4, rest,
+                             quant_word(pk[1].x, pk[1].y, q));
+        // the first lane of each quant block writes its scale
+        if (lane % L == 0 && lane * 4 < rest)
+            a.scales[base / B + lane * 4 / B] = q.scale;
+    }
+}
+
 // The gradient comes from `gs`: the fp32 array of the partition step
 // (F32Grad), or the int4 copies of the qgZ receive (I4Grad, zpp_i4grad.h).
 template <bool ADAMW, int B, class GS, bool QUANT = true>
-__global__ __launch_bounds__(kWave) void fused_kernel(FusedArgs a, GS gs) {
-    constexpr int C = B > 256 ? B : 256;  // elements per chunk (one wave)
-    constexpr int W = C / 256;            // float4 groups per lane
-    constexpr int L = B < 256 ? B / 4 : kWave;  // lanes per quant block
-    const int lane = threadIdx.x;
-    const size_t nchunks = (a.n + C - 1) / C;
-    for (size_t ch = xcd_grouped(blockIdx.x, gridDim.x, fused_xcd_run<GS>()); ch < nchunks;
-         ch += gridDim.x) {
-        const size_t base = ch * C;
-        const bool full = base + C <= a.n;
-        u32x2 pk[W];
-        u16x2 m2 = {0, 0};
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const size_t i = base + (size_t)w * 256 + (size_t)lane * 4;
-            if (full) {
-                f32x4 P = ld_nt(reinterpret_cast<const f32x4 *>(a.p + i));
-                f32x4 M = ld_nt(reinterpret_cast<const f32x4 *>(a.m + i));
-                f32x4 V = ld_nt(reinterpret_cast<const f32x4 *>(a.v + i));
-                const f32x4 G = grad_load4(gs, i);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float p = P[e], m = M[e], v = V[e];
-                    adam_update<ADAMW>(p, m, v, G[e], a.c);
-                    P[e] = p;
-                    M[e] = m;
-                    V[e] = v;
-                }
-                st_nt(reinterpret_cast<f32x4 *>(a.p + i), P);
-                st_nt(reinterpret_cast<f32x4 *>(a.m + i), M);
-                st_nt(reinterpret_cast<f32x4 *>(a.v + i), V);
-                pk[w] = u32x2{pack_bf16x2(P.x, P.y), pack_bf16x2(P.z, P.w)};
-                st_nt(reinterpret_cast<u32x2 *>(a.primary + i), pk[w]);
-                if (a.secondary)
-                    st_nt(reinterpret_cast<u32x2 *>(a.secondary + i), pk[w]);
-            } else {
-                // the last, partial chunk: element by element; absent elements
-                // hold bf16 zero, which no absmax can see
-                uint32_t h[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    h[e] = 0u;
-                    if (i + e < a.n) {
-                        float p = a.p[i + e], m = a.m[i + e], v = a.v[i + e];
-                        adam_update<ADAMW>(p, m, v, grad_at(gs, i + e), a.c);
-                        a.p[i + e] = p;
-                        a.m[i + e] = m;
-                        a.v[i + e] = v;
-                        h[e] = bf16_rne_bits(p);
-                        a.primary[i + e] = (uint16_t)h[e];
-                        if (a.secondary)
-                            a.secondary[i + e] = (uint16_t)h[e];
-                    }
-                }
-                pk[w] = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-            }
-            m2 = __builtin_elementwise_max(
-                m2, __builtin_elementwise_max(absbits2(pk[w].x), absbits2(pk[w].y)));
-        }
-        if constexpr (QUANT) {
-            uint32_t mx = max((uint32_t)m2.x, (uint32_t)m2.y);
-#pragma unroll
-            for (int off = L / 2; off >= 1; off >>= 1)
-                mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
-            const BlockQuant q = block_params(mx);
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                const size_t i = base + (size_t)w * 256 + (size_t)lane * 4;
-                const uint32_t c4 = quant_word(pk[w].x, pk[w].y, q);
-                if (full) {
-                    st_nt(reinterpret_cast<uint32_t *>(a.codes + i), c4);
-                } else {
-                    for (int e = 0; e < 4 && i + e < a.n; ++e)
-                        a.codes[i + e] = (int8_t)((c4 >> (8 * e)) & 0xFFu);
-                }
-            }
-            // the first lane of each quant block writes its scale
-            const size_t k = (base + (size_t)lane * 4) / B;
-            if (lane % L == 0 && k * B < a.n)
-                a.scales[k] = q.scale;
-        }
-    }
+__global__ __launch_bounds__(kWave) void fused_kernel(FusedArgs a, GS gs, TileSpan chunks) {
+    constexpr uint32_t C = B > 256 ? B : 256;
+    const uint32_t t = (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, fused_xcd_run<GS>());
+    const size_t base = (chunks.first + t) * C;
+    if (__builtin_expect(t < chunks.whole, 1))
+        fused_chunk<ADAMW, B, QUANT, true>(a, gs, base, C);
+    else
+        fused_chunk<ADAMW, B, QUANT, false>(a, gs, base, chunks.tail);
 }
 
 // Workgroups per CU for each gradient source.
@@ -168,16 +146,16 @@ template <> constexpr int fused_residency<I4GradIl>() { return ZPP_FUSED_RECV_IL
 
 template <int B, class GS, bool QUANT = true>
 void launch_fused_b(const FusedArgs &a, const GS &gs, hipStream_t stream) {
-    constexpr size_t C = B > 256 ? B : 256;
-    const size_t chunks = (a.n + C - 1) / C;
-    const unsigned grid = (unsigned)(chunks < ZPP_FUSED_MAX_GRID ? chunks : ZPP_FUSED_MAX_GRID);
+    constexpr uint32_t C = B > 256 ? B : 256;
     constexpr size_t lds = residency_lds(fused_residency<GS>());
-    if (a.c.adamw)
-        hipLaunchKernelGGL((fused_kernel<true, B, GS, QUANT>), dim3(grid), dim3(kWave), lds,
-                           stream, a, gs);
-    else
-        hipLaunchKernelGGL((fused_kernel<false, B, GS, QUANT>), dim3(grid), dim3(kWave), lds,
-                           stream, a, gs);
+    for_tiles(a.n, C, 1, kWave, [&](const TileSpan &chunks, unsigned grid) {
+        if (a.c.adamw)
+            hipLaunchKernelGGL((fused_kernel<true, B, GS, QUANT>), dim3(grid), dim3(kWave), lds,
+                               stream, a, gs, chunks);
+        else
+            hipLaunchKernelGGL((fused_kernel<false, B, GS, QUANT>), dim3(grid), dim3(kWave), lds,
+                               stream, a, gs, chunks);
+    });
 }
 
 template <class GS>

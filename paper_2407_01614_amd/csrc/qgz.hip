@@ -410,36 +410,31 @@ __global__ __launch_bounds__(kQgzThreads) void reduce_i4_scalar_kernel(ReduceArg
 // The reduction from a gradient source of zpp_i4grad.h: a lane holds G
 // groups of 4 consecutive elements at 256 t + 4 l of its wave's tile, as
 // above; each group is the source's gradient of those four elements, stored
-// as one float4 (1 KiB contiguous per wave store).  Partial tiles go element
-// by element.
+// as one float4 (1 KiB contiguous per wave store).
 template <class GS, int G>
-__global__ __launch_bounds__(kQgzThreads) void reduce_gs_kernel(GS gs, size_t n,
-                                                               float *__restrict__ out) {
+__global__ __launch_bounds__(kQgzThreads) void reduce_gs_kernel(GS gs, float *__restrict__ out,
+                                                               TileSpan tiles) {
     constexpr int kWaves = kQgzThreads / kWave;
     constexpr size_t C = 256 * G;
-    const size_t ntiles = (n + C - 1) / C;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    for (size_t tile = (size_t)blockIdx.x * kWaves + wave; tile < ntiles;
-         tile += (size_t)gridDim.x * kWaves) {
-        const size_t base = tile * C + (size_t)lane * 4;
-        if (tile * C + C <= n) {
-            f32x4 r[G];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t t = blockIdx.x * kWaves + wave;
+    const size_t base = (tiles.first + t) * C;
+    f32x4 r[G];
+    if (__builtin_expect(t < tiles.whole, 1)) {
 #pragma unroll
-            for (int g = 0; g < G; ++g)
-                r[g] = grad_load4(gs, base + (size_t)g * 256);
+        for (int g = 0; g < G; ++g)
+            r[g] = grad_load4<true>(gs, base, g * 256 + lane * 4, C);
 #pragma unroll
-            for (int g = 0; g < G; ++g)
-                st_nt(reinterpret_cast<f32x4 *>(out + base + (size_t)g * 256), r[g]);
-        } else {
+        for (int g = 0; g < G; ++g)
+            store4<true>(out + base, g * 256 + lane * 4, C, r[g]);
+    } else if (t == tiles.whole && tiles.tail) {
 #pragma unroll
-            for (int g = 0; g < G; ++g)
-                for (int e = 0; e < 4; ++e) {
-                    const size_t i = base + (size_t)g * 256 + e;
-                    if (i < n)
-                        out[i] = grad_at(gs, i);
-                }
-        }
+        for (int g = 0; g < G; ++g)
+            r[g] = grad_load4<false>(gs, base, g * 256 + lane * 4, tiles.tail);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            store4<false>(out + base, g * 256 + lane * 4, tiles.tail, r[g]);
     }
 }
 
@@ -563,13 +558,11 @@ hipError_t launch_dequant_reduce_i4_il(const uint8_t *codes, const float *scales
                                        bool vector_path, hipStream_t stream) {
     const I4GradIl gs = make_i4grad_il(codes, scales, num_src, block, scale_out);
     if (vector_path) {
-        constexpr size_t C = 256 * ZPP_QGZ_REDUCE_IL_GROUPS;
-        const size_t ntiles = (n + C - 1) / C;
-        const size_t waves = kQgzThreads / kWave;
-        const size_t need = (ntiles + waves - 1) / waves;
-        const unsigned grid = (unsigned)(need < ZPP_QGZ_MAX_GRID ? need : ZPP_QGZ_MAX_GRID);
-        hipLaunchKernelGGL((reduce_gs_kernel<I4GradIl, ZPP_QGZ_REDUCE_IL_GROUPS>), dim3(grid),
-                           dim3(kQgzThreads), 0, stream, gs, n, out);
+        for_tiles(n, 256 * ZPP_QGZ_REDUCE_IL_GROUPS, kQgzThreads / kWave, kQgzThreads,
+                  [&](const TileSpan &tiles, unsigned grid) {
+                      hipLaunchKernelGGL((reduce_gs_kernel<I4GradIl, ZPP_QGZ_REDUCE_IL_GROUPS>),
+                                         dim3(grid), dim3(kQgzThreads), 0, stream, gs, out, tiles);
+                  });
     } else {
         const size_t need = (n + kQgzThreads - 1) / kQgzThreads;
         const unsigned grid = (unsigned)(need < (1u << 20) ? need : (1u << 20));

@@ -40,9 +40,6 @@
 #ifndef ZPP_RECV_IL_RESIDENCY
 #define ZPP_RECV_IL_RESIDENCY 12
 #endif
-#ifndef ZPP_RECV_MAX_GRID
-#define ZPP_RECV_MAX_GRID (1u << 30)
-#endif
 
 namespace zpp {
 namespace {
@@ -58,6 +55,36 @@ struct RecvArgs {
     AdamConsts c;
 };
 
+// Runs of consecutive workgroups per XCD: grouped for the separate arrays
+// (zpp_i4grad.h), plain otherwise.
+template <class GS> constexpr size_t recv_xcd_run() { return 0; }
+template <> constexpr size_t recv_xcd_run<I4Grad>() { return kSeparateXcdRun; }
+
+template <bool ADAMW, bool WHOLE, class GS>
+__device__ __forceinline__ void recv_tile(const RecvArgs<GS> &a, size_t base, uint32_t rest) {
+    const uint32_t i = threadIdx.x * 4;
+    f32x4 P = load4<WHOLE>(a.p + base, i, rest);
+    f32x4 M = load4<WHOLE>(a.m + base, i, rest);
+    f32x4 V = load4<WHOLE>(a.v + base, i, rest);
+    const f32x4 G = grad_load4<WHOLE>(a.src, base, i, rest);
+    adam_update4<ADAMW>(P, M, V, G, a.c);
+    store4<WHOLE>(a.p + base, i, rest, P);
+    store4<WHOLE>(a.m + base, i, rest, M);
+    store4<WHOLE>(a.v + base, i, rest, V);
+    store4_bf16<WHOLE>(a.out + base, i, rest,
+                       u32x2{pack_bf16x2(P.x, P.y), pack_bf16x2(P.z, P.w)});
+}
+
+template <bool ADAMW, class GS>
+__global__ __launch_bounds__(kWave) void recv_adam_kernel(RecvArgs<GS> a, TileSpan tiles) {
+    const uint32_t t = (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, recv_xcd_run<GS>());
+    const size_t base = (tiles.first + t) * 256;
+    if (__builtin_expect(t < tiles.whole, 1))
+        recv_tile<ADAMW, true>(a, base, 256);
+    else
+        recv_tile<ADAMW, false>(a, base, tiles.tail);
+}
+
 template <bool ADAMW, class GS>
 __device__ __forceinline__ void scalar_step(const RecvArgs<GS> &a, size_t i) {
     const float g = grad_at(a.src, i);
@@ -67,47 +94,6 @@ __device__ __forceinline__ void scalar_step(const RecvArgs<GS> &a, size_t i) {
     a.m[i] = m;
     a.v[i] = v;
     a.out[i] = (uint16_t)bf16_rne_bits(p);
-}
-
-// Runs of consecutive workgroups per XCD: grouped for the separate arrays
-// (zpp_i4grad.h), plain otherwise.
-template <class GS> constexpr size_t recv_xcd_run() { return 0; }
-template <> constexpr size_t recv_xcd_run<I4Grad>() { return kSeparateXcdRun; }
-
-template <bool ADAMW, class GS>
-__global__ __launch_bounds__(kWave) void recv_adam_kernel(RecvArgs<GS> a) {
-    const size_t ntiles = (a.n + 255) / 256;
-    const int lane = threadIdx.x;
-    for (size_t t = xcd_grouped(blockIdx.x, gridDim.x, recv_xcd_run<GS>()); t < ntiles;
-         t += gridDim.x) {
-        const size_t i = t * 256 + (size_t)lane * 4;
-        if (t * 256 + 256 > a.n) {
-            // the last, partial tile: element by element
-            for (int e = 0; e < 4; ++e)
-                if (i + e < a.n)
-                    scalar_step<ADAMW, GS>(a, i + e);
-            continue;
-        }
-        f32x4 P = ld_nt(reinterpret_cast<const f32x4 *>(a.p + i));
-        f32x4 M = ld_nt(reinterpret_cast<const f32x4 *>(a.m + i));
-        f32x4 V = ld_nt(reinterpret_cast<const f32x4 *>(a.v + i));
-        const f32x4 G = grad_load4(a.src, i);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float p = P[e], m = M[e], v = V[e];
-            adam_update<ADAMW>(p, m, v, G[e], a.c);
-            P[e] = p;
-            M[e] = m;
-            V[e] = v;
-        }
-        st_nt(reinterpret_cast<f32x4 *>(a.p + i), P);
-        st_nt(reinterpret_cast<f32x4 *>(a.m + i), M);
-        st_nt(reinterpret_cast<f32x4 *>(a.v + i), V);
-        u32x2 o;
-        o.x = pack_bf16x2(P.x, P.y);
-        o.y = pack_bf16x2(P.z, P.w);
-        st_nt(reinterpret_cast<u32x2 *>(a.out + i), o);
-    }
 }
 
 // Any alignment: one element per thread, grid-stride.
@@ -122,15 +108,15 @@ template <class GS>
 hipError_t launch_recv(const RecvArgs<GS> &a, int residency, bool vector_path,
                        hipStream_t stream) {
     if (vector_path) {
-        const size_t tiles = (a.n + 255) / 256;
-        const unsigned grid = (unsigned)(tiles < ZPP_RECV_MAX_GRID ? tiles : ZPP_RECV_MAX_GRID);
         const size_t lds = residency_lds(residency);
-        if (a.c.adamw)
-            hipLaunchKernelGGL((recv_adam_kernel<true, GS>), dim3(grid), dim3(kWave), lds, stream,
-                               a);
-        else
-            hipLaunchKernelGGL((recv_adam_kernel<false, GS>), dim3(grid), dim3(kWave), lds,
-                               stream, a);
+        for_tiles(a.n, 256, 1, kWave, [&](const TileSpan &tiles, unsigned grid) {
+            if (a.c.adamw)
+                hipLaunchKernelGGL((recv_adam_kernel<true, GS>), dim3(grid), dim3(kWave), lds,
+                                   stream, a, tiles);
+            else
+                hipLaunchKernelGGL((recv_adam_kernel<false, GS>), dim3(grid), dim3(kWave), lds,
+                                   stream, a, tiles);
+        });
     } else {
         const size_t blocks = (a.n + kThreads - 1) / kThreads;
         const unsigned grid = (unsigned)(blocks < (1u << 20) ? blocks : (1u << 20));

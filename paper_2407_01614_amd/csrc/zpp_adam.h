@@ -26,4 +26,17 @@ __device__ __forceinline__ void adam_update(float &p, float &m, float &v, float 
     p = __builtin_fmaf(-c.step_size, m / denom, p);
 }
 
+template <bool ADAMW>
+__device__ __forceinline__ void adam_update4(f32x4 &P, f32x4 &M, f32x4 &V, const f32x4 &G,
+                                             const AdamConsts &c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float p = P[e], m = M[e], v = V[e];
+        adam_update<ADAMW>(p, m, v, G[e], c);
+        P[e] = p;
+        M[e] = m;
+        V[e] = v;
+    }
+}
+
 }  // namespace zpp

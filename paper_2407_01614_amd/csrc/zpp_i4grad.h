@@ -42,7 +42,7 @@ __device__ __forceinline__ float i4grad_scaled(float acc, float scale_out) {
     return acc * scale_out;
 }
 
-// The gradient of one element (tails and the any-alignment kernels).
+// The gradient of one element (the any-alignment kernels).
 __device__ __forceinline__ float i4grad_at(const I4Grad &s, size_t i) {
     float acc = 0.0f;
     for (uint32_t q = 0; q < s.num_src; ++q) {
@@ -53,17 +53,23 @@ __device__ __forceinline__ float i4grad_at(const I4Grad &s, size_t i) {
     return i4grad_scaled(acc, s.scale_out);
 }
 
-// The gradient of the four consecutive elements i .. i+3 (i a multiple of 4,
-// all four in range): one 2-byte code load and one scale per source, the
-// sources taken eight at a time with all eight loads in flight before their
-// fma passes, which keep the source order.  Whole batches of eight carry no
-// per-source test, so their loads issue back to back (the receive step at
-// the Llama-2-13B partition: 945 against 974 us, the dequant-reduce 259
-// against 270 us); a last partial batch tests each source.
+// The gradient of four consecutive elements, i .. i+3 of the tile of `rest`
+// elements at `base` (both multiples of 4, `base` the same for the whole
+// wave): one 2-byte code load and one scale per source, the sources taken
+// eight at a time with all eight loads in flight before their fma passes,
+// which keep the source order.  Whole batches of eight carry no per-source
+// test, so their loads issue back to back (the receive step at the
+// Llama-2-13B partition: 945 against 974 us, the dequant-reduce 259 against
+// 270 us); a last partial batch tests each source.
+// WHOLE: the tile lies inside the array; otherwise (the last, partial tile)
+// the group is clamped to the last one that starts inside and its second byte
+// to the array's last, so that a partial tile keeps the batches in flight
+// too; the values past the end are for the caller to drop.
 constexpr int kI4Batch = 8;
 
-template <bool FULL>
-__device__ __forceinline__ void i4grad_batch(float (&acc)[4], const I4Grad &s, size_t i, size_t k,
+template <bool FULL, bool WHOLE>
+__device__ __forceinline__ void i4grad_batch(float (&acc)[4], const I4Grad &s, size_t base_byte,
+                                             uint32_t byte0, uint32_t byte1, size_t k,
                                              uint32_t q0) {
     uint32_t w[kI4Batch];
     float sc[kI4Batch];
@@ -73,7 +79,11 @@ __device__ __forceinline__ void i4grad_batch(float (&acc)[4], const I4Grad &s, s
         w[j] = 0u;
         sc[j] = 0.0f;
         if (FULL || q < s.num_src) {
-            w[j] = ld_nt(reinterpret_cast<const uint16_t *>(s.codes[q] + i / 2));
+            const uint8_t *codes = s.codes[q] + base_byte;
+            if constexpr (WHOLE)
+                w[j] = ld_nt(reinterpret_cast<const uint16_t *>(codes + byte0));
+            else
+                w[j] = codes[byte0] | (uint32_t)codes[byte1] << 8;
             sc[j] = s.scales[q][k];
         }
     }
@@ -87,14 +97,24 @@ __device__ __forceinline__ void i4grad_batch(float (&acc)[4], const I4Grad &s, s
     }
 }
 
-__device__ __forceinline__ f32x4 i4grad_load4(const I4Grad &s, size_t i) {
+// start of the group of four that holds element i, or of the last group
+__device__ __forceinline__ uint32_t clamped_group(uint32_t i, uint32_t rest) {
+    return i < rest ? i : (rest - 1) & ~3u;
+}
+
+template <bool WHOLE>
+__device__ __forceinline__ f32x4 grad_load4(const I4Grad &s, size_t base, uint32_t i,
+                                            uint32_t rest) {
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    const size_t k = block_of(s.block, i);
+    if (!WHOLE)
+        i = clamped_group(i, rest);
+    const size_t k = block_of(s.block, base + i);
+    const uint32_t b0 = i / 2, b1 = WHOLE ? b0 + 1 : clamped(b0 + 1, (rest + 1) / 2);
     uint32_t q0 = 0;
     for (; q0 + kI4Batch <= s.num_src; q0 += kI4Batch)
-        i4grad_batch<true>(acc, s, i, k, q0);
+        i4grad_batch<true, WHOLE>(acc, s, base / 2, b0, b1, k, q0);
     if (q0 < s.num_src)
-        i4grad_batch<false>(acc, s, i, k, q0);
+        i4grad_batch<false, WHOLE>(acc, s, base / 2, b0, b1, k, q0);
     return f32x4{i4grad_scaled(acc[0], s.scale_out), i4grad_scaled(acc[1], s.scale_out),
                  i4grad_scaled(acc[2], s.scale_out), i4grad_scaled(acc[3], s.scale_out)};
 }
@@ -134,12 +154,14 @@ __device__ __forceinline__ float i4grad_at(const I4GradIl &s, size_t i) {
     return i4grad_scaled(acc, s.scale_out);
 }
 
-// The gradient of the four consecutive elements i .. i+3 (i a multiple of 4,
-// all four in range): the loads of the separate layout (a 2-byte code load
+// The gradient of four consecutive elements, i .. i+3 of the tile of `rest`
+// elements at `base`: the loads of the separate layout (a 2-byte code load
 // and a scale per source, sources eight at a time, all loads in flight before
 // the fma passes, which keep the source order), addressed in the interleaved
 // buffer: a wave's loads of one source are 128 contiguous bytes, and those of
-// all sources lie within one run of the buffer.
+// all sources lie within one run of the buffer.  A group that starts inside
+// the array lies inside the buffer whole (the buffer holds whole blocks), so
+// a partial tile only clamps the group.
 template <bool FULL>
 __device__ __forceinline__ void i4grad_il_batch(float (&acc)[4], const I4GradIl &s,
                                                 const uint8_t *base, size_t stride,
@@ -165,17 +187,20 @@ __device__ __forceinline__ void i4grad_il_batch(float (&acc)[4], const I4GradIl 
     }
 }
 
-__device__ __forceinline__ f32x4 i4grad_load4(const I4GradIl &s, size_t i) {
+template <bool WHOLE>
+__device__ __forceinline__ f32x4 grad_load4(const I4GradIl &s, size_t base, uint32_t i,
+                                            uint32_t rest) {
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    const size_t k = block_of(s.block, i);
-    const uint8_t *base = s.codes + il_code_byte(s, i, k, 0);
+    const size_t e = base + (WHOLE ? i : clamped_group(i, rest));
+    const size_t k = block_of(s.block, e);
+    const uint8_t *codes = s.codes + il_code_byte(s, e, k, 0);
     const size_t stride = s.block.block / 2;
-    const float *sbase = s.scales + k * s.num_src;
+    const float *scales = s.scales + k * s.num_src;
     uint32_t q0 = 0;
     for (; q0 + kI4Batch <= s.num_src; q0 += kI4Batch)
-        i4grad_il_batch<true>(acc, s, base, stride, sbase, q0);
+        i4grad_il_batch<true>(acc, s, codes, stride, scales, q0);
     if (q0 < s.num_src)
-        i4grad_il_batch<false>(acc, s, base, stride, sbase, q0);
+        i4grad_il_batch<false>(acc, s, codes, stride, scales, q0);
     return f32x4{i4grad_scaled(acc[0], s.scale_out), i4grad_scaled(acc[1], s.scale_out),
                  i4grad_scaled(acc[2], s.scale_out), i4grad_scaled(acc[3], s.scale_out)};
 }
@@ -186,19 +211,12 @@ struct F32Grad {
     const float *g;
 };
 
-__device__ __forceinline__ float grad_at(const F32Grad &s, size_t i) { return s.g[i]; }
-__device__ __forceinline__ f32x4 grad_load4(const F32Grad &s, size_t i) {
-    return ld_nt(reinterpret_cast<const f32x4 *>(s.g + i));
+template <bool WHOLE>
+__device__ __forceinline__ f32x4 grad_load4(const F32Grad &s, size_t base, uint32_t i,
+                                            uint32_t rest) {
+    return load4<WHOLE>(s.g + base, i, rest);
 }
 __device__ __forceinline__ float grad_at(const I4Grad &s, size_t i) { return i4grad_at(s, i); }
-__device__ __forceinline__ f32x4 grad_load4(const I4Grad &s, size_t i) {
-    return i4grad_load4(s, i);
-}
 __device__ __forceinline__ float grad_at(const I4GradIl &s, size_t i) { return i4grad_at(s, i); }
-__device__ __forceinline__ f32x4 grad_load4(const I4GradIl &s, size_t i) {
-    return i4grad_load4(s, i);
-}
-
-
 
 }  // namespace zpp

@@ -1,0 +1,127 @@
+"""GPU checks of the kernels' tile edges and dispatch rules: every result of a
+call equals, bit for bit, the one the same elements get from a call that takes
+another route (whole tiles, other alignment), and nothing past the end of an
+output is written.  The routes compared against are themselves checked against
+the oracle by the other GPU tests."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2407_01614_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+HP = dict(lr=1e-2, beta1=0.9, beta2=0.95, eps=1e-6, weight_decay=0.5)
+GUARD = 64
+
+
+@pytest.fixture(scope="module")
+def zpp():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2407_01614_amd import zpp as mod
+    return mod
+
+
+class Buf:
+    """`n` elements, `offset` elements into a buffer that goes on for GUARD
+    bytes behind them, filled with 0x5A."""
+
+    def __init__(self, n, dtype, offset=0, values=None):
+        self.size = torch.empty(0, dtype=dtype).element_size()
+        self.raw = torch.full(((n + offset) * self.size + GUARD,), 0x5A, dtype=torch.uint8,
+                              device="cuda")
+        self.end = (n + offset) * self.size
+        self.lo = offset * self.size
+        self.t = self.raw[:self.end].view(dtype)[offset:]
+        if values is not None:
+            self.t.copy_(torch.from_numpy(values)[:n])
+
+    def bits(self):
+        assert (self.raw[:self.lo] == 0x5A).all() and (self.raw[self.end:] == 0x5A).all(), \
+            "written outside the array"
+        return self.raw[self.lo:self.end].cpu().numpy()
+
+
+def state(n, full, offset=0):
+    p = synth.master_weights(full, 300)
+    m, v = synth.moments(full, 300)
+    return [Buf(n, torch.float32, offset, a) for a in (p, m, v)] + [Buf(n, torch.int16, offset)]
+
+
+def copies(zpp, full, k, block, interleaved):
+    """k int4 copies of `full` elements, as the interleaved buffer or as lists."""
+    x = [torch.from_numpy(synth.gradients(full, 301, q)).cuda() for q in range(k)]
+    if interleaved:
+        nc, ns = zpp.interleaved_sizes(full, block, k)
+        codes = torch.zeros(nc, dtype=torch.uint8, device="cuda")
+        scales = torch.zeros(ns, device="cuda")
+        for q in range(k):
+            zpp.quantize_blockwise_i4_interleaved(x[q], codes, scales, source=q, num_src=k,
+                                                  block=block)
+        return codes, scales
+    codes = [torch.zeros((full + 1) // 2, dtype=torch.uint8, device="cuda") for _ in range(k)]
+    scales = [torch.zeros(-(-full // block), device="cuda") for _ in range(k)]
+    for q in range(k):
+        zpp.quantize_blockwise_i4(x[q], codes[q], scales[q], block=block)
+    return codes, scales
+
+
+def receive(zpp, n, full, src, k, block, interleaved, single_pass, offset=0):
+    """The receive step of n elements from copies of `full`, into guarded
+    buffers: their bits, the int8 codes and scales last for the single pass."""
+    st = state(n, full, offset)
+    codes, scales = src
+    if not interleaved:  # exactly the bytes that n elements have
+        codes = [Buf((n + 1) // 2, torch.uint8, 0, c[:(n + 1) // 2].cpu().numpy()).t
+                 for c in codes]
+    args = [b.t for b in st[:3]] + [codes, scales] + ([k] if interleaved else []) + [st[3].t]
+    kw = dict(HP, step=3, scale_out=1.0 / k, n=n)
+    if not single_pass:
+        call = (zpp.qgz_receive_adam_step_interleaved if interleaved
+                else zpp.qgz_receive_adam_step)
+        call(*args, block=block, **kw)
+        return [b.bits() for b in st]
+    out = [Buf(n, torch.int16, offset), Buf(n, torch.int8, offset),
+           Buf(-(-n // 256), torch.float32)]
+    call = (zpp.qgz_receive_step_refresh_quantize_interleaved if interleaved
+            else zpp.qgz_receive_step_refresh_quantize)
+    call(*args, *[b.t for b in out], grad_block=block, block=256, **kw)
+    return [b.bits() for b in st + out]
+
+
+def same_start(got, ref, n, names):
+    for g, r, name in zip(got, ref, names):
+        assert np.array_equal(g, r[:g.size]), "%s at n = %d" % (name, n)
+
+
+NAMES = ("master", "exp_avg", "exp_avg_sq", "primary", "secondary")
+
+
+@pytest.mark.parametrize("interleaved", [False, True], ids=["separate", "interleaved"])
+@pytest.mark.parametrize("k,block", [(1, 64), (3, 256), (8, 192), (64, 512)])
+def test_partial_tiles(zpp, k, block, interleaved):
+    """A last tile that is not whole: each element as in a call of whole
+    tiles, and the int8 quantization of the short block as the quantizer
+    gives it for the primary that the pass wrote."""
+    full = 1024
+    src = copies(zpp, full, k, block, interleaved)
+    whole = receive(zpp, full, full, src, k, block, interleaved, False)
+    reduce = zpp.dequant_reduce_i4_interleaved if interleaved else zpp.dequant_reduce_i4
+    sum_args = (src[0], src[1]) + ((k,) if interleaved else ())
+    g = Buf(full, torch.float32)
+    reduce(*sum_args, full, g.t, block=block, scale_out=1.0 / k)
+    for n in (1, 2, 3, 5, 255, 257, 258, 259, 511, 512, 514, 767, 1021):
+        same_start(receive(zpp, n, full, src, k, block, interleaved, False), whole, n, NAMES)
+        got = receive(zpp, n, full, src, k, block, interleaved, True)
+        same_start(got[:4] + [got[4]], whole + [whole[3]], n, NAMES)
+        primary = torch.from_numpy(got[3].view(np.int16)).cuda()
+        codes, scales = Buf(n, torch.int8), Buf(-(-n // 256), torch.float32)
+        zpp.quantize_blockwise_i8(primary, codes.t, scales.t, block=256)
+        assert np.array_equal(got[5], codes.bits()) and np.array_equal(got[6], scales.bits()), n
+        s = Buf(n, torch.float32)
+        reduce(*sum_args, n, s.t, block=block, scale_out=1.0 / k)
+        same_start([s.bits()], [g.bits()], n, ("reduced",))
+        # the step from that gradient, and the pass with it
+        st = state(n, full)
+        zpp.adam_partition_step(*[b.t for b in st[:3]], s.t, st[3].t, step=3, **HP)
+        same_start([b.bits() for b in st], whole, n, NAMES)

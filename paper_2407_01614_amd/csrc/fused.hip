@@ -35,6 +35,8 @@
 // with 11, 1142 uncapped.  From one interleaved receive buffer
 // (ZPP_FUSED_RECV_IL_RESIDENCY): 1054 us with 14, 1062 with 16, 1075 with 12,
 // 1097 uncapped, against 1096 us from separate arrays in the same run.
+#include <type_traits>
+
 #include "zpp_adam.h"
 #include "zpp_chunk.h"
 #include "zpp_device.h"
@@ -51,7 +53,6 @@
 #ifndef ZPP_FUSED_RECV_IL_RESIDENCY
 #define ZPP_FUSED_RECV_IL_RESIDENCY 14
 #endif
-
 namespace zpp {
 namespace {
 
@@ -73,7 +74,7 @@ template <> constexpr size_t fused_xcd_run<I4Grad>() { return kSeparateXcdRun; }
 // One chunk of C consecutive elements from `base` on, `rest` of which lie
 // inside the arrays.  WHOLE: all of them; otherwise (the launch's last,
 // partial chunk) the absent elements hold bf16 zero, which no absmax can see.
-template <bool ADAMW, int B, bool QUANT, bool WHOLE, class GS>
+template <bool ADAMW, int B, bool QUANT, bool WHOLE, bool MANY, class GS>
 __device__ __forceinline__ void fused_chunk(const FusedArgs &a, const GS &gs, size_t base,
                                             uint32_t rest) {
     constexpr int C = B > 256 ? B : 256;  // elements per chunk (one wave)
@@ -81,20 +82,25 @@ __device__ __forceinline__ void fused_chunk(const FusedArgs &a, const GS &gs, si
     static_assert(W <= 2, "blocks of 64 to 512");
     constexpr int L = B < 256 ? B / 4 : kWave;  // lanes per quant block
     const uint32_t lane = threadIdx.x;
+    f32x4 P[W], M[W], V[W], G[W];
     u32x2 pk[W];
     u16x2 m2 = {0, 0};
 #pragma unroll
     for (int w = 0; w < W; ++w) {
         const uint32_t i = w * 256 + lane * 4;
-        f32x4 P = load4<WHOLE>(a.p + base, i, rest);
-        f32x4 M = load4<WHOLE>(a.m + base, i, rest);
-        f32x4 V = load4<WHOLE>(a.v + base, i, rest);
-        const f32x4 G = grad_load4<WHOLE>(gs, base, i, rest);
-        adam_update4<ADAMW>(P, M, V, G, a.c);
-        store4<WHOLE>(a.p + base, i, rest, P);
-        store4<WHOLE>(a.m + base, i, rest, M);
-        store4<WHOLE>(a.v + base, i, rest, V);
-        pk[w] = u32x2{pack_bf16x2(P.x, P.y), pack_bf16x2(P.z, P.w)};
+        P[w] = load4<WHOLE>(a.p + base, i, rest);
+        M[w] = load4<WHOLE>(a.m + base, i, rest);
+        V[w] = load4<WHOLE>(a.v + base, i, rest);
+    }
+    grad_tile<WHOLE, MANY>(G, gs, base, lane, rest);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const uint32_t i = w * 256 + lane * 4;
+        adam_update4<ADAMW>(P[w], M[w], V[w], G[w], a.c);
+        store4<WHOLE>(a.p + base, i, rest, P[w]);
+        store4<WHOLE>(a.m + base, i, rest, M[w]);
+        store4<WHOLE>(a.v + base, i, rest, V[w]);
+        pk[w] = u32x2{pack_bf16x2(P[w].x, P[w].y), pack_bf16x2(P[w].z, P[w].w)};
         if constexpr (!WHOLE) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -127,15 +133,15 @@ __device__ __forceinline__ void fused_chunk(const FusedArgs &a, const GS &gs, si
 
 // The gradient comes from `gs`: the fp32 array of the partition step
 // (F32Grad), or the int4 copies of the qgZ receive (I4Grad, zpp_i4grad.h).
-template <bool ADAMW, int B, class GS, bool QUANT = true>
+template <bool ADAMW, int B, class GS, bool QUANT, bool MANY>
 __global__ __launch_bounds__(kWave) void fused_kernel(FusedArgs a, GS gs, TileSpan chunks) {
     constexpr uint32_t C = B > 256 ? B : 256;
     const uint32_t t = (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, fused_xcd_run<GS>());
     const size_t base = (chunks.first + t) * C;
     if (__builtin_expect(t < chunks.whole, 1))
-        fused_chunk<ADAMW, B, QUANT, true>(a, gs, base, C);
+        fused_chunk<ADAMW, B, QUANT, true, MANY>(a, gs, base, C);
     else
-        fused_chunk<ADAMW, B, QUANT, false>(a, gs, base, chunks.tail);
+        fused_chunk<ADAMW, B, QUANT, false, MANY>(a, gs, base, chunks.tail);
 }
 
 // Workgroups per CU for each gradient source.
@@ -144,18 +150,30 @@ template <> constexpr int fused_residency<F32Grad>() { return ZPP_FUSED_RESIDENC
 template <> constexpr int fused_residency<I4Grad>() { return ZPP_FUSED_RECV_RESIDENCY; }
 template <> constexpr int fused_residency<I4GradIl>() { return ZPP_FUSED_RECV_IL_RESIDENCY; }
 
-template <int B, class GS, bool QUANT = true>
-void launch_fused_b(const FusedArgs &a, const GS &gs, hipStream_t stream) {
+template <int B, bool QUANT, bool MANY, class GS>
+void launch_fused_chunks(const FusedArgs &a, const GS &gs, int residency, hipStream_t stream) {
     constexpr uint32_t C = B > 256 ? B : 256;
-    constexpr size_t lds = residency_lds(fused_residency<GS>());
+    const size_t lds = residency_lds(residency);
     for_tiles(a.n, C, 1, kWave, [&](const TileSpan &chunks, unsigned grid) {
         if (a.c.adamw)
-            hipLaunchKernelGGL((fused_kernel<true, B, GS, QUANT>), dim3(grid), dim3(kWave), lds,
-                               stream, a, gs, chunks);
+            hipLaunchKernelGGL((fused_kernel<true, B, GS, QUANT, MANY>), dim3(grid), dim3(kWave),
+                               lds, stream, a, gs, chunks);
         else
-            hipLaunchKernelGGL((fused_kernel<false, B, GS, QUANT>), dim3(grid), dim3(kWave), lds,
-                               stream, a, gs, chunks);
+            hipLaunchKernelGGL((fused_kernel<false, B, GS, QUANT, MANY>), dim3(grid), dim3(kWave),
+                               lds, stream, a, gs, chunks);
     });
+}
+
+template <int B, bool QUANT = true, class GS>
+void launch_fused_b(const FusedArgs &a, const GS &gs, hipStream_t stream) {
+    int residency = fused_residency<GS>();
+    if constexpr (!std::is_same_v<GS, F32Grad>) {
+        if (gs.num_src >= kManySources)
+            residency = 0;  // left to the hardware (zpp_i4grad.h)
+        if (many_sources(gs.num_src, gs.block))
+            return launch_fused_chunks<B, QUANT, true>(a, gs, residency, stream);
+    }
+    launch_fused_chunks<B, QUANT, false>(a, gs, residency, stream);
 }
 
 template <class GS>
@@ -169,7 +187,7 @@ hipError_t launch_fused_gs(const FusedArgs &a, const GS &gs, uint32_t block,
     default: {
         // the step and its copies in one pass, then the quantization of
         // the primary it wrote (stream order)
-        launch_fused_b<256, GS, false>(a, gs, stream);
+        launch_fused_b<256, false>(a, gs, stream);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;

@@ -14,9 +14,9 @@
 // sources' pointers travel by value in the kernel arguments; a lane
 // accumulates its elements over the sources in order, one fma each.
 //
-// The dequant-reduce also reads the P copies from one interleaved receive
-// buffer (layout in zpp_i4grad.h): the gradient source of the receive
-// kernels forms each float4, so the bits are those of the separate arrays.
+// The dequant-reduce is one kernel over the gradient sources of the receive
+// kernels (zpp_i4grad.h): the P copies as separate arrays or in one
+// interleaved receive buffer, with the same bits.
 //
 // Blocks may be any multiple of 64 up to 4096; for those that are not powers
 // of two the quantizer gives each block an aligned group of 16 to 64 lanes
@@ -39,12 +39,6 @@
 #endif
 #ifndef ZPP_QGZ_QUANT_UNROLL
 #define ZPP_QGZ_QUANT_UNROLL 4
-#endif
-#ifndef ZPP_QGZ_REDUCE_GROUPS
-#define ZPP_QGZ_REDUCE_GROUPS 2
-#endif
-#ifndef ZPP_QGZ_REDUCE_IL_GROUPS
-#define ZPP_QGZ_REDUCE_IL_GROUPS 2
 #endif
 // Shape of the quantizer for blocks that are not powers of two
 // (zpp_chunk.h): at least three slots per lane, and the widest lane group
@@ -304,134 +298,34 @@ __global__ __launch_bounds__(kQgzThreads) void quant_i4_scalar_kernel(
     }
 }
 
-struct ReduceArgs {
-    const uint8_t *codes[kMaxShards];
-    const float *scales[kMaxShards];
-    uint32_t num_src;
-    size_t n;
-    BlockDiv block;
-    float scale_out;
-    float *out;
-};
+// The dequant-reduce, from either gradient source of zpp_i4grad.h: a lane
+// holds G groups of 4 consecutive elements at 256 g + 4 l of its wave's tile,
+// so each source is read as 128-byte contiguous wave loads (2 bytes per lane)
+// and every group is stored as one float4 (1 KiB contiguous per wave store).
+// From separate arrays workgroups are renumbered in runs per XCD
+// (kSeparateXcdRun), so that the tiles sharing a line of a source's scales
+// read it through one L2.
+template <class GS> constexpr size_t reduce_xcd_run() { return 0; }
+template <> constexpr size_t reduce_xcd_run<I4Grad>() { return kSeparateXcdRun; }
 
-// A lane holds G groups of 4 consecutive elements; group t of lane l in a
-// wave's tile starts at 256 t + 4 l, so each source is read as 128-byte
-// contiguous wave loads (2 bytes per lane) and every store of the wave
-// writes 1 KiB contiguously.  Sources are taken eight at a time, all their
-// loads in flight before the fma passes, which keep the order q = 0, 1, ...
-// Workgroups are renumbered in runs per XCD (kSeparateXcdRun), so that the
-// tiles sharing a line of a source's scales read it through one L2.
-template <int G>
-__global__ __launch_bounds__(kQgzThreads) void reduce_i4_kernel(ReduceArgs a) {
-    constexpr int kBatch = 8;
-    constexpr int kWaves = kQgzThreads / kWave;
-    constexpr size_t C = 256 * G;
-    const size_t ntiles = (a.n + C - 1) / C;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const size_t wg = xcd_grouped(blockIdx.x, gridDim.x, kSeparateXcdRun);
-    for (size_t tile = wg * kWaves + wave; tile < ntiles;
-         tile += (size_t)gridDim.x * kWaves) {
-        const size_t base = tile * C + (size_t)lane * 4;
-        const bool full = tile * C + C <= a.n;
-        float acc[G][4];
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                acc[g][e] = 0.0f;
-        for (uint32_t q0 = 0; q0 < a.num_src; q0 += kBatch) {
-            uint32_t w[kBatch][G];
-            float s[kBatch][G];
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                const uint32_t q = q0 + j;
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const size_t i = base + (size_t)g * 256;
-                    w[j][g] = 0;
-                    s[j][g] = 0.0f;
-                    if (q < a.num_src) {
-                        if (full) {
-                            w[j][g] = ld_nt(reinterpret_cast<const uint16_t *>(a.codes[q] + i / 2));
-                        } else {
-                            if (i < a.n)
-                                w[j][g] = a.codes[q][i / 2];
-                            if (i + 2 < a.n)
-                                w[j][g] |= (uint32_t)a.codes[q][i / 2 + 1] << 8;
-                        }
-                        if (i < a.n)
-                            s[j][g] = a.scales[q][block_of(a.block, i)];
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                if (q0 + j < a.num_src) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            acc[g][e] = __builtin_fmaf(i4_code(w[j][g], e), s[j][g], acc[g][e]);
-                }
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const size_t i = base + (size_t)g * 256;
-            if (full) {
-                st_nt(reinterpret_cast<f32x4 *>(a.out + i),
-                      f32x4{acc[g][0] * a.scale_out, acc[g][1] * a.scale_out,
-                            acc[g][2] * a.scale_out, acc[g][3] * a.scale_out});
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (i + e < a.n)
-                        a.out[i + e] = acc[g][e] * a.scale_out;
-            }
-        }
-    }
-}
-
-// Any alignment: one element per thread.
-__global__ __launch_bounds__(kQgzThreads) void reduce_i4_scalar_kernel(ReduceArgs a) {
-    for (size_t i = (size_t)blockIdx.x * kQgzThreads + threadIdx.x; i < a.n;
-         i += (size_t)gridDim.x * kQgzThreads) {
-        float acc = 0.0f;
-        for (uint32_t q = 0; q < a.num_src; ++q) {
-            const uint32_t byte = a.codes[q][i / 2];
-            const uint32_t nib = (i % 2 == 0) ? (byte & 0xFu) : (byte >> 4);
-            acc = __builtin_fmaf(i4_code(nib, 0), a.scales[q][block_of(a.block, i)], acc);
-        }
-        a.out[i] = acc * a.scale_out;
-    }
-}
-
-// The reduction from a gradient source of zpp_i4grad.h: a lane holds G
-// groups of 4 consecutive elements at 256 t + 4 l of its wave's tile, as
-// above; each group is the source's gradient of those four elements, stored
-// as one float4 (1 KiB contiguous per wave store).
-template <class GS, int G>
+template <class GS, int G, bool MANY>
 __global__ __launch_bounds__(kQgzThreads) void reduce_gs_kernel(GS gs, float *__restrict__ out,
                                                                TileSpan tiles) {
     constexpr int kWaves = kQgzThreads / kWave;
     constexpr size_t C = 256 * G;
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t t = blockIdx.x * kWaves + wave;
+    const uint32_t t = (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, reduce_xcd_run<GS>()) * kWaves +
+                       wave;
     const size_t base = (tiles.first + t) * C;
     f32x4 r[G];
     if (__builtin_expect(t < tiles.whole, 1)) {
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-            r[g] = grad_load4<true>(gs, base, g * 256 + lane * 4, C);
+        grad_tile<true, MANY>(r, gs, base, lane, C);
 #pragma unroll
         for (int g = 0; g < G; ++g)
             store4<true>(out + base, g * 256 + lane * 4, C, r[g]);
     } else if (t == tiles.whole && tiles.tail) {
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-            r[g] = grad_load4<false>(gs, base, g * 256 + lane * 4, tiles.tail);
+        grad_tile<false, MANY>(r, gs, base, lane, tiles.tail);
 #pragma unroll
         for (int g = 0; g < G; ++g)
             store4<false>(out + base, g * 256 + lane * 4, tiles.tail, r[g]);
@@ -445,6 +339,37 @@ __global__ __launch_bounds__(kQgzThreads) void reduce_gs_scalar_kernel(GS gs, si
     for (size_t i = (size_t)blockIdx.x * kQgzThreads + threadIdx.x; i < n;
          i += (size_t)gridDim.x * kQgzThreads)
         out[i] = grad_at(gs, i);
+}
+
+template <int G, bool MANY, class GS>
+void launch_reduce_gs(const GS &gs, size_t n, float *out, hipStream_t stream) {
+    for_tiles(n, 256 * G, kQgzThreads / kWave, kQgzThreads,
+              [&](const TileSpan &tiles, unsigned grid) {
+                  hipLaunchKernelGGL((reduce_gs_kernel<GS, G, MANY>), dim3(grid),
+                                     dim3(kQgzThreads), 0, stream, gs, out, tiles);
+              });
+}
+
+// MANY sources: two groups per lane stream better (13.1 M elements of 16
+// separate copies: 32.9 against 35.4 us, 50 M: 117 against 127), one puts a
+// short array on more waves (500,000 elements: 3.1 against 4.1 us): two from
+// the length that gives every CU its 32 waves.  Fewer sources keep two.
+template <class GS>
+hipError_t launch_reduce(const GS &gs, size_t n, float *out, bool vector_path,
+                         hipStream_t stream) {
+    if (!vector_path) {
+        const size_t need = (n + kQgzThreads - 1) / kQgzThreads;
+        const unsigned grid = (unsigned)(need < (1u << 20) ? need : (1u << 20));
+        hipLaunchKernelGGL(reduce_gs_scalar_kernel<GS>, dim3(grid), dim3(kQgzThreads), 0, stream,
+                           gs, n, out);
+    } else if (!many_sources(gs.num_src, gs.block)) {
+        launch_reduce_gs<2, false>(gs, n, out, stream);
+    } else if (n >= (size_t)512 * 32 * kCUs) {
+        launch_reduce_gs<2, true>(gs, n, out, stream);
+    } else {
+        launch_reduce_gs<1, true>(gs, n, out, stream);
+    }
+    return hipGetLastError();
 }
 
 template <int B>
@@ -527,49 +452,15 @@ hipError_t launch_dequant_reduce_i4(const uint8_t *const *src_codes,
                                     const float *const *src_scales, uint32_t num_src, size_t n,
                                     uint32_t block, float scale_out, float *out,
                                     bool vector_path, hipStream_t stream) {
-    ReduceArgs a = {};
-    for (uint32_t q = 0; q < num_src; ++q) {
-        a.codes[q] = src_codes[q];
-        a.scales[q] = src_scales[q];
-    }
-    a.num_src = num_src;
-    a.n = n;
-    a.block = make_block_div(block);
-    a.scale_out = scale_out;
-    a.out = out;
-    if (vector_path) {
-        constexpr size_t C = 256 * ZPP_QGZ_REDUCE_GROUPS;
-        const size_t ntiles = (n + C - 1) / C;
-        const size_t waves = kQgzThreads / kWave;
-        const size_t need = (ntiles + waves - 1) / waves;
-        const unsigned grid = (unsigned)(need < ZPP_QGZ_MAX_GRID ? need : ZPP_QGZ_MAX_GRID);
-        hipLaunchKernelGGL((reduce_i4_kernel<ZPP_QGZ_REDUCE_GROUPS>), dim3(grid),
-                           dim3(kQgzThreads), 0, stream, a);
-    } else {
-        const size_t need = (n + kQgzThreads - 1) / kQgzThreads;
-        const unsigned grid = (unsigned)(need < (1u << 20) ? need : (1u << 20));
-        hipLaunchKernelGGL(reduce_i4_scalar_kernel, dim3(grid), dim3(kQgzThreads), 0, stream, a);
-    }
-    return hipGetLastError();
+    return launch_reduce(make_i4grad(src_codes, src_scales, num_src, block, scale_out), n, out,
+                         vector_path, stream);
 }
 
 hipError_t launch_dequant_reduce_i4_il(const uint8_t *codes, const float *scales, uint32_t num_src,
                                        size_t n, uint32_t block, float scale_out, float *out,
                                        bool vector_path, hipStream_t stream) {
-    const I4GradIl gs = make_i4grad_il(codes, scales, num_src, block, scale_out);
-    if (vector_path) {
-        for_tiles(n, 256 * ZPP_QGZ_REDUCE_IL_GROUPS, kQgzThreads / kWave, kQgzThreads,
-                  [&](const TileSpan &tiles, unsigned grid) {
-                      hipLaunchKernelGGL((reduce_gs_kernel<I4GradIl, ZPP_QGZ_REDUCE_IL_GROUPS>),
-                                         dim3(grid), dim3(kQgzThreads), 0, stream, gs, out, tiles);
-                  });
-    } else {
-        const size_t need = (n + kQgzThreads - 1) / kQgzThreads;
-        const unsigned grid = (unsigned)(need < (1u << 20) ? need : (1u << 20));
-        hipLaunchKernelGGL(reduce_gs_scalar_kernel<I4GradIl>, dim3(grid), dim3(kQgzThreads), 0,
-                           stream, gs, n, out);
-    }
-    return hipGetLastError();
+    return launch_reduce(make_i4grad_il(codes, scales, num_src, block, scale_out), n, out,
+                         vector_path, stream);
 }
 
 }  // namespace zpp

@@ -40,7 +40,6 @@
 #ifndef ZPP_RECV_IL_RESIDENCY
 #define ZPP_RECV_IL_RESIDENCY 12
 #endif
-
 namespace zpp {
 namespace {
 
@@ -60,14 +59,15 @@ struct RecvArgs {
 template <class GS> constexpr size_t recv_xcd_run() { return 0; }
 template <> constexpr size_t recv_xcd_run<I4Grad>() { return kSeparateXcdRun; }
 
-template <bool ADAMW, bool WHOLE, class GS>
+template <bool ADAMW, bool WHOLE, bool MANY, class GS>
 __device__ __forceinline__ void recv_tile(const RecvArgs<GS> &a, size_t base, uint32_t rest) {
     const uint32_t i = threadIdx.x * 4;
     f32x4 P = load4<WHOLE>(a.p + base, i, rest);
     f32x4 M = load4<WHOLE>(a.m + base, i, rest);
     f32x4 V = load4<WHOLE>(a.v + base, i, rest);
-    const f32x4 G = grad_load4<WHOLE>(a.src, base, i, rest);
-    adam_update4<ADAMW>(P, M, V, G, a.c);
+    f32x4 G[1];
+    grad_tile<WHOLE, MANY>(G, a.src, base, threadIdx.x, rest);
+    adam_update4<ADAMW>(P, M, V, G[0], a.c);
     store4<WHOLE>(a.p + base, i, rest, P);
     store4<WHOLE>(a.m + base, i, rest, M);
     store4<WHOLE>(a.v + base, i, rest, V);
@@ -75,14 +75,14 @@ __device__ __forceinline__ void recv_tile(const RecvArgs<GS> &a, size_t base, ui
                        u32x2{pack_bf16x2(P.x, P.y), pack_bf16x2(P.z, P.w)});
 }
 
-template <bool ADAMW, class GS>
+template <bool ADAMW, bool MANY, class GS>
 __global__ __launch_bounds__(kWave) void recv_adam_kernel(RecvArgs<GS> a, TileSpan tiles) {
     const uint32_t t = (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, recv_xcd_run<GS>());
     const size_t base = (tiles.first + t) * 256;
     if (__builtin_expect(t < tiles.whole, 1))
-        recv_tile<ADAMW, true>(a, base, 256);
+        recv_tile<ADAMW, true, MANY>(a, base, 256);
     else
-        recv_tile<ADAMW, false>(a, base, tiles.tail);
+        recv_tile<ADAMW, false, MANY>(a, base, tiles.tail);
 }
 
 template <bool ADAMW, class GS>
@@ -104,19 +104,29 @@ __global__ __launch_bounds__(kThreads) void recv_adam_scalar_kernel(RecvArgs<GS>
         scalar_step<ADAMW, GS>(a, i);
 }
 
+template <bool MANY, class GS>
+void launch_recv_tiles(const RecvArgs<GS> &a, int residency, hipStream_t stream) {
+    const size_t lds = residency_lds(residency);
+    for_tiles(a.n, 256, 1, kWave, [&](const TileSpan &tiles, unsigned grid) {
+        if (a.c.adamw)
+            hipLaunchKernelGGL((recv_adam_kernel<true, MANY, GS>), dim3(grid), dim3(kWave), lds,
+                               stream, a, tiles);
+        else
+            hipLaunchKernelGGL((recv_adam_kernel<false, MANY, GS>), dim3(grid), dim3(kWave), lds,
+                               stream, a, tiles);
+    });
+}
+
 template <class GS>
 hipError_t launch_recv(const RecvArgs<GS> &a, int residency, bool vector_path,
                        hipStream_t stream) {
     if (vector_path) {
-        const size_t lds = residency_lds(residency);
-        for_tiles(a.n, 256, 1, kWave, [&](const TileSpan &tiles, unsigned grid) {
-            if (a.c.adamw)
-                hipLaunchKernelGGL((recv_adam_kernel<true, GS>), dim3(grid), dim3(kWave), lds,
-                                   stream, a, tiles);
-            else
-                hipLaunchKernelGGL((recv_adam_kernel<false, GS>), dim3(grid), dim3(kWave), lds,
-                                   stream, a, tiles);
-        });
+        if (a.src.num_src >= kManySources)
+            residency = 0;  // left to the hardware (zpp_i4grad.h)
+        if (many_sources(a.src.num_src, a.src.block))
+            launch_recv_tiles<true>(a, residency, stream);
+        else
+            launch_recv_tiles<false>(a, residency, stream);
     } else {
         const size_t blocks = (a.n + kThreads - 1) / kThreads;
         const unsigned grid = (unsigned)(blocks < (1u << 20) ? blocks : (1u << 20));

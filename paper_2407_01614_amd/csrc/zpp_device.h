@@ -53,6 +53,7 @@ __device__ __forceinline__ size_t block_of(const BlockDiv &d, size_t i) {
 // holds at most kLdsPerCU / residency_lds(k) = k such workgroups, and the
 // dispatcher still hands out the one-shot grid as workgroups retire.
 // residency_lds(0) = 0 leaves residency to the hardware.
+constexpr size_t kCUs = 256;              // CUs of an MI355X
 constexpr size_t kLdsPerCU = 160 * 1024;  // LDS of one gfx950 CU
 constexpr size_t residency_lds(int workgroups_per_cu) {
     return workgroups_per_cu <= 0 ? 0 : (kLdsPerCU / workgroups_per_cu) / 1024 * 1024;

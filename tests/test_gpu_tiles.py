@@ -98,7 +98,7 @@ NAMES = ("master", "exp_avg", "exp_avg_sq", "primary", "secondary")
 
 
 @pytest.mark.parametrize("interleaved", [False, True], ids=["separate", "interleaved"])
-@pytest.mark.parametrize("k,block", [(1, 64), (3, 256), (8, 192), (64, 512)])
+@pytest.mark.parametrize("k,block", [(1, 64), (3, 256), (8, 192), (19, 256), (64, 512)])
 def test_partial_tiles(zpp, k, block, interleaved):
     """A last tile that is not whole: each element as in a call of whole
     tiles, and the int8 quantization of the short block as the quantizer
@@ -125,3 +125,41 @@ def test_partial_tiles(zpp, k, block, interleaved):
         st = state(n, full)
         zpp.adam_partition_step(*[b.t for b in st[:3]], s.t, st[3].t, step=3, **HP)
         same_start([b.bits() for b in st], whole, n, NAMES)
+
+
+@pytest.mark.parametrize("interleaved", [False, True], ids=["separate", "interleaved"])
+@pytest.mark.parametrize("k,n,block", [(15, 1029, 256), (16, 1029, 256), (23, 1029, 512),
+                                       (31, 1029, 256), (33, 1029, 768), (45, 1029, 192),
+                                       (63, 1029, 256), (16, 4194304 + 258, 256),
+                                       (5, 2053, 256), (6, 2053, 320), (7, 2053, 256)])
+def test_source_counts(zpp, k, n, block, interleaved):
+    """Every batch length of the int4 sources, below and from the count that
+    takes the many-source form, against the oracle bit for bit; scales that
+    are zero, subnormal, huge, infinite and NaN among them."""
+    import oracle
+    codes = [synth.rng(302, 0, q).integers(0, 256, (n + 1) // 2, dtype=np.uint8)
+             for q in range(k)]
+    nb = -(-n // block)
+    scales = [synth.random_scales(nb, 303, q) for q in range(k)]
+    for q, bad in enumerate((0.0, 1e-45, 3e38, np.inf, np.nan)):
+        scales[q % k][min(q, nb - 1)] = bad
+    ref = oracle.dequant_reduce_i4(codes, scales, n, block, 1.0 / 3.0)
+    out = Buf(n, torch.float32)
+    if interleaved:
+        c = np.zeros((nb, k, block // 2), np.uint8)
+        for q in range(k):
+            flat = np.zeros(nb * block // 2, np.uint8)
+            flat[:codes[q].size] = codes[q]
+            c[:, q] = flat.reshape(nb, -1)
+        zpp.dequant_reduce_i4_interleaved(
+            torch.from_numpy(c.reshape(-1)).cuda(),
+            torch.from_numpy(np.stack(scales, 1).reshape(-1)).cuda(), k, n, out.t, block=block,
+            scale_out=float(np.float32(1.0 / 3.0)))
+    else:
+        zpp.dequant_reduce_i4([torch.from_numpy(c).cuda() for c in codes],
+                              [torch.from_numpy(s).cuda() for s in scales], n, out.t, block=block,
+                              scale_out=float(np.float32(1.0 / 3.0)))
+    got = out.bits().view(np.float32)
+    nan = np.isnan(ref)
+    assert nan.any() and np.array_equal(nan, np.isnan(got))
+    assert np.array_equal(got[~nan].view(np.uint32), ref[~nan].view(np.uint32))

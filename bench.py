@@ -83,20 +83,18 @@ def parse():
 
 # The sources each kernel is built from: a counter figure in the traffic file
 # is reported only while their digest still matches.
-_COMMON = ["zpp_device.h", "zpp_launch.h"]
+_COMMON = ["zpp_device.h", "zpp_launch.h", "zpp_chunk.h"]
 TRAFFIC_SOURCES = {
     "adam": ["adam.hip", "zpp_adam.h"] + _COMMON,
     "refresh": ["refresh.hip"] + _COMMON,
-    "quant": ["quant.hip", "zpp_quant.h", "zpp_chunk.h"] + _COMMON,
-    "refresh_quant": ["quant.hip", "zpp_quant.h", "zpp_chunk.h"] + _COMMON,
+    "quant": ["quant.hip", "zpp_quant.h"] + _COMMON,
+    "refresh_quant": ["quant.hip", "zpp_quant.h"] + _COMMON,
     "gather": ["gather.hip"] + _COMMON,
-    "fused": ["fused.hip", "zpp_adam.h", "zpp_quant.h", "zpp_i4grad.h", "zpp_chunk.h"] + _COMMON,
-    "quant_i4": ["qgz.hip", "zpp_quant.h", "zpp_i4grad.h", "zpp_chunk.h"] + _COMMON,
-    "reduce_i4": ["qgz.hip", "zpp_i4grad.h", "zpp_quant.h", "zpp_chunk.h"] + _COMMON,
-    "receive_adam": ["receive_adam.hip", "zpp_adam.h", "zpp_quant.h", "zpp_i4grad.h",
-                     "zpp_chunk.h"] + _COMMON,
-    "fused_receive": ["fused.hip", "zpp_adam.h", "zpp_quant.h", "zpp_i4grad.h",
-                      "zpp_chunk.h"] + _COMMON,
+    "fused": ["fused.hip", "zpp_adam.h", "zpp_quant.h", "zpp_i4grad.h"] + _COMMON,
+    "quant_i4": ["qgz.hip", "zpp_quant.h", "zpp_i4grad.h"] + _COMMON,
+    "reduce_i4": ["qgz.hip", "zpp_i4grad.h", "zpp_quant.h"] + _COMMON,
+    "receive_adam": ["receive_adam.hip", "zpp_adam.h", "zpp_quant.h", "zpp_i4grad.h"] + _COMMON,
+    "fused_receive": ["fused.hip", "zpp_adam.h", "zpp_quant.h", "zpp_i4grad.h"] + _COMMON,
 }
 
 

@@ -31,6 +31,8 @@
  *     a NULL event means "no event".
  *   - Validation is synchronous and happens before anything is enqueued; on
  *     any validation error nothing is enqueued (no kernel, no event).
+ *   - Pointers need the alignment of their elements and no more; every call
+ *     is fastest when its outputs start on 128-byte lines.
  *   - A size of 0 is a valid no-op that still honours the wait events and
  *     records `done_after`, so a waiter never hangs.
  *   - If the HIP runtime rejects a launch, the call returns ZPP_EHIP and
@@ -90,8 +92,7 @@ typedef struct {
  *   arrays).  grad: float[n], read only.  primary_bf16: uint16_t[n] out, the
  *   rank's slice of the layer the forward AllGather(L, P) assembles.
  * None of the five ranges may overlap another (ZPP_EOVERLAP).  Pointers must
- * be aligned to their element size (ZPP_EALIGN); 16-byte alignment of all
- * five selects the vector kernel.  hp must be non-NULL. */
+ * be aligned to their element size (ZPP_EALIGN).  hp must be non-NULL. */
 ZPP_API zpp_status zpp_adam_partition_step(float *master, float *exp_avg, float *exp_avg_sq,
                                            const float *grad, uint16_t *primary_bf16, size_t n,
                                            const zpp_adam_hparams *hp, hipStream_t stream);
@@ -122,7 +123,7 @@ ZPP_API zpp_status zpp_refresh_secondary(uint16_t *secondary_bf16, const uint16_
  * out.  block: a multiple of 64 in [64, 4096], else ZPP_EINVAL.
  * Order on `stream`: wait `wait_before`, quantize, record `done_after`.
  * No two of the three ranges may overlap (ZPP_EOVERLAP).  Alignment: src 2,
- * scales 4 (ZPP_EALIGN); src 16 and codes 8 bytes select the vector kernel. */
+ * scales 4 (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_quantize_blockwise_i8(const uint16_t *src_bf16, size_t n, uint32_t block,
                                              int8_t *codes, float *scales, hipStream_t stream,
                                              hipEvent_t wait_before, hipEvent_t done_after);
@@ -140,8 +141,7 @@ ZPP_API zpp_status zpp_quantize_blockwise_i8(const uint16_t *src_bf16, size_t n,
  * quantize, record `done_after`, which the gather of these codes must wait
  * on (the paper's fix).  No two of the four ranges may overlap
  * (ZPP_EOVERLAP).  Alignment: secondary and src 2 bytes, scales 4
- * (ZPP_EALIGN); src and secondary 16 and codes 8 bytes select the vector
- * kernel. */
+ * (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_refresh_quantize_i8(uint16_t *secondary_bf16, const uint16_t *src_bf16,
                                            size_t n, uint32_t block, int8_t *codes, float *scales,
                                            hipStream_t stream, hipEvent_t wait_before,
@@ -166,11 +166,7 @@ ZPP_API zpp_status zpp_refresh_quantize_i8(uint16_t *secondary_bf16, const uint1
  * Order on `stream`: wait `wait_before`, run, record `done_after` (the event
  * a gather of the codes waits on).
  * No two ranges may overlap (ZPP_EOVERLAP).  Alignment: floats 4, bf16 2
- * bytes (ZPP_EALIGN); 16-byte fp32 arrays, 8-byte bf16 arrays and 4-byte
- * codes select the single-pass kernel (for the two-kernel blocks, the
- * quantization's vector kernel further needs a 16-byte primary_bf16 and
- * 8-byte codes), otherwise the three scalar kernels run one after
- * another. */
+ * bytes (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_adam_step_refresh_quantize(float *master, float *exp_avg, float *exp_avg_sq,
                                                   const float *grad, uint16_t *primary_bf16,
                                                   uint16_t *secondary_bf16, int8_t *codes,
@@ -202,8 +198,7 @@ ZPP_API zpp_status zpp_adam_step_refresh_quantize(float *master, float *exp_avg,
  * buffers wait for this read).  num_wait <= ZPP_MAX_WAIT_EVENTS, every event
  * non-NULL.
  * out must not overlap any shard range (ZPP_EOVERLAP).  Alignment: out 2,
- * scales 4 (ZPP_EALIGN); shard_elems % 16 == 0 with 16-byte aligned codes
- * and out selects the vector kernel. */
+ * scales 4 (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_dequant_gather_layer(const int8_t *const *shard_codes,
                                             const float *const *shard_scales, uint32_t num_shards,
                                             size_t shard_elems, uint32_t block, size_t layer_elems,
@@ -228,7 +223,7 @@ ZPP_API zpp_status zpp_dequant_gather_layer(const int8_t *const *shard_codes,
  * float[ceil(n/block)] out.  block: a multiple of 64 in [64, 4096].
  * Order on `stream`: wait `wait_before`, quantize, record `done_after`.
  * No two ranges may overlap (ZPP_EOVERLAP).  Alignment: src and scales 4
- * bytes (ZPP_EALIGN); 16-byte src and 2-byte codes select the vector kernel. */
+ * bytes (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_quantize_blockwise_i4(const float *src, size_t n, uint32_t block,
                                              uint8_t *codes, float *scales, hipStream_t stream,
                                              hipEvent_t wait_before, hipEvent_t done_after);
@@ -245,8 +240,7 @@ ZPP_API zpp_status zpp_quantize_blockwise_i4(const float *src, size_t n, uint32_
  * Order on `stream`: wait for every event of wait_events[0..num_wait) (the
  * exchange that delivered the sources), reduce, record `done_after`.
  * out must not overlap any source range (ZPP_EOVERLAP).  Alignment: out and
- * scales 4 bytes (ZPP_EALIGN); 16-byte out and 2-byte codes select the vector
- * kernel. */
+ * scales 4 bytes (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_dequant_reduce_i4(const uint8_t *const *src_codes,
                                          const float *const *src_scales, uint32_t num_src, size_t n,
                                          uint32_t block, float scale_out, float *out,
@@ -275,8 +269,7 @@ ZPP_API zpp_status zpp_dequant_reduce_i4(const uint8_t *const *src_codes,
  * exchange that delivered the sources), step, record `done_after`.
  * No two of the four outputs may overlap, nor any output a source range
  * (ZPP_EOVERLAP).  Alignment: floats and scales 4, bf16 2 bytes
- * (ZPP_EALIGN); 16-byte state arrays, an 8-byte primary and 2-byte codes
- * select the vector kernel. */
+ * (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_qgz_receive_adam_step(float *master, float *exp_avg, float *exp_avg_sq,
                                              const uint8_t *const *src_codes,
                                              const float *const *src_scales, uint32_t num_src,
@@ -306,10 +299,7 @@ ZPP_API zpp_status zpp_qgz_receive_adam_step(float *master, float *exp_avg, floa
  * Order on `stream`: wait for every event of wait_events[0..num_wait),
  * run, record `done_after` (the event a gather of the codes waits on).
  * No two outputs may overlap, nor any output a source range (ZPP_EOVERLAP).
- * Alignment: floats and scales 4, bf16 2 bytes (ZPP_EALIGN); 16-byte state
- * arrays, 8-byte bf16 arrays, 4-byte codes and 2-byte source codes select
- * the single-pass kernel, otherwise the three scalar kernels run one after
- * another. */
+ * Alignment: floats and scales 4, bf16 2 bytes (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_qgz_receive_step_refresh_quantize(
     float *master, float *exp_avg, float *exp_avg_sq, const uint8_t *const *src_codes,
     const float *const *src_scales, uint32_t num_src, uint32_t grad_block, float scale_out,
@@ -338,8 +328,7 @@ ZPP_API zpp_status zpp_qgz_receive_step_refresh_quantize(
  * [1, ZPP_MAX_SHARDS], source < num_src, n <= SIZE_MAX / 16 / num_src.
  * Order on `stream`: wait `wait_before`, quantize, record `done_after`.
  * No two of src, the codes buffer and the scales buffer may overlap
- * (ZPP_EOVERLAP).  Alignment: src and scales 4 bytes (ZPP_EALIGN); 16-byte
- * src and 2-byte codes select the vector kernel. */
+ * (ZPP_EOVERLAP).  Alignment: src and scales 4 bytes (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_quantize_blockwise_i4_interleaved(const float *src, size_t n,
                                                          uint32_t block, uint32_t source,
                                                          uint32_t num_src, uint8_t *codes,
@@ -353,8 +342,7 @@ ZPP_API zpp_status zpp_quantize_blockwise_i4_interleaved(const float *src, size_
  * B = block.  n <= SIZE_MAX / 16 / num_src.  out: float[n], which must not
  * overlap the buffer (ZPP_EOVERLAP).  Order on `stream`: wait for every
  * event of wait_events[0..num_wait), reduce, record `done_after`.
- * Alignment: out and scales 4 bytes (ZPP_EALIGN); 16-byte out and 2-byte
- * codes select the vector kernel. */
+ * Alignment: out and scales 4 bytes (ZPP_EALIGN). */
 ZPP_API zpp_status zpp_dequant_reduce_i4_interleaved(const uint8_t *codes, const float *scales,
                                                      uint32_t num_src, size_t n, uint32_t block,
                                                      float scale_out, float *out,

@@ -64,53 +64,29 @@ __device__ __forceinline__ void adam_tile(const AdamArgs &a, size_t base, uint32
 template <bool ADAMW, int U>
 __global__ __launch_bounds__(kAdamThreads) void adam_vec_kernel(AdamArgs a, TileSpan tiles) {
     constexpr uint32_t kTile = kAdamThreads * 4 * U;
-    const size_t base = (tiles.first + blockIdx.x) * kTile;
-    if (__builtin_expect(blockIdx.x < tiles.whole, 1))
+    const uint32_t t = tile_of(blockIdx.x, gridDim.x, tiles, 0);
+    const size_t base = (tiles.first + t) * kTile;
+    if (__builtin_expect(t < tiles.whole, 1))
         adam_tile<ADAMW, U, true>(a, base, kTile);
     else
         adam_tile<ADAMW, U, false>(a, base, tiles.tail);
 }
 
-// Any alignment: one element per thread, grid-stride.
-template <bool ADAMW>
-__global__ __launch_bounds__(kThreads) void adam_scalar_kernel(AdamArgs a) {
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < a.n; i += stride) {
-        float p = a.p[i], m = a.m[i], v = a.v[i];
-        adam_update<ADAMW>(p, m, v, a.g[i], a.c);
-        a.p[i] = p;
-        a.m[i] = m;
-        a.v[i] = v;
-        a.out[i] = (uint16_t)bf16_rne_bits(p);
-    }
-}
-
 }  // namespace
 
 hipError_t launch_adam(float *p, float *m, float *v, const float *g, uint16_t *out, size_t n,
-                       const AdamConsts &c, bool vector_path, hipStream_t stream) {
-    AdamArgs a{p, m, v, g, out, n, c};
-    if (vector_path) {
-        constexpr uint32_t kTile = kAdamThreads * 4 * ZPP_ADAM_UNROLL;
-        constexpr size_t lds = residency_lds(ZPP_ADAM_RESIDENCY);
-        for_tiles(n, kTile, 1, kAdamThreads, [&](const TileSpan &tiles, unsigned grid) {
-            if (c.adamw)
-                hipLaunchKernelGGL((adam_vec_kernel<true, ZPP_ADAM_UNROLL>), dim3(grid),
-                                   dim3(kAdamThreads), lds, stream, a, tiles);
-            else
-                hipLaunchKernelGGL((adam_vec_kernel<false, ZPP_ADAM_UNROLL>), dim3(grid),
-                                   dim3(kAdamThreads), lds, stream, a, tiles);
-        });
-    } else {
-        size_t blocks = (n + kThreads - 1) / kThreads;
-        const unsigned grid = (unsigned)(blocks < (1u << 20) ? blocks : (1u << 20));
+                       const AdamConsts &c, bool on_lines, hipStream_t stream) {
+    const AdamArgs a{p, m, v, g, out, n, c};
+    constexpr uint32_t kTile = kAdamThreads * 4 * ZPP_ADAM_UNROLL;
+    constexpr size_t lds = residency_lds(ZPP_ADAM_RESIDENCY);
+    for_tiles(n, kTile, 1, kAdamThreads, on_lines, [&](const TileSpan &tiles, unsigned grid) {
         if (c.adamw)
-            hipLaunchKernelGGL((adam_scalar_kernel<true>), dim3(grid), dim3(kThreads), 0,
-                               stream, a);
+            hipLaunchKernelGGL((adam_vec_kernel<true, ZPP_ADAM_UNROLL>), dim3(grid),
+                               dim3(kAdamThreads), lds, stream, a, tiles);
         else
-            hipLaunchKernelGGL((adam_scalar_kernel<false>), dim3(grid), dim3(kThreads), 0,
-                               stream, a);
-    }
+            hipLaunchKernelGGL((adam_vec_kernel<false, ZPP_ADAM_UNROLL>), dim3(grid),
+                               dim3(kAdamThreads), lds, stream, a, tiles);
+    });
     return hipGetLastError();
 }
 

@@ -136,7 +136,7 @@ __device__ __forceinline__ void fused_chunk(const FusedArgs &a, const GS &gs, si
 template <bool ADAMW, int B, class GS, bool QUANT, bool MANY>
 __global__ __launch_bounds__(kWave) void fused_kernel(FusedArgs a, GS gs, TileSpan chunks) {
     constexpr uint32_t C = B > 256 ? B : 256;
-    const uint32_t t = (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, fused_xcd_run<GS>());
+    const uint32_t t = tile_of(blockIdx.x, gridDim.x, chunks, fused_xcd_run<GS>());
     const size_t base = (chunks.first + t) * C;
     if (__builtin_expect(t < chunks.whole, 1))
         fused_chunk<ADAMW, B, QUANT, true, MANY>(a, gs, base, C);
@@ -151,10 +151,11 @@ template <> constexpr int fused_residency<I4Grad>() { return ZPP_FUSED_RECV_RESI
 template <> constexpr int fused_residency<I4GradIl>() { return ZPP_FUSED_RECV_IL_RESIDENCY; }
 
 template <int B, bool QUANT, bool MANY, class GS>
-void launch_fused_chunks(const FusedArgs &a, const GS &gs, int residency, hipStream_t stream) {
+void launch_fused_chunks(const FusedArgs &a, const GS &gs, int residency, bool on_lines,
+                         hipStream_t stream) {
     constexpr uint32_t C = B > 256 ? B : 256;
     const size_t lds = residency_lds(residency);
-    for_tiles(a.n, C, 1, kWave, [&](const TileSpan &chunks, unsigned grid) {
+    for_tiles(a.n, C, 1, kWave, on_lines, [&](const TileSpan &chunks, unsigned grid) {
         if (a.c.adamw)
             hipLaunchKernelGGL((fused_kernel<true, B, GS, QUANT, MANY>), dim3(grid), dim3(kWave),
                                lds, stream, a, gs, chunks);
@@ -165,35 +166,33 @@ void launch_fused_chunks(const FusedArgs &a, const GS &gs, int residency, hipStr
 }
 
 template <int B, bool QUANT = true, class GS>
-void launch_fused_b(const FusedArgs &a, const GS &gs, hipStream_t stream) {
+void launch_fused_b(const FusedArgs &a, const GS &gs, bool on_lines, hipStream_t stream) {
     int residency = fused_residency<GS>();
     if constexpr (!std::is_same_v<GS, F32Grad>) {
         if (gs.num_src >= kManySources)
             residency = 0;  // left to the hardware (zpp_i4grad.h)
         if (many_sources(gs.num_src, gs.block))
-            return launch_fused_chunks<B, QUANT, true>(a, gs, residency, stream);
+            return launch_fused_chunks<B, QUANT, true>(a, gs, residency, on_lines, stream);
     }
-    launch_fused_chunks<B, QUANT, false>(a, gs, residency, stream);
+    launch_fused_chunks<B, QUANT, false>(a, gs, residency, on_lines, stream);
 }
 
 template <class GS>
-hipError_t launch_fused_gs(const FusedArgs &a, const GS &gs, uint32_t block,
+hipError_t launch_fused_gs(const FusedArgs &a, const GS &gs, uint32_t block, bool on_lines,
                            hipStream_t stream) {
     switch (block) {
-    case 64: launch_fused_b<64>(a, gs, stream); break;
-    case 128: launch_fused_b<128>(a, gs, stream); break;
-    case 256: launch_fused_b<256>(a, gs, stream); break;
-    case 512: launch_fused_b<512>(a, gs, stream); break;
+    case 64: launch_fused_b<64>(a, gs, on_lines, stream); break;
+    case 128: launch_fused_b<128>(a, gs, on_lines, stream); break;
+    case 256: launch_fused_b<256>(a, gs, on_lines, stream); break;
+    case 512: launch_fused_b<512>(a, gs, on_lines, stream); break;
     default: {
         // the step and its copies in one pass, then the quantization of
         // the primary it wrote (stream order)
-        launch_fused_b<256, false>(a, gs, stream);
+        launch_fused_b<256, false>(a, gs, on_lines, stream);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
-        const bool qvec = reinterpret_cast<uintptr_t>(a.primary) % 16 == 0 &&
-                          reinterpret_cast<uintptr_t>(a.codes) % 8 == 0;
-        return launch_quantize(a.primary, a.n, block, a.codes, a.scales, qvec, stream);
+        return launch_quantize(a.primary, a.n, block, a.codes, a.scales, on_lines, stream);
     }
     }
     return hipGetLastError();
@@ -203,63 +202,30 @@ hipError_t launch_fused_gs(const FusedArgs &a, const GS &gs, uint32_t block,
 
 hipError_t launch_fused(float *p, float *m, float *v, const float *g, uint16_t *primary,
                         uint16_t *secondary, int8_t *codes, float *scales, size_t n,
-                        uint32_t block, const AdamConsts &c, bool vector_path,
-                        hipStream_t stream) {
-    if (!vector_path) {
-        // any alignment: the three separate scalar kernels, one after another
-        // on the stream, compute the same values
-        hipError_t e = launch_adam(p, m, v, g, primary, n, c, false, stream);
-        if (e == hipSuccess && secondary)
-            e = launch_refresh(secondary, primary, n, false, stream);
-        if (e == hipSuccess)
-            e = launch_quantize(primary, n, block, codes, scales, false, stream);
-        return e;
-    }
+                        uint32_t block, const AdamConsts &c, bool on_lines, hipStream_t stream) {
     const FusedArgs a{p, m, v, primary, secondary, codes, scales, n, c};
-    return launch_fused_gs(a, F32Grad{g}, block, stream);
+    return launch_fused_gs(a, F32Grad{g}, block, on_lines, stream);
 }
 
 hipError_t launch_fused_receive(float *p, float *m, float *v, const uint8_t *const *src_codes,
                                 const float *const *src_scales, uint32_t num_src,
                                 uint32_t grad_block, float scale_out, uint16_t *primary,
                                 uint16_t *secondary, int8_t *codes, float *scales, size_t n,
-                                uint32_t block, const AdamConsts &c, bool vector_path,
+                                uint32_t block, const AdamConsts &c, bool on_lines,
                                 hipStream_t stream) {
-    if (!vector_path) {
-        // any alignment: the receive step, the refresh and the quantization
-        // as scalar kernels, one after another on the stream
-        hipError_t e = launch_receive_adam(p, m, v, src_codes, src_scales, num_src, grad_block,
-                                           scale_out, primary, n, c, false, stream);
-        if (e == hipSuccess && secondary)
-            e = launch_refresh(secondary, primary, n, false, stream);
-        if (e == hipSuccess)
-            e = launch_quantize(primary, n, block, codes, scales, false, stream);
-        return e;
-    }
     const FusedArgs a{p, m, v, primary, secondary, codes, scales, n, c};
     return launch_fused_gs(a, make_i4grad(src_codes, src_scales, num_src, grad_block, scale_out),
-                           block, stream);
+                           block, on_lines, stream);
 }
 
 hipError_t launch_fused_receive_il(float *p, float *m, float *v, const uint8_t *src_codes,
                                    const float *src_scales, uint32_t num_src, uint32_t grad_block,
                                    float scale_out, uint16_t *primary, uint16_t *secondary,
                                    int8_t *codes, float *scales, size_t n, uint32_t block,
-                                   const AdamConsts &c, bool vector_path, hipStream_t stream) {
-    if (!vector_path) {
-        // any alignment: the receive step, the refresh and the quantization
-        // as scalar kernels, one after another on the stream
-        hipError_t e = launch_receive_adam_il(p, m, v, src_codes, src_scales, num_src, grad_block,
-                                              scale_out, primary, n, c, false, stream);
-        if (e == hipSuccess && secondary)
-            e = launch_refresh(secondary, primary, n, false, stream);
-        if (e == hipSuccess)
-            e = launch_quantize(primary, n, block, codes, scales, false, stream);
-        return e;
-    }
+                                   const AdamConsts &c, bool on_lines, hipStream_t stream) {
     const FusedArgs a{p, m, v, primary, secondary, codes, scales, n, c};
     return launch_fused_gs(a, make_i4grad_il(src_codes, src_scales, num_src, grad_block, scale_out),
-                           block, stream);
+                           block, on_lines, stream);
 }
 
 }  // namespace zpp

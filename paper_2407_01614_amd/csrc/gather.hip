@@ -55,7 +55,14 @@ struct GatherArgs {
     size_t shard_elems;
     size_t layer_elems;
     BlockDiv block;
+    uint32_t on_lines;  // every shard's part of the output starts on a line
 };
+
+// The workgroup's place along its shard: in runs per XCD where the shards'
+// parts of the output do not start on lines (kOffLineXcdRun, zpp_device.h).
+__device__ __forceinline__ size_t gather_place(bool on_lines) {
+    return on_lines ? blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x, kOffLineXcdRun);
+}
 
 __device__ __forceinline__ float code_f32(uint32_t w, int byte) {
     return (float)(int)(int8_t)(uint8_t)(w >> (8 * byte));
@@ -94,6 +101,27 @@ __device__ __forceinline__ u32x2 dequant_word_any(uint32_t w, float s) {
     return r;
 }
 
+// The 8 elements from i on, those below `valid`, of a shard's last, partial
+// row: all their codes loaded at once (clamped into the shard, which never
+// crosses a block within a lane's 8) rather than one after the other.
+__device__ __forceinline__ void gather_tail(const int8_t *__restrict__ codes,
+                                            const float *__restrict__ scales,
+                                            uint16_t *__restrict__ out, const BlockDiv &block,
+                                            size_t i, size_t valid) {
+    if (i >= valid)
+        return;
+    const uint32_t rest = valid - i < 8 ? (uint32_t)(valid - i) : 8u;
+    const float s = scales[block_of(block, i)];
+    int8_t c[8];
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e)
+        c[e] = codes[i + clamped(e, rest)];
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e)
+        if (e < rest)
+            out[i + e] = (uint16_t)bf16_rne_bits((float)c[e] * s);
+}
+
 // A row is one wave-wide pass: 64 lanes x 8 consecutive codes = 512 output
 // elements, read as one contiguous 512-byte load and written as one
 // contiguous 1 KiB store.  A tile is U rows per wave.
@@ -111,7 +139,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_vec_kernel(GatherArgs a
     const float *__restrict__ scales = a.shards.scales[j];
     uint16_t *__restrict__ out = a.out + lo;
     const size_t ntiles = (valid + kTile - 1) / kTile;
-    for (size_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    for (size_t t = gather_place(a.on_lines); t < ntiles; t += gridDim.x) {
         const size_t base = t * kTile + (size_t)threadIdx.x * 8;
         if ((t + 1) * kTile <= valid) {
             u32x2 c[U];
@@ -119,7 +147,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_vec_kernel(GatherArgs a
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const size_t i = base + (size_t)u * kRow;
-                c[u] = ld_nt(reinterpret_cast<const u32x2 *>(codes + i));
+                c[u] = ld_nt_at<u32x2, 1>(codes + i);
                 s[u] = scales[block_of(a.block, i)];
             }
 #pragma unroll
@@ -134,21 +162,15 @@ __global__ __launch_bounds__(kGatherThreads) void gather_vec_kernel(GatherArgs a
                     r0 = dequant_word_any(c[u].x, s[u]);
                     r1 = dequant_word_any(c[u].y, s[u]);
                 }
-                st_nt(reinterpret_cast<u32x4 *>(out + i), u32x4{r0.x, r0.y, r1.x, r1.y});
+                st_nt_at<u32x4, 2>(out + i, u32x4{r0.x, r0.y, r1.x, r1.y});
             }
         } else {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const size_t i0 = base + (size_t)u * kRow;
-                for (size_t i = i0; i < i0 + 8 && i < valid; ++i) {
-                    const float x = (float)codes[i] * scales[block_of(a.block, i)];
-                    out[i] = (uint16_t)bf16_rne_bits(x);
-                }
-            }
+            for (int u = 0; u < U; ++u)
+                gather_tail(codes, scales, out, a.block, base + (size_t)u * kRow, valid);
         }
     }
 }
-
 
 // One row of 512 elements per one-wave workgroup, one workgroup per row (a
 // one-shot grid: no loop, so the scale loads come before any store and the
@@ -166,10 +188,10 @@ __global__ __launch_bounds__(kWave) void gather_row_kernel(GatherArgs a) {
     const float *__restrict__ scales = a.shards.scales[j];
     uint16_t *__restrict__ out = a.out + lo;
     const uint32_t lane = threadIdx.x;
-    const size_t r = blockIdx.x;
+    const size_t r = gather_place(a.on_lines);
     const size_t i = r * 512 + (size_t)lane * 8;
     if ((r + 1) * 512 <= valid) {
-        const u32x2 c = ld_nt(reinterpret_cast<const u32x2 *>(codes + i));
+        const u32x2 c = ld_nt_at<u32x2, 1>(codes + i);
         // the row's scales: uniform indices, scalar loads
         const size_t k0 = r * 512 / B;
         float sv[kBlocks];
@@ -192,12 +214,9 @@ __global__ __launch_bounds__(kWave) void gather_row_kernel(GatherArgs a) {
             r0 = dequant_word_any(c.x, s);
             r1 = dequant_word_any(c.y, s);
         }
-        st_nt(reinterpret_cast<u32x4 *>(out + i), u32x4{r0.x, r0.y, r1.x, r1.y});
+        st_nt_at<u32x4, 2>(out + i, u32x4{r0.x, r0.y, r1.x, r1.y});
     } else {
-        for (size_t e = i; e < i + 8 && e < valid; ++e) {
-            const float x = (float)codes[e] * scales[e / B];
-            out[e] = (uint16_t)bf16_rne_bits(x);
-        }
+        gather_tail(codes, scales, out, a.block, i, valid);
     }
 }
 
@@ -206,27 +225,10 @@ void launch_rows(const GatherArgs &a, unsigned rows, unsigned shards, hipStream_
     hipLaunchKernelGGL((gather_row_kernel<B>), dim3(rows, shards), dim3(kWave), 0, stream, a);
 }
 
-// Any shard length and alignment: one output element per thread.
-__global__ __launch_bounds__(kThreads) void gather_scalar_kernel(GatherArgs a) {
-    const uint32_t j = blockIdx.y;
-    const size_t lo = (size_t)j * a.shard_elems;
-    if (lo >= a.layer_elems)
-        return;
-    const size_t rest = a.layer_elems - lo;
-    const size_t valid = rest < a.shard_elems ? rest : a.shard_elems;
-    const int8_t *codes = a.shards.codes[j];
-    const float *scales = a.shards.scales[j];
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < valid; i += stride) {
-        const float x = (float)codes[i] * scales[block_of(a.block, i)];
-        a.out[lo + i] = (uint16_t)bf16_rne_bits(x);
-    }
-}
-
 }  // namespace
 
 hipError_t launch_gather(const GatherShards &shards, uint32_t num_shards, size_t shard_elems,
-                         uint32_t block, size_t layer_elems, uint16_t *out, bool vector_path,
+                         uint32_t block, size_t layer_elems, uint16_t *out, bool on_lines,
                          hipStream_t stream) {
     GatherArgs a;
     a.shards = shards;
@@ -234,9 +236,10 @@ hipError_t launch_gather(const GatherShards &shards, uint32_t num_shards, size_t
     a.shard_elems = shard_elems;
     a.layer_elems = layer_elems;
     a.block = make_block_div(block);
+    a.on_lines = on_lines;
     const size_t per_shard = shard_elems < layer_elems ? shard_elems : layer_elems;
     const size_t nrows = (per_shard + 511) / 512;
-    if (vector_path && (block & (block - 1)) == 0 && nrows <= ZPP_GATHER_ROW_MAX_GRID_X) {
+    if ((block & (block - 1)) == 0 && nrows <= ZPP_GATHER_ROW_MAX_GRID_X) {
         // only the shards that hold layer elements
         const unsigned gy = (unsigned)((layer_elems + shard_elems - 1) / shard_elems);
         const unsigned gx = (unsigned)nrows;
@@ -249,18 +252,13 @@ hipError_t launch_gather(const GatherShards &shards, uint32_t num_shards, size_t
         case 2048: launch_rows<2048>(a, gx, gy, stream); break;
         default: launch_rows<4096>(a, gx, gy, stream); break;
         }
-    } else if (vector_path) {
+    } else {
         constexpr size_t kTile = (size_t)kGatherThreads * 8 * ZPP_GATHER_UNROLL;
         const size_t tiles = (per_shard + kTile - 1) / kTile;
         const unsigned gx =
             (unsigned)(tiles < ZPP_GATHER_MAX_GRID_X ? tiles : ZPP_GATHER_MAX_GRID_X);
         hipLaunchKernelGGL((gather_vec_kernel<ZPP_GATHER_UNROLL>), dim3(gx, num_shards),
                            dim3(kGatherThreads), residency_lds(ZPP_GATHER_RESIDENCY), stream, a);
-    } else {
-        const size_t blocks = (per_shard + kThreads - 1) / kThreads;
-        const unsigned gx = (unsigned)(blocks < (1u << 20) ? blocks : (1u << 20));
-        hipLaunchKernelGGL(gather_scalar_kernel, dim3(gx, num_shards), dim3(kThreads), 0,
-                           stream, a);
     }
     return hipGetLastError();
 }

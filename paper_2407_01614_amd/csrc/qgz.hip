@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kQgzThreads) void quant_i4_kernel(
             for (int g = 0; g < G; ++g) {
                 const size_t i = (t0 + u) * C + (size_t)g * 256 + (size_t)lane * 4;
                 if (t0 + u < ntiles && i + 4 <= n) {
-                    x[u][g] = ld_nt(reinterpret_cast<const f32x4 *>(src + i));
+                    x[u][g] = ld_nt_at<f32x4, 4>(src + i);
                 } else {
                     float h[4];
 #pragma unroll
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kQgzThreads) void quant_i4_kernel(
                     const size_t byte0 = i4_out_byte(i, kShift, q_src, num_src);
                     // the second byte holds elements i + 2 and i + 3
                     if (i + 2 < n) {
-                        st_nt(reinterpret_cast<uint16_t *>(codes + byte0), (uint16_t)h);
+                        st_nt_at<uint16_t, 1>(codes + byte0, (uint16_t)h);
                     } else if (i < n) {
                         codes[byte0] = (uint8_t)h;
                     }
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kQgzThreads) void quant_i4_grp_kernel(
                 x[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                 const uint32_t j = (uint32_t)(v * G + li);
                 if (j < gpb)
-                    x[v] = ld_nt(reinterpret_cast<const f32x4 *>(src + k * B + (size_t)j * 4));
+                    x[v] = ld_nt_at<f32x4, 4>(src + k * B + (size_t)j * 4);
             }
         } else {
 #pragma unroll
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kQgzThreads) void quant_i4_grp_kernel(
                 const size_t i = k * B + (size_t)j * 4;
                 if (valid && j < gpb) {
                     if (i + 4 <= n) {
-                        x[v] = ld_nt(reinterpret_cast<const f32x4 *>(src + i));
+                        x[v] = ld_nt_at<f32x4, 4>(src + i);
                     } else if (i < n) {
                         float h[4];
 #pragma unroll
@@ -259,41 +259,11 @@ __global__ __launch_bounds__(kQgzThreads) void quant_i4_grp_kernel(
             const size_t byte0 = i4_out_byte_any(i, k, B, q_src, num_src);
             // the second byte holds elements i + 2 and i + 3
             if (i + 2 < n)
-                st_nt(reinterpret_cast<uint16_t *>(codes + byte0), (uint16_t)h);
+                st_nt_at<uint16_t, 1>(codes + byte0, (uint16_t)h);
             else
                 codes[byte0] = (uint8_t)h;
         }
         if (valid && li == 0)
-            scales[k * num_src + q_src] = q.scale;
-    }
-}
-
-// Any alignment: one wave per block, lanes stride through it; each code
-// byte is written by the lane that owns its even element.
-__global__ __launch_bounds__(kQgzThreads) void quant_i4_scalar_kernel(
-    const float *__restrict__ src, size_t n, uint32_t block, uint8_t *__restrict__ codes,
-    float *__restrict__ scales, uint32_t q_src, uint32_t num_src) {
-    const size_t nblocks = (n + block - 1) / block;
-    const int lane = threadIdx.x & (kWave - 1);
-    const size_t wave0 = (size_t)blockIdx.x * (kQgzThreads / kWave) + threadIdx.x / kWave;
-    const size_t nwaves = (size_t)gridDim.x * (kQgzThreads / kWave);
-    for (size_t k = wave0; k < nblocks; k += nwaves) {
-        const size_t lo = k * block;
-        const size_t hi = (lo + block < n) ? lo + block : n;
-        uint32_t mx = 0;
-        for (size_t i = lo + lane; i < hi; i += kWave)
-            mx = max(mx, __float_as_uint(src[i]) & 0x7FFFFFFFu);
-        for (int off = kWave / 2; off >= 1; off >>= 1)
-            mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
-        const I4Quant q = i4_params(mx);
-        // block is even, so a code byte never straddles two blocks
-        for (size_t i = lo + 2 * lane; i < hi; i += 2 * kWave) {
-            const float x0 = src[i];
-            const float x1 = (i + 1 < hi) ? src[i + 1] : 0.0f;
-            const uint32_t h = i4_half(f32x4{x0, x1, 0.0f, 0.0f}, q);
-            codes[i4_out_byte_any(i, k, block, q_src, num_src)] = (uint8_t)(h & 0xFFu);
-        }
-        if (lane == 0)
             scales[k * num_src + q_src] = q.scale;
     }
 }
@@ -315,8 +285,7 @@ __global__ __launch_bounds__(kQgzThreads) void reduce_gs_kernel(GS gs, float *__
     constexpr size_t C = 256 * G;
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t t = (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, reduce_xcd_run<GS>()) * kWaves +
-                       wave;
+    const uint32_t t = tile_of(blockIdx.x, gridDim.x, tiles, reduce_xcd_run<GS>()) * kWaves + wave;
     const size_t base = (tiles.first + t) * C;
     f32x4 r[G];
     if (__builtin_expect(t < tiles.whole, 1)) {
@@ -332,18 +301,9 @@ __global__ __launch_bounds__(kQgzThreads) void reduce_gs_kernel(GS gs, float *__
     }
 }
 
-// Any alignment: one element per thread.
-template <class GS>
-__global__ __launch_bounds__(kQgzThreads) void reduce_gs_scalar_kernel(GS gs, size_t n,
-                                                                      float *__restrict__ out) {
-    for (size_t i = (size_t)blockIdx.x * kQgzThreads + threadIdx.x; i < n;
-         i += (size_t)gridDim.x * kQgzThreads)
-        out[i] = grad_at(gs, i);
-}
-
 template <int G, bool MANY, class GS>
-void launch_reduce_gs(const GS &gs, size_t n, float *out, hipStream_t stream) {
-    for_tiles(n, 256 * G, kQgzThreads / kWave, kQgzThreads,
+void launch_reduce_gs(const GS &gs, size_t n, float *out, bool on_lines, hipStream_t stream) {
+    for_tiles(n, 256 * G, kQgzThreads / kWave, kQgzThreads, on_lines,
               [&](const TileSpan &tiles, unsigned grid) {
                   hipLaunchKernelGGL((reduce_gs_kernel<GS, G, MANY>), dim3(grid),
                                      dim3(kQgzThreads), 0, stream, gs, out, tiles);
@@ -355,20 +315,13 @@ void launch_reduce_gs(const GS &gs, size_t n, float *out, hipStream_t stream) {
 // short array on more waves (500,000 elements: 3.1 against 4.1 us): two from
 // the length that gives every CU its 32 waves.  Fewer sources keep two.
 template <class GS>
-hipError_t launch_reduce(const GS &gs, size_t n, float *out, bool vector_path,
-                         hipStream_t stream) {
-    if (!vector_path) {
-        const size_t need = (n + kQgzThreads - 1) / kQgzThreads;
-        const unsigned grid = (unsigned)(need < (1u << 20) ? need : (1u << 20));
-        hipLaunchKernelGGL(reduce_gs_scalar_kernel<GS>, dim3(grid), dim3(kQgzThreads), 0, stream,
-                           gs, n, out);
-    } else if (!many_sources(gs.num_src, gs.block)) {
-        launch_reduce_gs<2, false>(gs, n, out, stream);
-    } else if (n >= (size_t)512 * 32 * kCUs) {
-        launch_reduce_gs<2, true>(gs, n, out, stream);
-    } else {
-        launch_reduce_gs<1, true>(gs, n, out, stream);
-    }
+hipError_t launch_reduce(const GS &gs, size_t n, float *out, bool on_lines, hipStream_t stream) {
+    if (!many_sources(gs.num_src, gs.block))
+        launch_reduce_gs<2, false>(gs, n, out, on_lines, stream);
+    else if (n >= (size_t)512 * 32 * kCUs)
+        launch_reduce_gs<2, true>(gs, n, out, on_lines, stream);
+    else
+        launch_reduce_gs<1, true>(gs, n, out, on_lines, stream);
     return hipGetLastError();
 }
 
@@ -410,57 +363,49 @@ void launch_quant_i4_grp_g(uint32_t G, const float *src, size_t n, uint32_t bloc
 
 hipError_t launch_quantize_i4_il(const float *src, size_t n, uint32_t block, uint32_t source,
                                  uint32_t num_src, uint8_t *codes, float *scales,
-                                 bool vector_path, hipStream_t stream) {
-    if (vector_path) {
-        switch (block) {
-        case 64: launch_quant_i4_b<64>(src, n, codes, scales, source, num_src, stream); break;
-        case 128: launch_quant_i4_b<128>(src, n, codes, scales, source, num_src, stream); break;
-        case 256: launch_quant_i4_b<256>(src, n, codes, scales, source, num_src, stream); break;
-        case 512: launch_quant_i4_b<512>(src, n, codes, scales, source, num_src, stream); break;
-        case 1024: launch_quant_i4_b<1024>(src, n, codes, scales, source, num_src, stream); break;
-        case 2048: launch_quant_i4_b<2048>(src, n, codes, scales, source, num_src, stream); break;
-        case 4096: launch_quant_i4_b<4096>(src, n, codes, scales, source, num_src, stream); break;
-        default: {
-            const GroupShape sh = group_shape(block / 4, 16, ZPP_QGZ_GROUP_MIN_FILL, 3);
-            if (sh.S <= 4)
-                launch_quant_i4_grp_g<4>(sh.G, src, n, block, codes, scales, source, num_src,
-                                         stream);
-            else if (sh.S <= 8)
-                launch_quant_i4_grp_g<8>(sh.G, src, n, block, codes, scales, source, num_src,
-                                         stream);
-            else
-                launch_quant_i4_grp_g<16>(sh.G, src, n, block, codes, scales, source, num_src,
-                                          stream);
-        }
-        }
-    } else {
-        const size_t nblocks = (n + block - 1) / block;
-        const size_t need = (nblocks + (kQgzThreads / kWave) - 1) / (kQgzThreads / kWave);
-        const unsigned grid = (unsigned)(need < (1u << 20) ? need : (1u << 20));
-        hipLaunchKernelGGL(quant_i4_scalar_kernel, dim3(grid), dim3(kQgzThreads), 0, stream, src,
-                           n, block, codes, scales, source, num_src);
+                                 bool, hipStream_t stream) {
+    switch (block) {
+    case 64: launch_quant_i4_b<64>(src, n, codes, scales, source, num_src, stream); break;
+    case 128: launch_quant_i4_b<128>(src, n, codes, scales, source, num_src, stream); break;
+    case 256: launch_quant_i4_b<256>(src, n, codes, scales, source, num_src, stream); break;
+    case 512: launch_quant_i4_b<512>(src, n, codes, scales, source, num_src, stream); break;
+    case 1024: launch_quant_i4_b<1024>(src, n, codes, scales, source, num_src, stream); break;
+    case 2048: launch_quant_i4_b<2048>(src, n, codes, scales, source, num_src, stream); break;
+    case 4096: launch_quant_i4_b<4096>(src, n, codes, scales, source, num_src, stream); break;
+    default: {
+        const GroupShape sh = group_shape(block / 4, 16, ZPP_QGZ_GROUP_MIN_FILL, 3);
+        if (sh.S <= 4)
+            launch_quant_i4_grp_g<4>(sh.G, src, n, block, codes, scales, source, num_src,
+                                     stream);
+        else if (sh.S <= 8)
+            launch_quant_i4_grp_g<8>(sh.G, src, n, block, codes, scales, source, num_src,
+                                     stream);
+        else
+            launch_quant_i4_grp_g<16>(sh.G, src, n, block, codes, scales, source, num_src,
+                                      stream);
+    }
     }
     return hipGetLastError();
 }
 
 hipError_t launch_quantize_i4(const float *src, size_t n, uint32_t block, uint8_t *codes,
-                              float *scales, bool vector_path, hipStream_t stream) {
-    return launch_quantize_i4_il(src, n, block, 0, 1, codes, scales, vector_path, stream);
+                              float *scales, bool on_lines, hipStream_t stream) {
+    return launch_quantize_i4_il(src, n, block, 0, 1, codes, scales, on_lines, stream);
 }
 
 hipError_t launch_dequant_reduce_i4(const uint8_t *const *src_codes,
                                     const float *const *src_scales, uint32_t num_src, size_t n,
                                     uint32_t block, float scale_out, float *out,
-                                    bool vector_path, hipStream_t stream) {
+                                    bool on_lines, hipStream_t stream) {
     return launch_reduce(make_i4grad(src_codes, src_scales, num_src, block, scale_out), n, out,
-                         vector_path, stream);
+                         on_lines, stream);
 }
 
 hipError_t launch_dequant_reduce_i4_il(const uint8_t *codes, const float *scales, uint32_t num_src,
                                        size_t n, uint32_t block, float scale_out, float *out,
-                                       bool vector_path, hipStream_t stream) {
+                                       bool on_lines, hipStream_t stream) {
     return launch_reduce(make_i4grad_il(codes, scales, num_src, block, scale_out), n, out,
-                         vector_path, stream);
+                         on_lines, stream);
 }
 
 }  // namespace zpp

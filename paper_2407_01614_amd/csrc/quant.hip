@@ -58,12 +58,21 @@ namespace {
 
 constexpr int kQuantThreads = ZPP_QUANT_THREADS;
 
+// The workgroup's place in the array.  The pass with the copy takes runs of
+// workgroups per XCD where its outputs do not start on lines (zpp_device.h):
+// 131 M elements off by one 123 us without, 116 with.  The quantizer alone
+// gains nothing from them (10.0 us at 13.1 M without, 10.2 with).
+template <bool COPY>
+__device__ __forceinline__ size_t group_of(bool on_lines) {
+    return COPY && !on_lines ? xcd_grouped(blockIdx.x, gridDim.x, kOffLineXcdRun) : blockIdx.x;
+}
+
 // With COPY the loaded bf16 are also stored to `copy`, bit for bit (the
 // secondary refresh taken into the quantization's pass).
 template <int B, int U, bool COPY>
 __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
     const uint16_t *__restrict__ src, size_t n, int8_t *__restrict__ codes,
-    float *__restrict__ scales, uint16_t *__restrict__ copy) {
+    float *__restrict__ scales, uint16_t *__restrict__ copy, bool on_lines) {
     constexpr int L = (B / 8 < kWave) ? B / 8 : kWave;  // lanes per quant block
     constexpr int V = (B / 8 > kWave) ? B / (8 * kWave) : 1;
     constexpr int kGroupsPerWave = kWave / L;
@@ -75,7 +84,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
     const int li = lane % L;
     const int wave = threadIdx.x / kWave;
 
-    for (size_t g0 = (size_t)blockIdx.x * kGroupsPerBlock; g0 < nblocks;
+    for (size_t g0 = group_of<COPY>(on_lines) * kGroupsPerBlock; g0 < nblocks;
          g0 += (size_t)gridDim.x * kGroupsPerBlock) {
         // all U rows of loads first, then the reductions and stores
         u32x4 x[U][V];
@@ -87,7 +96,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
             for (int v = 0; v < V; ++v) {
                 const size_t i = k * B + ((size_t)v * L + li) * 8;
                 if (valid && i + 8 <= n) {
-                    x[u][v] = ld_nt(reinterpret_cast<const u32x4 *>(src + i));
+                    x[u][v] = ld_nt_at<u32x4, 2>(src + i);
                 } else {
                     uint32_t h[8];
 #pragma unroll
@@ -121,9 +130,9 @@ __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
                 c.x = quant_word(x[u][v].x, x[u][v].y, q);
                 c.y = quant_word(x[u][v].z, x[u][v].w, q);
                 if (valid && i + 8 <= n) {
-                    st_nt(reinterpret_cast<u32x2 *>(codes + i), c);
+                    st_nt_at<u32x2, 1>(codes + i, c);
                     if (COPY)
-                        st_nt(reinterpret_cast<u32x4 *>(copy + i), x[u][v]);
+                        st_nt_at<u32x4, 2>(copy + i, x[u][v]);
                 } else if (valid) {
                     for (int e = 0; e < 8 && i + e < n; ++e) {
                         codes[i + e] =
@@ -151,7 +160,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
 template <int G, int S, bool COPY>
 __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
     const uint16_t *__restrict__ src, size_t n, uint32_t B, int8_t *__restrict__ codes,
-    float *__restrict__ scales, uint16_t *__restrict__ copy) {
+    float *__restrict__ scales, uint16_t *__restrict__ copy, bool on_lines) {
     constexpr int kGroupsPerWave = kWave / G;
     constexpr int kGroupsPerBlock = kGroupsPerWave * (kQuantThreads / kWave);
     const uint32_t vpb = B / 8;
@@ -159,7 +168,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
     const int lane = threadIdx.x & (kWave - 1);
     const int li = lane % G;
     const size_t kw = (size_t)(threadIdx.x / kWave) * kGroupsPerWave + lane / G;
-    for (size_t g0 = (size_t)blockIdx.x * kGroupsPerBlock; g0 < nblocks;
+    for (size_t g0 = group_of<COPY>(on_lines) * kGroupsPerBlock; g0 < nblocks;
          g0 += (size_t)gridDim.x * kGroupsPerBlock) {
         const size_t k = g0 + kw;
         const bool valid = k < nblocks;
@@ -171,7 +180,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
                 x[v] = u32x4{0u, 0u, 0u, 0u};
                 const uint32_t j = (uint32_t)(v * G + li);
                 if (j < vpb)
-                    x[v] = ld_nt(reinterpret_cast<const u32x4 *>(src + k * B + (size_t)j * 8));
+                    x[v] = ld_nt_at<u32x4, 2>(src + k * B + (size_t)j * 8);
             }
         } else {
 #pragma unroll
@@ -181,7 +190,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
                 const size_t i = k * B + (size_t)j * 8;
                 if (valid && j < vpb) {
                     if (i + 8 <= n) {
-                        x[v] = ld_nt(reinterpret_cast<const u32x4 *>(src + i));
+                        x[v] = ld_nt_at<u32x4, 2>(src + i);
                     } else if (i < n) {
                         uint32_t h[8];
 #pragma unroll
@@ -214,9 +223,9 @@ __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
             c.x = quant_word(x[v].x, x[v].y, q);
             c.y = quant_word(x[v].z, x[v].w, q);
             if (i + 8 <= n) {
-                st_nt(reinterpret_cast<u32x2 *>(codes + i), c);
+                st_nt_at<u32x2, 1>(codes + i, c);
                 if (COPY)
-                    st_nt(reinterpret_cast<u32x4 *>(copy + i), x[v]);
+                    st_nt_at<u32x4, 2>(copy + i, x[v]);
             } else {
                 for (int e = 0; e < 8 && i + e < n; ++e) {
                     codes[i + e] =
@@ -231,38 +240,9 @@ __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
     }
 }
 
-// Any alignment, any block: one wave per quant block, lanes stride through it
-// element by element.
-__global__ __launch_bounds__(kThreads) void quant_scalar_kernel(
-    const uint16_t *__restrict__ src, size_t n, uint32_t block, int8_t *__restrict__ codes,
-    float *__restrict__ scales, uint16_t *__restrict__ copy) {
-    const size_t nblocks = (n + block - 1) / block;
-    const int lane = threadIdx.x & (kWave - 1);
-    const size_t wave0 = (size_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
-    const size_t nwaves = (size_t)gridDim.x * (kThreads / kWave);
-    for (size_t k = wave0; k < nblocks; k += nwaves) {
-        const size_t lo = k * block;
-        const size_t hi = (lo + block < n) ? lo + block : n;
-        uint32_t mx = 0;
-        for (size_t i = lo + lane; i < hi; i += kWave)
-            mx = max(mx, (uint32_t)src[i] & 0x7FFFu);
-        for (int off = kWave / 2; off >= 1; off >>= 1)
-            mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
-        const BlockQuant q = block_params(mx);
-        for (size_t i = lo + lane; i < hi; i += kWave) {
-            const uint16_t h = src[i];
-            codes[i] = (int8_t)quant_one(bf16_lo((uint32_t)h), q);
-            if (copy)
-                copy[i] = h;
-        }
-        if (lane == 0)
-            scales[k] = q.scale;
-    }
-}
-
 template <int B, bool COPY>
 void launch_vec(const uint16_t *src, size_t n, int8_t *codes, float *scales, uint16_t *copy,
-                hipStream_t stream) {
+                bool on_lines, hipStream_t stream) {
     constexpr int L = (B / 8 < kWave) ? B / 8 : kWave;
     constexpr int U = COPY ? ZPP_QUANT_COPY_UNROLL : ZPP_QUANT_UNROLL;
     constexpr size_t kGroupsPerBlock = (kWave / L) * (kQuantThreads / kWave) * U;
@@ -270,53 +250,53 @@ void launch_vec(const uint16_t *src, size_t n, int8_t *codes, float *scales, uin
     const size_t need = (nblocks + kGroupsPerBlock - 1) / kGroupsPerBlock;
     const unsigned grid = (unsigned)(need < ZPP_QUANT_MAX_GRID ? need : ZPP_QUANT_MAX_GRID);
     hipLaunchKernelGGL((quant_vec_kernel<B, U, COPY>), dim3(grid), dim3(kQuantThreads), 0,
-                       stream, src, n, codes, scales, copy);
+                       stream, src, n, codes, scales, copy, on_lines);
 }
 
 template <int G, int S, bool COPY>
 void launch_grp(const uint16_t *src, size_t n, uint32_t block, int8_t *codes, float *scales,
-                uint16_t *copy, hipStream_t stream) {
+                uint16_t *copy, bool on_lines, hipStream_t stream) {
     constexpr size_t kGroupsPerBlock = (kWave / G) * (kQuantThreads / kWave);
     const size_t nblocks = (n + block - 1) / block;
     const size_t need = (nblocks + kGroupsPerBlock - 1) / kGroupsPerBlock;
     const unsigned grid = (unsigned)(need < ZPP_QUANT_MAX_GRID ? need : ZPP_QUANT_MAX_GRID);
     hipLaunchKernelGGL((quant_grp_kernel<G, S, COPY>), dim3(grid), dim3(kQuantThreads), 0,
-                       stream, src, n, block, codes, scales, copy);
+                       stream, src, n, block, codes, scales, copy, on_lines);
 }
 
 template <int S, bool COPY>
 void launch_grp_g(uint32_t G, const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
-                  float *scales, uint16_t *copy, hipStream_t stream) {
+                  float *scales, uint16_t *copy, bool on_lines, hipStream_t stream) {
     switch (G) {
-    case 16: launch_grp<16, S, COPY>(src, n, block, codes, scales, copy, stream); break;
-    case 32: launch_grp<32, S, COPY>(src, n, block, codes, scales, copy, stream); break;
-    default: launch_grp<64, S, COPY>(src, n, block, codes, scales, copy, stream); break;
+    case 16: launch_grp<16, S, COPY>(src, n, block, codes, scales, copy, on_lines, stream); break;
+    case 32: launch_grp<32, S, COPY>(src, n, block, codes, scales, copy, on_lines, stream); break;
+    default: launch_grp<64, S, COPY>(src, n, block, codes, scales, copy, on_lines, stream); break;
     }
 }
 
 template <bool COPY>
 void launch_vector(const uint16_t *src, size_t n, uint32_t block, int8_t *codes, float *scales,
-                   uint16_t *copy, hipStream_t stream) {
+                   uint16_t *copy, bool on_lines, hipStream_t stream) {
     switch (block) {
-    case 64: launch_vec<64, COPY>(src, n, codes, scales, copy, stream); break;
-    case 128: launch_vec<128, COPY>(src, n, codes, scales, copy, stream); break;
-    case 256: launch_vec<256, COPY>(src, n, codes, scales, copy, stream); break;
-    case 512: launch_vec<512, COPY>(src, n, codes, scales, copy, stream); break;
-    case 1024: launch_vec<1024, COPY>(src, n, codes, scales, copy, stream); break;
-    case 2048: launch_vec<2048, COPY>(src, n, codes, scales, copy, stream); break;
-    case 4096: launch_vec<4096, COPY>(src, n, codes, scales, copy, stream); break;
+    case 64: launch_vec<64, COPY>(src, n, codes, scales, copy, on_lines, stream); break;
+    case 128: launch_vec<128, COPY>(src, n, codes, scales, copy, on_lines, stream); break;
+    case 256: launch_vec<256, COPY>(src, n, codes, scales, copy, on_lines, stream); break;
+    case 512: launch_vec<512, COPY>(src, n, codes, scales, copy, on_lines, stream); break;
+    case 1024: launch_vec<1024, COPY>(src, n, codes, scales, copy, on_lines, stream); break;
+    case 2048: launch_vec<2048, COPY>(src, n, codes, scales, copy, on_lines, stream); break;
+    case 4096: launch_vec<4096, COPY>(src, n, codes, scales, copy, on_lines, stream); break;
     default: {
         const GroupShape sh =
             COPY ? group_shape(block / 8, 16, ZPP_QUANT_COPY_GROUP_MIN_FILL, 2)
                  : group_shape(block / 8, 16, ZPP_QUANT_GROUP_MIN_FILL, 2);
         if (sh.S <= 2)
-            launch_grp_g<2, COPY>(sh.G, src, n, block, codes, scales, copy, stream);
+            launch_grp_g<2, COPY>(sh.G, src, n, block, codes, scales, copy, on_lines, stream);
         else if (sh.S <= 4)
-            launch_grp_g<4, COPY>(sh.G, src, n, block, codes, scales, copy, stream);
+            launch_grp_g<4, COPY>(sh.G, src, n, block, codes, scales, copy, on_lines, stream);
         else if (sh.S <= 8)
-            launch_grp_g<8, COPY>(sh.G, src, n, block, codes, scales, copy, stream);
+            launch_grp_g<8, COPY>(sh.G, src, n, block, codes, scales, copy, on_lines, stream);
         else
-            launch_grp_g<16, COPY>(sh.G, src, n, block, codes, scales, copy, stream);
+            launch_grp_g<16, COPY>(sh.G, src, n, block, codes, scales, copy, on_lines, stream);
     }
     }
 }
@@ -324,26 +304,18 @@ void launch_vector(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
 }  // namespace
 
 hipError_t launch_quantize_copy(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
-                                float *scales, uint16_t *copy, bool vector_path,
+                                float *scales, uint16_t *copy, bool on_lines,
                                 hipStream_t stream) {
-    if (vector_path) {
-        if (copy)
-            launch_vector<true>(src, n, block, codes, scales, copy, stream);
-        else
-            launch_vector<false>(src, n, block, codes, scales, nullptr, stream);
-    } else {
-        const size_t nblocks = (n + block - 1) / block;
-        const size_t need = (nblocks + (kThreads / kWave) - 1) / (kThreads / kWave);
-        const unsigned grid = (unsigned)(need < (1u << 20) ? need : (1u << 20));
-        hipLaunchKernelGGL(quant_scalar_kernel, dim3(grid), dim3(kThreads), 0, stream, src, n,
-                           block, codes, scales, copy);
-    }
+    if (copy)
+        launch_vector<true>(src, n, block, codes, scales, copy, on_lines, stream);
+    else
+        launch_vector<false>(src, n, block, codes, scales, nullptr, on_lines, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_quantize(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
-                           float *scales, bool vector_path, hipStream_t stream) {
-    return launch_quantize_copy(src, n, block, codes, scales, nullptr, vector_path, stream);
+                           float *scales, bool on_lines, hipStream_t stream) {
+    return launch_quantize_copy(src, n, block, codes, scales, nullptr, on_lines, stream);
 }
 
 }  // namespace zpp

@@ -77,7 +77,7 @@ __device__ __forceinline__ void recv_tile(const RecvArgs<GS> &a, size_t base, ui
 
 template <bool ADAMW, bool MANY, class GS>
 __global__ __launch_bounds__(kWave) void recv_adam_kernel(RecvArgs<GS> a, TileSpan tiles) {
-    const uint32_t t = (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, recv_xcd_run<GS>());
+    const uint32_t t = tile_of(blockIdx.x, gridDim.x, tiles, recv_xcd_run<GS>());
     const size_t base = (tiles.first + t) * 256;
     if (__builtin_expect(t < tiles.whole, 1))
         recv_tile<ADAMW, true, MANY>(a, base, 256);
@@ -85,29 +85,10 @@ __global__ __launch_bounds__(kWave) void recv_adam_kernel(RecvArgs<GS> a, TileSp
         recv_tile<ADAMW, false, MANY>(a, base, tiles.tail);
 }
 
-template <bool ADAMW, class GS>
-__device__ __forceinline__ void scalar_step(const RecvArgs<GS> &a, size_t i) {
-    const float g = grad_at(a.src, i);
-    float p = a.p[i], m = a.m[i], v = a.v[i];
-    adam_update<ADAMW>(p, m, v, g, a.c);
-    a.p[i] = p;
-    a.m[i] = m;
-    a.v[i] = v;
-    a.out[i] = (uint16_t)bf16_rne_bits(p);
-}
-
-// Any alignment: one element per thread, grid-stride.
-template <bool ADAMW, class GS>
-__global__ __launch_bounds__(kThreads) void recv_adam_scalar_kernel(RecvArgs<GS> a) {
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < a.n; i += stride)
-        scalar_step<ADAMW, GS>(a, i);
-}
-
 template <bool MANY, class GS>
-void launch_recv_tiles(const RecvArgs<GS> &a, int residency, hipStream_t stream) {
+void launch_recv_tiles(const RecvArgs<GS> &a, int residency, bool on_lines, hipStream_t stream) {
     const size_t lds = residency_lds(residency);
-    for_tiles(a.n, 256, 1, kWave, [&](const TileSpan &tiles, unsigned grid) {
+    for_tiles(a.n, 256, 1, kWave, on_lines, [&](const TileSpan &tiles, unsigned grid) {
         if (a.c.adamw)
             hipLaunchKernelGGL((recv_adam_kernel<true, MANY, GS>), dim3(grid), dim3(kWave), lds,
                                stream, a, tiles);
@@ -118,25 +99,13 @@ void launch_recv_tiles(const RecvArgs<GS> &a, int residency, hipStream_t stream)
 }
 
 template <class GS>
-hipError_t launch_recv(const RecvArgs<GS> &a, int residency, bool vector_path,
-                       hipStream_t stream) {
-    if (vector_path) {
-        if (a.src.num_src >= kManySources)
-            residency = 0;  // left to the hardware (zpp_i4grad.h)
-        if (many_sources(a.src.num_src, a.src.block))
-            launch_recv_tiles<true>(a, residency, stream);
-        else
-            launch_recv_tiles<false>(a, residency, stream);
-    } else {
-        const size_t blocks = (a.n + kThreads - 1) / kThreads;
-        const unsigned grid = (unsigned)(blocks < (1u << 20) ? blocks : (1u << 20));
-        if (a.c.adamw)
-            hipLaunchKernelGGL((recv_adam_scalar_kernel<true, GS>), dim3(grid), dim3(kThreads), 0,
-                               stream, a);
-        else
-            hipLaunchKernelGGL((recv_adam_scalar_kernel<false, GS>), dim3(grid), dim3(kThreads),
-                               0, stream, a);
-    }
+hipError_t launch_recv(const RecvArgs<GS> &a, int residency, bool on_lines, hipStream_t stream) {
+    if (a.src.num_src >= kManySources)
+        residency = 0;  // left to the hardware (zpp_i4grad.h)
+    if (many_sources(a.src.num_src, a.src.block))
+        launch_recv_tiles<true>(a, residency, on_lines, stream);
+    else
+        launch_recv_tiles<false>(a, residency, on_lines, stream);
     return hipGetLastError();
 }
 
@@ -158,7 +127,7 @@ I4Grad make_i4grad(const uint8_t *const *src_codes, const float *const *src_scal
 hipError_t launch_receive_adam(float *p, float *m, float *v, const uint8_t *const *src_codes,
                                const float *const *src_scales, uint32_t num_src, uint32_t block,
                                float scale_out, uint16_t *out, size_t n, const AdamConsts &c,
-                               bool vector_path, hipStream_t stream) {
+                               bool on_lines, hipStream_t stream) {
     RecvArgs<I4Grad> a = {};
     a.src = make_i4grad(src_codes, src_scales, num_src, block, scale_out);
     a.p = p;
@@ -167,7 +136,7 @@ hipError_t launch_receive_adam(float *p, float *m, float *v, const uint8_t *cons
     a.out = out;
     a.n = n;
     a.c = c;
-    return launch_recv(a, ZPP_RECV_RESIDENCY, vector_path, stream);
+    return launch_recv(a, ZPP_RECV_RESIDENCY, on_lines, stream);
 }
 
 I4GradIl make_i4grad_il(const uint8_t *codes, const float *scales, uint32_t num_src,
@@ -184,7 +153,7 @@ I4GradIl make_i4grad_il(const uint8_t *codes, const float *scales, uint32_t num_
 hipError_t launch_receive_adam_il(float *p, float *m, float *v, const uint8_t *codes,
                                   const float *scales, uint32_t num_src, uint32_t block,
                                   float scale_out, uint16_t *out, size_t n, const AdamConsts &c,
-                                  bool vector_path, hipStream_t stream) {
+                                  bool on_lines, hipStream_t stream) {
     RecvArgs<I4GradIl> a = {};
     a.src = make_i4grad_il(codes, scales, num_src, block, scale_out);
     a.p = p;
@@ -193,7 +162,7 @@ hipError_t launch_receive_adam_il(float *p, float *m, float *v, const uint8_t *c
     a.out = out;
     a.n = n;
     a.c = c;
-    return launch_recv(a, ZPP_RECV_IL_RESIDENCY, vector_path, stream);
+    return launch_recv(a, ZPP_RECV_IL_RESIDENCY, on_lines, stream);
 }
 
 }  // namespace zpp

@@ -17,74 +17,57 @@
 #ifndef ZPP_REFRESH_RESIDENCY
 #define ZPP_REFRESH_RESIDENCY 0
 #endif
-#ifndef ZPP_REFRESH_MAX_GRID
-#define ZPP_REFRESH_MAX_GRID (1u << 20)
-#endif
 
 namespace zpp {
 namespace {
 
 constexpr int kRefreshThreads = ZPP_REFRESH_THREADS;
 
+// One tile of 512 U elements; the lanes of a partial tile's last vector go
+// element by element, all loads before the stores.
 template <int U>
 __global__ __launch_bounds__(kRefreshThreads) void refresh_vec_kernel(
-    uint16_t *__restrict__ dst, const uint16_t *__restrict__ src, size_t count) {
-    constexpr size_t kTile = (size_t)kRefreshThreads * 8 * U;  // 8 bf16 per 16-byte vector
-    const size_t ntiles = (count + kTile - 1) / kTile;
-    for (size_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const size_t base = t * kTile + (size_t)threadIdx.x * 8;
-        if ((t + 1) * kTile <= count) {
-            u32x4 x[U];
+    uint16_t *__restrict__ dst, const uint16_t *__restrict__ src, TileSpan tiles) {
+    constexpr uint32_t kTile = kRefreshThreads * 8 * U;  // 8 bf16 per 16-byte vector
+    const uint32_t t = tile_of(blockIdx.x, gridDim.x, tiles, 0);
+    dst += (tiles.first + t) * kTile;
+    src += (tiles.first + t) * kTile;
+    if (__builtin_expect(t < tiles.whole, 1)) {
+        u32x4 x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                x[u] = ld_nt(reinterpret_cast<const u32x4 *>(src + base +
-                                                             (size_t)u * kRefreshThreads * 8));
+        for (int u = 0; u < U; ++u)
+            x[u] = ld_nt_at<u32x4, 2>(src + (u * kRefreshThreads + threadIdx.x) * 8);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                st_nt(reinterpret_cast<u32x4 *>(dst + base + (size_t)u * kRefreshThreads * 8),
-                      x[u]);
-        } else {
+        for (int u = 0; u < U; ++u)
+            st_nt_at<u32x4, 2>(dst + (u * kRefreshThreads + threadIdx.x) * 8, x[u]);
+    } else {
+        uint16_t x[U][8];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const size_t i0 = base + (size_t)u * kRefreshThreads * 8;
-                if (i0 + 8 <= count) {
-                    st_nt(reinterpret_cast<u32x4 *>(dst + i0),
-                          ld_nt(reinterpret_cast<const u32x4 *>(src + i0)));
-                } else {
-                    for (size_t i = i0; i < count && i < i0 + 8; ++i)
-                        dst[i] = src[i];
-                }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                x[u][e] = src[clamped((u * kRefreshThreads + threadIdx.x) * 8 + e, tiles.tail)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t i = (u * kRefreshThreads + threadIdx.x) * 8 + e;
+                if (i < tiles.tail)
+                    dst[i] = x[u][e];
             }
-        }
     }
-}
-
-__global__ __launch_bounds__(kThreads) void refresh_scalar_kernel(uint16_t *__restrict__ dst,
-                                                                  const uint16_t *__restrict__ src,
-                                                                  size_t count) {
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < count; i += stride)
-        dst[i] = src[i];
 }
 
 }  // namespace
 
-hipError_t launch_refresh(uint16_t *dst, const uint16_t *src, size_t count, bool vector_path,
+hipError_t launch_refresh(uint16_t *dst, const uint16_t *src, size_t count, bool on_lines,
                           hipStream_t stream) {
-    if (vector_path) {
-        constexpr size_t kTile = (size_t)kRefreshThreads * 8 * ZPP_REFRESH_UNROLL;
-        const size_t tiles = (count + kTile - 1) / kTile;
-        const unsigned grid =
-            (unsigned)(tiles < ZPP_REFRESH_MAX_GRID ? tiles : ZPP_REFRESH_MAX_GRID);
-        hipLaunchKernelGGL((refresh_vec_kernel<ZPP_REFRESH_UNROLL>), dim3(grid),
-                           dim3(kRefreshThreads), residency_lds(ZPP_REFRESH_RESIDENCY), stream,
-                           dst, src, count);
-    } else {
-        const size_t blocks = (count + kThreads - 1) / kThreads;
-        const unsigned grid = (unsigned)(blocks < (1u << 20) ? blocks : (1u << 20));
-        hipLaunchKernelGGL(refresh_scalar_kernel, dim3(grid), dim3(kThreads), 0, stream, dst,
-                           src, count);
-    }
+    for_tiles(count, kRefreshThreads * 8 * ZPP_REFRESH_UNROLL, 1, kRefreshThreads, on_lines,
+              [&](const TileSpan &tiles, unsigned grid) {
+                  hipLaunchKernelGGL((refresh_vec_kernel<ZPP_REFRESH_UNROLL>), dim3(grid),
+                                     dim3(kRefreshThreads), residency_lds(ZPP_REFRESH_RESIDENCY),
+                                     stream, dst, src, tiles);
+              });
     return hipGetLastError();
 }
 

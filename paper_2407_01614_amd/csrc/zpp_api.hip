@@ -3,6 +3,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "zpp.h"
 #include "zpp_launch.h"
 
@@ -16,6 +18,15 @@ zpp_status hip_fail(hipError_t e) {
 }
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
+
+// Whether every output (NULL: not asked for) starts on a 128-byte line, which
+// decides the order a launch's workgroups take (zpp_launch.h).
+bool on_lines(std::initializer_list<const void *> outputs) {
+    for (const void *p : outputs)
+        if (!aligned(p, 128))
+            return false;
+    return true;
+}
 
 // Do [a, a + abytes) and [b, b + bbytes) share a byte?
 bool overlaps(const void *a, size_t abytes, const void *b, size_t bbytes) {
@@ -117,10 +128,9 @@ ZPP_API zpp_status zpp_adam_partition_step(float *master, float *exp_avg, float 
     const size_t bytes[5] = {4 * n, 4 * n, 4 * n, 4 * n, 2 * n};
     if (any_overlap(ptrs, bytes, 5))
         return ZPP_EOVERLAP;
-    const bool vec = aligned(master, 16) && aligned(exp_avg, 16) && aligned(exp_avg_sq, 16) &&
-                     aligned(grad, 16) && aligned(primary_bf16, 16);
+    const bool lines = on_lines({master, exp_avg, exp_avg_sq, primary_bf16});
     const hipError_t e = zpp::launch_adam(master, exp_avg, exp_avg_sq, grad, primary_bf16, n,
-                                          adam_consts(*hp), vec, stream);
+                                          adam_consts(*hp), lines, stream);
     return e == hipSuccess ? ZPP_OK : hip_fail(e);
 }
 
@@ -154,12 +164,11 @@ ZPP_API zpp_status zpp_adam_step_refresh_quantize(float *master, float *exp_avg,
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool vec = aligned(master, 16) && aligned(exp_avg, 16) && aligned(exp_avg_sq, 16) &&
-                         aligned(grad, 16) && aligned(primary_bf16, 8) &&
-                         aligned(secondary_bf16, 8) && aligned(codes, 4);
+        const bool lines =
+            on_lines({master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16, codes});
         const hipError_t e =
             zpp::launch_fused(master, exp_avg, exp_avg_sq, grad, primary_bf16, secondary_bf16,
-                              codes, scales, n, block, adam_consts(*hp), vec, stream);
+                              codes, scales, n, block, adam_consts(*hp), lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -183,8 +192,8 @@ ZPP_API zpp_status zpp_refresh_secondary(uint16_t *secondary_bf16, const uint16_
     if (st != ZPP_OK)
         return st;
     if (count) {
-        const bool vec = aligned(secondary_bf16, 16) && aligned(src_bf16, 16);
-        const hipError_t e = zpp::launch_refresh(secondary_bf16, src_bf16, count, vec, stream);
+        const bool lines = on_lines({secondary_bf16});
+        const hipError_t e = zpp::launch_refresh(secondary_bf16, src_bf16, count, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -210,8 +219,8 @@ ZPP_API zpp_status zpp_quantize_blockwise_i8(const uint16_t *src_bf16, size_t n,
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool vec = aligned(src_bf16, 16) && aligned(codes, 8);
-        const hipError_t e = zpp::launch_quantize(src_bf16, n, block, codes, scales, vec, stream);
+        const bool lines = on_lines({codes});
+        const hipError_t e = zpp::launch_quantize(src_bf16, n, block, codes, scales, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -239,9 +248,9 @@ ZPP_API zpp_status zpp_refresh_quantize_i8(uint16_t *secondary_bf16, const uint1
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool vec = aligned(src_bf16, 16) && aligned(secondary_bf16, 16) && aligned(codes, 8);
+        const bool lines = on_lines({secondary_bf16, codes});
         const hipError_t e =
-            zpp::launch_quantize_copy(src_bf16, n, block, codes, scales, secondary_bf16, vec,
+            zpp::launch_quantize_copy(src_bf16, n, block, codes, scales, secondary_bf16, lines,
                                       stream);
         if (e != hipSuccess)
             return hip_fail(e);
@@ -270,7 +279,6 @@ ZPP_API zpp_status zpp_dequant_gather_layer(const int8_t *const *shard_codes,
         return ZPP_EINVAL;
     const size_t nblocks = (shard_elems + block - 1) / block;
     zpp::GatherShards shards = {};
-    bool vec = (shard_elems % 16 == 0) && aligned(out_bf16, 16);
     for (uint32_t j = 0; j < num_shards; ++j) {
         if (!shard_codes[j] || !shard_scales[j])
             return ZPP_EINVAL;
@@ -278,7 +286,6 @@ ZPP_API zpp_status zpp_dequant_gather_layer(const int8_t *const *shard_codes,
             return ZPP_EALIGN;
         shards.codes[j] = shard_codes[j];
         shards.scales[j] = shard_scales[j];
-        vec = vec && aligned(shard_codes[j], 16);
     }
     if (layer_elems) {
         if (!out_bf16)
@@ -296,8 +303,9 @@ ZPP_API zpp_status zpp_dequant_gather_layer(const int8_t *const *shard_codes,
             return st;
     }
     if (layer_elems) {
+        const bool lines = on_lines({out_bf16}) && shard_elems % 64 == 0;
         const hipError_t e = zpp::launch_gather(shards, num_shards, shard_elems, block,
-                                                layer_elems, out_bf16, vec, stream);
+                                                layer_elems, out_bf16, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -325,8 +333,8 @@ ZPP_API zpp_status zpp_quantize_blockwise_i4(const float *src, size_t n, uint32_
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool vec = aligned(src, 16) && aligned(codes, 2);
-        const hipError_t e = zpp::launch_quantize_i4(src, n, block, codes, scales, vec, stream);
+        const bool lines = on_lines({codes});
+        const hipError_t e = zpp::launch_quantize_i4(src, n, block, codes, scales, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -351,13 +359,11 @@ ZPP_API zpp_status zpp_dequant_reduce_i4(const uint8_t *const *src_codes,
         return ZPP_EINVAL;
     const size_t nblocks = (n + block - 1) / block;
     const size_t nbytes = (n + 1) / 2;
-    bool vec = aligned(out, 16);
     for (uint32_t q = 0; q < num_src; ++q) {
         if (!src_codes[q] || !src_scales[q])
             return ZPP_EINVAL;
         if (!aligned(src_scales[q], 4))
             return ZPP_EALIGN;
-        vec = vec && aligned(src_codes[q], 2);
     }
     if (n) {
         if (!out)
@@ -375,8 +381,9 @@ ZPP_API zpp_status zpp_dequant_reduce_i4(const uint8_t *const *src_codes,
             return st;
     }
     if (n) {
+        const bool lines = on_lines({out});
         const hipError_t e = zpp::launch_dequant_reduce_i4(src_codes, src_scales, num_src, n,
-                                                           block, scale_out, out, vec, stream);
+                                                           block, scale_out, out, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -407,14 +414,11 @@ ZPP_API zpp_status zpp_qgz_receive_adam_step(float *master, float *exp_avg, floa
         return ZPP_EINVAL;
     const size_t nblocks = (n + block - 1) / block;
     const size_t nbytes = (n + 1) / 2;
-    bool vec = aligned(master, 16) && aligned(exp_avg, 16) && aligned(exp_avg_sq, 16) &&
-               aligned(primary_bf16, 8);
     for (uint32_t q = 0; q < num_src; ++q) {
         if (!src_codes[q] || !src_scales[q])
             return ZPP_EINVAL;
         if (!aligned(src_scales[q], 4))
             return ZPP_EALIGN;
-        vec = vec && aligned(src_codes[q], 2);
     }
     if (n) {
         if (!master || !exp_avg || !exp_avg_sq || !primary_bf16)
@@ -438,9 +442,10 @@ ZPP_API zpp_status zpp_qgz_receive_adam_step(float *master, float *exp_avg, floa
             return st;
     }
     if (n) {
+        const bool lines = on_lines({master, exp_avg, exp_avg_sq, primary_bf16});
         const hipError_t e = zpp::launch_receive_adam(master, exp_avg, exp_avg_sq, src_codes,
                                                       src_scales, num_src, block, scale_out,
-                                                      primary_bf16, n, adam_consts(*hp), vec,
+                                                      primary_bf16, n, adam_consts(*hp), lines,
                                                       stream);
         if (e != hipSuccess)
             return hip_fail(e);
@@ -472,14 +477,11 @@ ZPP_API zpp_status zpp_qgz_receive_step_refresh_quantize(
     const size_t gblocks = (n + grad_block - 1) / grad_block;
     const size_t nblocks = (n + block - 1) / block;
     const size_t nbytes = (n + 1) / 2;
-    bool vec = aligned(master, 16) && aligned(exp_avg, 16) && aligned(exp_avg_sq, 16) &&
-               aligned(primary_bf16, 8) && aligned(secondary_bf16, 8) && aligned(codes, 4);
     for (uint32_t q = 0; q < num_src; ++q) {
         if (!src_codes[q] || !src_scales[q])
             return ZPP_EINVAL;
         if (!aligned(src_scales[q], 4))
             return ZPP_EALIGN;
-        vec = vec && aligned(src_codes[q], 2);
     }
     if (n) {
         if (!master || !exp_avg || !exp_avg_sq || !primary_bf16 || !codes || !scales)
@@ -505,9 +507,11 @@ ZPP_API zpp_status zpp_qgz_receive_step_refresh_quantize(
             return st;
     }
     if (n) {
+        const bool lines =
+            on_lines({master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16, codes});
         const hipError_t e = zpp::launch_fused_receive(
             master, exp_avg, exp_avg_sq, src_codes, src_scales, num_src, grad_block, scale_out,
-            primary_bf16, secondary_bf16, codes, scales, n, block, adam_consts(*hp), vec, stream);
+            primary_bf16, secondary_bf16, codes, scales, n, block, adam_consts(*hp), lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -539,9 +543,9 @@ ZPP_API zpp_status zpp_quantize_blockwise_i4_interleaved(const float *src, size_
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool vec = aligned(src, 16) && aligned(codes, 2);
+        const bool lines = on_lines({codes});
         const hipError_t e = zpp::launch_quantize_i4_il(src, n, block, source, num_src, codes,
-                                                        scales, vec, stream);
+                                                        scales, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -582,9 +586,9 @@ ZPP_API zpp_status zpp_dequant_reduce_i4_interleaved(const uint8_t *codes, const
             return st;
     }
     if (n) {
-        const bool vec = aligned(out, 16) && aligned(codes, 2);
+        const bool lines = on_lines({out});
         const hipError_t e = zpp::launch_dequant_reduce_i4_il(codes, scales, num_src, n, block,
-                                                              scale_out, out, vec, stream);
+                                                              scale_out, out, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -633,11 +637,10 @@ ZPP_API zpp_status zpp_qgz_receive_adam_step_interleaved(
             return st;
     }
     if (n) {
-        const bool vec = aligned(master, 16) && aligned(exp_avg, 16) && aligned(exp_avg_sq, 16) &&
-                         aligned(primary_bf16, 8) && aligned(codes, 2);
+        const bool lines = on_lines({master, exp_avg, exp_avg_sq, primary_bf16});
         const hipError_t e = zpp::launch_receive_adam_il(master, exp_avg, exp_avg_sq, codes,
                                                          scales, num_src, block, scale_out,
-                                                         primary_bf16, n, adam_consts(*hp), vec,
+                                                         primary_bf16, n, adam_consts(*hp), lines,
                                                          stream);
         if (e != hipSuccess)
             return hip_fail(e);
@@ -693,12 +696,11 @@ ZPP_API zpp_status zpp_qgz_receive_step_refresh_quantize_interleaved(
             return st;
     }
     if (n) {
-        const bool vec = aligned(master, 16) && aligned(exp_avg, 16) && aligned(exp_avg_sq, 16) &&
-                         aligned(primary_bf16, 8) && aligned(secondary_bf16, 8) &&
-                         aligned(codes, 4) && aligned(src_codes, 2);
+        const bool lines =
+            on_lines({master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16, codes});
         const hipError_t e = zpp::launch_fused_receive_il(
             master, exp_avg, exp_avg_sq, src_codes, src_scales, num_src, grad_block, scale_out,
-            primary_bf16, secondary_bf16, codes, scales, n, block, adam_consts(*hp), vec, stream);
+            primary_bf16, secondary_bf16, codes, scales, n, block, adam_consts(*hp), lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }

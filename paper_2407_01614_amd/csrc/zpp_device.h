@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "zpp_chunk.h"
 #include "zpp_launch.h"
 
 namespace zpp {
@@ -72,7 +73,27 @@ struct TileSpan {
     size_t first;
     uint32_t whole;
     uint32_t tail;
+    uint32_t on_lines;  // every output starts on a cache line
 };
+
+// Outputs that do not start on a 128-byte line: a wave's store then ends inside
+// a line that the next tile's wave goes on with, and two XCDs that each write
+// their part of it cost two partial writes of memory.  So neighbouring tiles
+// run on one XCD, in runs of this many, and their parts meet in its L2: the
+// Adam step at 13.1 M elements off by one 81.3 us without, 70.2 / 69.6 /
+// 69.3 / 68.9 with runs of 16 / 32 / 64 / 128 (100 M: 618, 543 / 531 / 518 /
+// 511), the fused step 105 and 80, the receive step 82 and 72, the gather of
+// 200 M 121 and 102.  Stored as ordinary, temporal ones they were slower (73
+// us for the Adam step, 95 without the runs).
+constexpr size_t kOffLineXcdRun = 128;
+
+// The tile of workgroup w of the launch: renumbered in runs of `run` per XCD
+// where the outputs start on lines.
+__device__ __forceinline__ uint32_t tile_of(uint32_t w, uint32_t grid, const TileSpan &tiles,
+                                            size_t run) {
+    return (uint32_t)(tiles.on_lines ? xcd_grouped(w, grid, run)
+                                     : xcd_grouped(w, grid, kOffLineXcdRun));
+}
 
 // One-shot grids over the tiles of C elements of an array of n, `per_wg` of
 // them to a workgroup of `threads`, in as many launches as HIP's limit of
@@ -81,37 +102,43 @@ struct TileSpan {
 // kernel the code of a whole tile is straight, and the rare partial tile's
 // lies behind it.
 template <class F>
-void for_tiles(size_t n, uint32_t C, uint32_t per_wg, uint32_t threads, F &&launch) {
+void for_tiles(size_t n, uint32_t C, uint32_t per_wg, uint32_t threads, bool on_lines, F &&launch) {
     const size_t tiles = (n + C - 1) / C, most = (((size_t)1 << 31) / threads) * per_wg;
     for (size_t t = 0; t < tiles; t += most) {
         const size_t count = tiles - t < most ? tiles - t : most;
         const size_t whole = n / C - t < count ? n / C - t : count;
-        launch(TileSpan{t, (uint32_t)whole, whole < count ? (uint32_t)(n % C) : 0u},
+        launch(TileSpan{t, (uint32_t)whole, whole < count ? (uint32_t)(n % C) : 0u, on_lines},
                (unsigned)((count + per_wg - 1) / per_wg));
     }
 }
 
 // Streaming accesses: every byte is touched once, so loads and stores are
 // marked non-temporal.
-#ifndef ZPP_NT_LOAD
-#define ZPP_NT_LOAD 1
-#endif
-#ifndef ZPP_NT_STORE
-#define ZPP_NT_STORE 1
-#endif
 template <typename T>
 __device__ __forceinline__ T ld_nt(const T *p) {
-    if constexpr (ZPP_NT_LOAD)
-        return __builtin_nontemporal_load(p);
-    else
-        return *p;
+    return __builtin_nontemporal_load(p);
 }
 template <typename T>
 __device__ __forceinline__ void st_nt(T *p, T v) {
-    if constexpr (ZPP_NT_STORE)
-        __builtin_nontemporal_store(v, p);
-    else
-        *p = v;
+    __builtin_nontemporal_store(v, p);
+}
+
+// The same for vectors at addresses that are aligned to an element (A bytes)
+// and no further: the hardware takes vector accesses of global memory at any
+// address, so one kernel serves every alignment.  Kernels of their own for
+// arrays off the vectors' alignment, an element at a time, took at 13.1 M
+// elements off by one (us, against these accesses): the int8 quantizer 23.3
+// (10.0), the dequant-reduce of 8 copies 110 (30), the receive step 165 (72),
+// the fused step 126 (80), the gather of 16.8 M 29.1 (10.8).
+template <class V, int A>
+__device__ __forceinline__ V ld_nt_at(const void *p) {
+    typedef V U __attribute__((aligned(A)));
+    return __builtin_nontemporal_load(reinterpret_cast<const U *>(p));
+}
+template <class V, int A>
+__device__ __forceinline__ void st_nt_at(void *p, V v) {
+    typedef V U __attribute__((aligned(A)));
+    __builtin_nontemporal_store(v, reinterpret_cast<U *>(p));
 }
 
 // Four consecutive elements i .. i+3 of a tile whose arrays start at p and
@@ -129,7 +156,7 @@ __device__ __forceinline__ uint32_t clamped(uint32_t i, uint32_t r) { return i <
 template <bool WHOLE>
 __device__ __forceinline__ f32x4 load4(const float *p, uint32_t i, uint32_t r) {
     if constexpr (WHOLE)
-        return ld_nt(reinterpret_cast<const f32x4 *>(p + i));
+        return ld_nt_at<f32x4, 4>(p + i);
     else
         return f32x4{p[clamped(i, r)], p[clamped(i + 1, r)], p[clamped(i + 2, r)],
                      p[clamped(i + 3, r)]};
@@ -138,7 +165,7 @@ __device__ __forceinline__ f32x4 load4(const float *p, uint32_t i, uint32_t r) {
 template <bool WHOLE>
 __device__ __forceinline__ void store4(float *p, uint32_t i, uint32_t r, const f32x4 &v) {
     if constexpr (WHOLE) {
-        st_nt(reinterpret_cast<f32x4 *>(p + i), v);
+        st_nt_at<f32x4, 4>(p + i, v);
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -151,7 +178,7 @@ __device__ __forceinline__ void store4(float *p, uint32_t i, uint32_t r, const f
 template <bool WHOLE>
 __device__ __forceinline__ void store4_bf16(uint16_t *p, uint32_t i, uint32_t r, const u32x2 &v) {
     if constexpr (WHOLE) {
-        st_nt(reinterpret_cast<u32x2 *>(p + i), v);
+        st_nt_at<u32x2, 2>(p + i, v);
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -164,7 +191,7 @@ __device__ __forceinline__ void store4_bf16(uint16_t *p, uint32_t i, uint32_t r,
 template <bool WHOLE>
 __device__ __forceinline__ void store4_i8(int8_t *p, uint32_t i, uint32_t r, uint32_t v) {
     if constexpr (WHOLE) {
-        st_nt(reinterpret_cast<uint32_t *>(p + i), v);
+        st_nt_at<uint32_t, 1>(p + i, v);
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)

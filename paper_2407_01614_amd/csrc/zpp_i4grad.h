@@ -42,17 +42,6 @@ __device__ __forceinline__ float i4grad_scaled(float acc, float scale_out) {
     return acc * scale_out;
 }
 
-// The gradient of one element (the any-alignment kernels).
-__device__ __forceinline__ float i4grad_at(const I4Grad &s, size_t i) {
-    float acc = 0.0f;
-    for (uint32_t q = 0; q < s.num_src; ++q) {
-        const uint32_t byte = s.codes[q][i / 2];
-        const uint32_t nib = (i % 2 == 0) ? (byte & 0xFu) : (byte >> 4);
-        acc = __builtin_fmaf(i4_code(nib, 0), s.scales[q][block_of(s.block, i)], acc);
-    }
-    return i4grad_scaled(acc, s.scale_out);
-}
-
 // The gradient of a lane's groups of four consecutive elements, group g at
 // 256 g + 4 lane of a tile: one 2-byte code load and one scale per source and
 // group.  N sources at a time, all their loads in flight before the fma
@@ -103,7 +92,7 @@ struct I4From {
     __device__ __forceinline__ uint32_t codes(uint32_t q, int g) const {
         const uint8_t *c = s.codes[q] + byte0;
         if constexpr (WHOLE)
-            return ld_nt(reinterpret_cast<const uint16_t *>(c + byte[g]));
+            return ld_nt_at<uint16_t, 1>(c + byte[g]);
         else
             return c[byte[g]] | (uint32_t)c[byte1[g]] << 8;
     }
@@ -148,17 +137,6 @@ __device__ __forceinline__ size_t il_code_byte(const I4GradIl &s, size_t i, size
     return (k * s.num_src + q) * (B / 2) + ((i - k * B) >> 1);
 }
 
-__device__ __forceinline__ float i4grad_at(const I4GradIl &s, size_t i) {
-    float acc = 0.0f;
-    const size_t k = block_of(s.block, i);
-    for (uint32_t q = 0; q < s.num_src; ++q) {
-        const uint32_t byte = s.codes[il_code_byte(s, i, k, q)];
-        const uint32_t nib = (i % 2 == 0) ? (byte & 0xFu) : (byte >> 4);
-        acc = __builtin_fmaf(i4_code(nib, 0), s.scales[k * s.num_src + q], acc);
-    }
-    return i4grad_scaled(acc, s.scale_out);
-}
-
 // The loads of the separate layout (a 2-byte code load and a scale per source),
 // addressed in the interleaved buffer: a wave's loads of one source are 128
 // contiguous bytes, and those of all sources lie within one run of the buffer.
@@ -171,7 +149,7 @@ struct I4IlFrom {
     const float *scales[G];
     template <bool WHOLE>
     __device__ __forceinline__ uint32_t codes(uint32_t q, int g) const {
-        return ld_nt(reinterpret_cast<const uint16_t *>(base[g] + q * stride));
+        return ld_nt_at<uint16_t, 1>(base[g] + q * stride);
     }
     __device__ __forceinline__ float scale(uint32_t q, int g) const { return scales[g][q]; }
 };
@@ -223,14 +201,14 @@ struct TileCodes {
     size_t byte;
     uint32_t lane;
     __device__ __forceinline__ uint32_t operator()(uint32_t q) const {
-        return ld_nt(reinterpret_cast<const uint16_t *>(s.codes[q] + byte + 2 * lane));
+        return ld_nt_at<uint16_t, 1>(s.codes[q] + byte + 2 * lane);
     }
 };
 struct TileCodesIl {
     const uint8_t *base;
     uint32_t stride, lane;
     __device__ __forceinline__ uint32_t operator()(uint32_t q) const {
-        return ld_nt(reinterpret_cast<const uint16_t *>(base + q * stride + 2 * lane));
+        return ld_nt_at<uint16_t, 1>(base + q * stride + 2 * lane);
     }
 };
 __device__ __forceinline__ TileCodes tile_codes(const I4Grad &s, size_t base, size_t,
@@ -336,8 +314,5 @@ __device__ __forceinline__ void grad_tile(f32x4 (&r)[G], const GS &s, size_t bas
 inline bool many_sources(uint32_t num_src, const BlockDiv &block) {
     return num_src >= kManySources && block.block % 256 == 0;
 }
-
-__device__ __forceinline__ float grad_at(const I4Grad &s, size_t i) { return i4grad_at(s, i); }
-__device__ __forceinline__ float grad_at(const I4GradIl &s, size_t i) { return i4grad_at(s, i); }
 
 }  // namespace zpp

@@ -1,5 +1,7 @@
 // Internal launchers behind the C ABI.  Arguments are already validated; each
 // launcher only enqueues its kernel on `stream` and returns the launch error.
+// `on_lines`: every output array starts on a 128-byte line (kOffLineXcdRun in
+// zpp_device.h says what that decides); nothing else depends on alignment.
 #pragma once
 
 #include <hip/hip_runtime_api.h>
@@ -48,25 +50,25 @@ struct AdamConsts {
 };
 
 hipError_t launch_adam(float *p, float *m, float *v, const float *g, uint16_t *out, size_t n,
-                       const AdamConsts &c, bool vector_path, hipStream_t stream);
+                       const AdamConsts &c, bool on_lines, hipStream_t stream);
 
-hipError_t launch_refresh(uint16_t *dst, const uint16_t *src, size_t count, bool vector_path,
+hipError_t launch_refresh(uint16_t *dst, const uint16_t *src, size_t count, bool on_lines,
                           hipStream_t stream);
 
 hipError_t launch_quantize(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
-                           float *scales, bool vector_path, hipStream_t stream);
+                           float *scales, bool on_lines, hipStream_t stream);
 
 // The quantization that also stores the bf16 it reads to `copy`: the
 // secondary refresh and its quantization in one pass.
 hipError_t launch_quantize_copy(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
-                                float *scales, uint16_t *copy, bool vector_path,
+                                float *scales, uint16_t *copy, bool on_lines,
                                 hipStream_t stream);
 
 // Adam step + bf16 primary + optional bf16 secondary + int8 codes/scales of
-// the primary, in one pass (vector_path) or as the three scalar kernels.
+// the primary.
 hipError_t launch_fused(float *p, float *m, float *v, const float *g, uint16_t *primary,
                         uint16_t *secondary, int8_t *codes, float *scales, size_t n,
-                        uint32_t block, const AdamConsts &c, bool vector_path,
+                        uint32_t block, const AdamConsts &c, bool on_lines,
                         hipStream_t stream);
 
 constexpr uint32_t kMaxShards = 64;
@@ -77,18 +79,18 @@ struct GatherShards {
 };
 
 hipError_t launch_gather(const GatherShards &shards, uint32_t num_shards, size_t shard_elems,
-                         uint32_t block, size_t layer_elems, uint16_t *out, bool vector_path,
+                         uint32_t block, size_t layer_elems, uint16_t *out, bool on_lines,
                          hipStream_t stream);
 
 // qgZ: int4 quantization of fp32 gradients, and the dequantize-and-reduce
 // of num_src quantized copies of one partition.
 hipError_t launch_quantize_i4(const float *src, size_t n, uint32_t block, uint8_t *codes,
-                              float *scales, bool vector_path, hipStream_t stream);
+                              float *scales, bool on_lines, hipStream_t stream);
 
 hipError_t launch_dequant_reduce_i4(const uint8_t *const *src_codes,
                                     const float *const *src_scales, uint32_t num_src, size_t n,
                                     uint32_t block, float scale_out, float *out,
-                                    bool vector_path, hipStream_t stream);
+                                    bool on_lines, hipStream_t stream);
 
 struct I4Grad;
 struct I4GradIl;
@@ -99,13 +101,12 @@ I4Grad make_i4grad(const uint8_t *const *src_codes, const float *const *src_scal
 
 // The fused pass with the qgZ receive: the gradient comes from num_src int4
 // copies (blocks of grad_block) instead of an fp32 array, then as
-// launch_fused (vector_path) or the receive step, refresh and quantization as
-// scalar kernels.
+// launch_fused.
 hipError_t launch_fused_receive(float *p, float *m, float *v, const uint8_t *const *src_codes,
                                 const float *const *src_scales, uint32_t num_src,
                                 uint32_t grad_block, float scale_out, uint16_t *primary,
                                 uint16_t *secondary, int8_t *codes, float *scales, size_t n,
-                                uint32_t block, const AdamConsts &c, bool vector_path,
+                                uint32_t block, const AdamConsts &c, bool on_lines,
                                 hipStream_t stream);
 
 // The int4 copies interleaved in one receive buffer (layout in
@@ -117,24 +118,24 @@ I4GradIl make_i4grad_il(const uint8_t *codes, const float *scales, uint32_t num_
 hipError_t launch_receive_adam_il(float *p, float *m, float *v, const uint8_t *codes,
                                   const float *scales, uint32_t num_src, uint32_t block,
                                   float scale_out, uint16_t *out, size_t n, const AdamConsts &c,
-                                  bool vector_path, hipStream_t stream);
+                                  bool on_lines, hipStream_t stream);
 hipError_t launch_fused_receive_il(float *p, float *m, float *v, const uint8_t *src_codes,
                                    const float *src_scales, uint32_t num_src, uint32_t grad_block,
                                    float scale_out, uint16_t *primary, uint16_t *secondary,
                                    int8_t *codes, float *scales, size_t n, uint32_t block,
-                                   const AdamConsts &c, bool vector_path, hipStream_t stream);
+                                   const AdamConsts &c, bool on_lines, hipStream_t stream);
 
 // The dequant-reduce from the interleaved receive buffer.
 hipError_t launch_dequant_reduce_i4_il(const uint8_t *codes, const float *scales, uint32_t num_src,
                                        size_t n, uint32_t block, float scale_out, float *out,
-                                       bool vector_path, hipStream_t stream);
+                                       bool on_lines, hipStream_t stream);
 
 // int4 quantization of one source's n values into its slots of an
 // interleaved receive buffer of num_src sources (num_src = 1: the plain
 // layout of launch_quantize_i4).
 hipError_t launch_quantize_i4_il(const float *src, size_t n, uint32_t block, uint32_t source,
                                  uint32_t num_src, uint8_t *codes, float *scales,
-                                 bool vector_path, hipStream_t stream);
+                                 bool on_lines, hipStream_t stream);
 
 // The qgZ receive fused into the partition step: the gradient of every
 // element is the dequantize-and-reduce of the num_src int4 sources (times
@@ -142,6 +143,6 @@ hipError_t launch_quantize_i4_il(const float *src, size_t n, uint32_t block, uin
 hipError_t launch_receive_adam(float *p, float *m, float *v, const uint8_t *const *src_codes,
                                const float *const *src_scales, uint32_t num_src, uint32_t block,
                                float scale_out, uint16_t *out, size_t n, const AdamConsts &c,
-                               bool vector_path, hipStream_t stream);
+                               bool on_lines, hipStream_t stream);
 
 }  // namespace zpp

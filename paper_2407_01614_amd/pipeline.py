@@ -27,7 +27,7 @@ edges on the primary and the codes are events too, so one iteration's gathers
 overlap the next iteration's optimizer step.
 
 Buffers are laid out flat in HBM, one allocation per array, 256-byte
-aligned (torch's allocator), so every kernel takes its 16-byte vector path.
+aligned (torch's allocator), so every output starts on a cache line.
 """
 import functools
 

@@ -163,3 +163,78 @@ def test_source_counts(zpp, k, n, block, interleaved):
     nan = np.isnan(ref)
     assert nan.any() and np.array_equal(nan, np.isnan(got))
     assert np.array_equal(got[~nan].view(np.uint32), ref[~nan].view(np.uint32))
+
+
+def every_call(zpp, n, block, offset, interleaved):
+    """Each call once with every array `offset` elements into its buffer: the
+    bits of all its outputs."""
+    got = {}
+
+    def arrays(*specs):
+        return [Buf(m, dt, offset, v) for m, dt, v in specs]
+
+    def take(name, bufs):
+        got.update({"%s[%d]" % (name, i): b.bits() for i, b in enumerate(bufs)})
+
+    nb = -(-n // block)
+    f32, i16, i8, u8 = torch.float32, torch.int16, torch.int8, torch.uint8
+    g, w = synth.gradients(n, 310), synth.bf16_weights(n, 311).view(np.int16)
+    st = state(n, n, offset)
+    gb, = arrays((n, f32, g))
+    zpp.adam_partition_step(*[b.t for b in st[:3]], gb.t, st[3].t, step=3, **HP)
+    take("adam", st)
+    st, out = state(n, n, offset), arrays((n, i16, None), (n, i8, None), (nb, f32, None))
+    zpp.adam_step_refresh_quantize(*[b.t for b in st[:3]], gb.t, st[3].t, *[b.t for b in out],
+                                   block=block, step=3, **HP)
+    take("fused", st + out)
+    wb, = arrays((n, i16, w))
+    out = arrays((n, i16, None), (n, i8, None), (nb, f32, None))
+    zpp.refresh_quantize_i8(out[0].t, wb.t, out[1].t, out[2].t, block=block)
+    take("refresh_quantize", out)
+    out = arrays((n, i16, None))
+    zpp.refresh_secondary(out[0].t, wb.t)
+    take("refresh", out)
+    out = arrays((n, i8, None), (nb, f32, None))
+    zpp.quantize_blockwise_i8(wb.t, out[0].t, out[1].t, block=block)
+    take("quantize_i8", out)
+    layer = arrays((2 * n - 3, i16, None))
+    zpp.dequant_gather_layer([out[0].t, out[0].t], [out[1].t, out[1].t], n, 2 * n - 3, layer[0].t,
+                             block=block)
+    take("gather", layer)
+    k = 3
+    if interleaved:
+        nc, ns = zpp.interleaved_sizes(n, block, k)
+        codes, scales = arrays((nc, u8, np.zeros(nc, np.uint8)), (ns, f32, np.zeros(ns, np.float32)))
+        for q in range(k):
+            zpp.quantize_blockwise_i4_interleaved(gb.t, codes.t, scales.t, source=q, num_src=k,
+                                                  block=block)
+        take("quantize_i4", (codes, scales))
+        src, reduce, step = ((codes.t, scales.t, k), zpp.dequant_reduce_i4_interleaved,
+                             zpp.qgz_receive_adam_step_interleaved)
+    else:
+        copies = [arrays(((n + 1) // 2, u8, None), (nb, f32, None)) for _ in range(k)]
+        for c, s in copies:
+            zpp.quantize_blockwise_i4(gb.t, c.t, s.t, block=block)
+            take("quantize_i4", (c, s))
+        src, reduce, step = (([c.t for c, _ in copies], [s.t for _, s in copies]),
+                             zpp.dequant_reduce_i4, zpp.qgz_receive_adam_step)
+    out = arrays((n, f32, None))
+    reduce(*src, n, out[0].t, block=block, scale_out=0.5)
+    take("reduce", out)
+    st = state(n, n, offset)
+    step(*[b.t for b in st[:3]], *src, st[3].t, block=block, scale_out=0.5, step=3, **HP)
+    take("receive", st)
+    return got
+
+
+@pytest.mark.parametrize("interleaved", [False, True], ids=["separate", "interleaved"])
+@pytest.mark.parametrize("n,block", [(2051, 256), (300 * 256 + 7, 64), (263001, 320), (9999, 4096)])
+def test_alignments(zpp, n, block, interleaved):
+    """Arrays that start off a vector's alignment, on it but off a cache line,
+    and on a line: the same bits, and nothing outside the arrays written.
+    (263,001 elements are more tiles than one run of workgroups per XCD.)"""
+    ref = every_call(zpp, n, block, 0, interleaved)
+    for offset in (1, 2, 3, 5, 8, 32, 64, 128):
+        got = every_call(zpp, n, block, offset, interleaved)
+        for name, r in ref.items():
+            assert np.array_equal(got[name], r), (name, offset)

@@ -14,6 +14,9 @@ LIB = os.path.join(PKG, "libzpp.so")
 # the plain HBM streams that bench.py times beside the kernels (not the path)
 CEILING_LIB = os.path.join(PKG, "libzpp_ceiling.so")
 CEILING_SOURCES = ["ceiling.hip"]
+# the Python binding's tensor marshalling (host code)
+MARSHAL_LIB = os.path.join(PKG, "_marshal.so")
+MARSHAL_SOURCE = "marshal.cpp"
 
 SOURCES = ["zpp_api.hip", "adam.hip", "refresh.hip", "quant.hip", "gather.hip", "fused.hip",
            "qgz.hip", "receive_adam.hip"]
@@ -69,6 +72,31 @@ def build_ceiling(verbose=False):
     return build(out=CEILING_LIB, verbose=verbose, sources=CEILING_SOURCES)
 
 
+def build_marshal(verbose=False):
+    """Compile the binding's tensor marshalling (host code against torch's
+    headers) into _marshal.so."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    tmp = MARSHAL_LIB + ".tmp%d" % os.getpid()
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           *[x for d in cpp_extension.include_paths() for x in ("-isystem", d)],
+           "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, MARSHAL_SOURCE), "-o", tmp,
+           "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stderr)
+    os.replace(tmp, MARSHAL_LIB)
+    return MARSHAL_LIB
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
     print(build_ceiling(verbose=True))
+    print(build_marshal(verbose=True))

@@ -2,9 +2,10 @@
 
 Argument marshalling only: every step of the partition path runs in the HIP
 kernels of the library.  PyTorch supplies device memory (tensors) and streams;
-events are plain HIP events created here.
+events are plain HIP events created here.  The tensor checks of the common
+case run natively (``_marshal``, csrc/marshal.cpp).
 
-The library must have been built (``paper_2407_01614_amd.build``); importing
+Both must have been built (``paper_2407_01614_amd.build``); importing
 this module fails loudly otherwise.  There is no fallback of any kind.
 """
 import ctypes
@@ -22,6 +23,8 @@ MAX_WAIT_EVENTS = 64
 if not os.path.exists(LIB_PATH):
     raise ImportError("libzpp.so is not built (%s); run `python -m paper_2407_01614_amd.build`"
                       % LIB_PATH)
+
+from . import _marshal  # noqa: E402  (built beside the library)
 
 _lib = ctypes.CDLL(LIB_PATH)
 _P = ctypes.c_void_p
@@ -189,7 +192,7 @@ def stream_handle(stream):
     """Raw hipStream_t of a torch stream, an int handle, or None (the current
     torch stream of the current device)."""
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     if stream.device.index != torch.cuda.current_device():
@@ -228,10 +231,75 @@ def _dev(t, dtypes, name):
     return t
 
 
-_F32 = (torch.float32,)
-_BF16 = (torch.bfloat16, torch.int16, torch.uint16)
-_I8 = (torch.int8,)
-_U8 = (torch.uint8, torch.int8)
+# dtypes an argument may have, as `_marshal` takes them
+_F32 = _marshal.F32
+_BF16 = _marshal.BF16 | _marshal.I16 | _marshal.U16
+_I8 = _marshal.I8
+_U8 = _marshal.U8 | _marshal.I8
+_OPTIONAL = _marshal.OPTIONAL
+_DTYPES = {_F32: (torch.float32,), _BF16: (torch.bfloat16, torch.int16, torch.uint16),
+           _I8: (torch.int8,), _U8: (torch.uint8, torch.int8)}
+
+
+def _numel(t, kind, name):
+    """Elements of the tensor that sets a call's size."""
+    if not isinstance(t, torch.Tensor):
+        _dev(t, _DTYPES[kind], name)
+    return t.numel()
+
+
+def _device():
+    """The current device, or -1 where there is none (no tensor is on it)."""
+    try:
+        return torch.cuda.current_device()
+    except (RuntimeError, AssertionError):
+        return -1
+
+
+def _addresses(names, too_small, *args):
+    """Addresses of the tensors in args = (tensor, kind, elements needed, ...),
+    in order; an optional one's None stays None.  `names` and the message
+    `too_small` are for the checks here, which run where the native ones do
+    not settle it."""
+    found = _marshal.addresses(_device(), *args)
+    if found is not None:
+        return found
+    given = []
+    for name, t, kind, need in zip(names, args[::3], args[1::3], args[2::3]):
+        if t is not None or not kind & _OPTIONAL:
+            _dev(t, _DTYPES[kind & ~_OPTIONAL], name)
+            given.append((t, need))
+    if any(t.numel() < need for t, need in given):
+        raise ValueError(too_small)
+    return tuple(None if t is None else t.data_ptr() for t in args[::3])
+
+
+def _address_array(tensors, kind, need, name, too_small):
+    """A C array of the addresses of a sequence of tensors; the messages as
+    for `_addresses`, with the tensor's place in them."""
+    found = _marshal.address_array(_device(), tensors, kind, need)
+    if found is not None:
+        return found
+    for j, t in enumerate(tensors):
+        _dev(t, _DTYPES[kind], "%s[%d]" % (name, j))
+        if t.numel() < need:
+            raise ValueError(too_small % j)
+    return (_P * len(tensors))(*[t.data_ptr() for t in tensors])
+
+
+def _events(wait_events):
+    waits = [_event_handle(e) for e in wait_events]
+    return ((_P * len(waits))(*waits) if waits else None), len(waits)
+
+
+def _sources(codes, scales, n, block):
+    """Address arrays of the int4 copies of n elements as separate arrays."""
+    k = len(codes)
+    if k != len(scales) or not 1 <= k <= MAX_SHARDS:
+        raise ValueError("1..%d sources, one scales tensor each" % MAX_SHARDS)
+    small = "source %d buffers too small"
+    return (_address_array(codes, _U8, (n + 1) // 2, "src_codes", small),
+            _address_array(scales, _F32, num_blocks(n, block), "src_scales", small), k)
 
 
 # --------------------------------------------------------------------------
@@ -240,19 +308,13 @@ _U8 = (torch.uint8, torch.int8)
 def adam_partition_step(master, exp_avg, exp_avg_sq, grad, primary_bf16, *, lr, beta1, beta2,
                         eps, weight_decay, step, adamw=True, n=None, stream=None):
     """zpp_adam_partition_step over the first ``n`` elements (default: all)."""
-    for t, name in ((master, "master"), (exp_avg, "exp_avg"), (exp_avg_sq, "exp_avg_sq"),
-                    (grad, "grad")):
-        _dev(t, _F32, name)
-    _dev(primary_bf16, _BF16, "primary_bf16")
     if n is None:
-        n = master.numel()
-    if any(t.numel() < n for t in (master, exp_avg, exp_avg_sq, grad, primary_bf16)):
-        raise ValueError("a buffer holds fewer than n elements")
+        n = _numel(master, _F32, "master")
+    p = _addresses(("master", "exp_avg", "exp_avg_sq", "grad", "primary_bf16"),
+                   "a buffer holds fewer than n elements", master, _F32, n, exp_avg, _F32, n,
+                   exp_avg_sq, _F32, n, grad, _F32, n, primary_bf16, _BF16, n)
     hp = AdamHParams(lr, beta1, beta2, eps, weight_decay, 1 if adamw else 0, int(step))
-    st = _lib.zpp_adam_partition_step(master.data_ptr(), exp_avg.data_ptr(),
-                                      exp_avg_sq.data_ptr(), grad.data_ptr(),
-                                      primary_bf16.data_ptr(), n, ctypes.byref(hp),
-                                      stream_handle(stream))
+    st = _lib.zpp_adam_partition_step(*p, n, ctypes.byref(hp), stream_handle(stream))
     _check(st, "zpp_adam_partition_step")
 
 
@@ -262,40 +324,28 @@ def adam_step_refresh_quantize(master, exp_avg, exp_avg_sq, grad, primary_bf16, 
                                done_after=None):
     """zpp_adam_step_refresh_quantize: the partition step, the secondary copy
     (``secondary_bf16`` may be None) and its int8 quantization in one pass."""
-    for t, name in ((master, "master"), (exp_avg, "exp_avg"), (exp_avg_sq, "exp_avg_sq"),
-                    (grad, "grad"), (scales, "scales")):
-        _dev(t, _F32, name)
-    _dev(primary_bf16, _BF16, "primary_bf16")
-    if secondary_bf16 is not None:
-        _dev(secondary_bf16, _BF16, "secondary_bf16")
-    _dev(codes, _I8, "codes")
     if n is None:
-        n = master.numel()
-    bufs = [master, exp_avg, exp_avg_sq, grad, primary_bf16, codes]
-    if secondary_bf16 is not None:
-        bufs.append(secondary_bf16)
-    if any(t.numel() < n for t in bufs) or scales.numel() < num_blocks(n, block):
-        raise ValueError("a buffer is too small for n = %d" % n)
+        n = _numel(master, _F32, "master")
+    p = _addresses(("master", "exp_avg", "exp_avg_sq", "grad", "primary_bf16", "secondary_bf16",
+                    "codes", "scales"), "a buffer is too small for n = %d" % n,
+                   master, _F32, n, exp_avg, _F32, n, exp_avg_sq, _F32, n, grad, _F32, n,
+                   primary_bf16, _BF16, n, secondary_bf16, _BF16 | _OPTIONAL, n, codes, _I8, n,
+                   scales, _F32, num_blocks(n, block))
     hp = AdamHParams(lr, beta1, beta2, eps, weight_decay, 1 if adamw else 0, int(step))
-    st = _lib.zpp_adam_step_refresh_quantize(
-        master.data_ptr(), exp_avg.data_ptr(), exp_avg_sq.data_ptr(), grad.data_ptr(),
-        primary_bf16.data_ptr(), secondary_bf16.data_ptr() if secondary_bf16 is not None else None,
-        codes.data_ptr(), scales.data_ptr(), n, block, ctypes.byref(hp), stream_handle(stream),
-        _event_handle(wait_before), _event_handle(done_after))
+    st = _lib.zpp_adam_step_refresh_quantize(*p, n, block, ctypes.byref(hp),
+                                             stream_handle(stream), _event_handle(wait_before),
+                                             _event_handle(done_after))
     _check(st, "zpp_adam_step_refresh_quantize")
 
 
 def refresh_secondary(secondary_bf16, src_bf16, count=None, *, stream=None, wait_before=None,
                       done_after=None):
     """zpp_refresh_secondary: copy ``count`` bf16 (default: all of src)."""
-    _dev(secondary_bf16, _BF16, "secondary_bf16")
-    _dev(src_bf16, _BF16, "src_bf16")
     if count is None:
-        count = src_bf16.numel()
-    if secondary_bf16.numel() < count or src_bf16.numel() < count:
-        raise ValueError("a buffer holds fewer than count elements")
-    st = _lib.zpp_refresh_secondary(secondary_bf16.data_ptr(), src_bf16.data_ptr(), count,
-                                    stream_handle(stream), _event_handle(wait_before),
+        count = _numel(src_bf16, _BF16, "src_bf16")
+    p = _addresses(("secondary_bf16", "src_bf16"), "a buffer holds fewer than count elements",
+                   secondary_bf16, _BF16, count, src_bf16, _BF16, count)
+    st = _lib.zpp_refresh_secondary(*p, count, stream_handle(stream), _event_handle(wait_before),
                                     _event_handle(done_after))
     _check(st, "zpp_refresh_secondary")
 
@@ -309,15 +359,12 @@ def num_blocks(n, block):
 def quantize_blockwise_i8(src_bf16, codes, scales, *, block=256, n=None, stream=None,
                           wait_before=None, done_after=None):
     """zpp_quantize_blockwise_i8 over the first ``n`` elements of src."""
-    _dev(src_bf16, _BF16, "src_bf16")
-    _dev(codes, _I8, "codes")
-    _dev(scales, _F32, "scales")
     if n is None:
-        n = src_bf16.numel()
-    if src_bf16.numel() < n or codes.numel() < n or scales.numel() < num_blocks(n, block):
-        raise ValueError("a buffer is too small for n = %d" % n)
-    st = _lib.zpp_quantize_blockwise_i8(src_bf16.data_ptr(), n, block, codes.data_ptr(),
-                                        scales.data_ptr(), stream_handle(stream),
+        n = _numel(src_bf16, _BF16, "src_bf16")
+    src, c, sc = _addresses(("src_bf16", "codes", "scales"),
+                            "a buffer is too small for n = %d" % n, src_bf16, _BF16, n,
+                            codes, _I8, n, scales, _F32, num_blocks(n, block))
+    st = _lib.zpp_quantize_blockwise_i8(src, n, block, c, sc, stream_handle(stream),
                                         _event_handle(wait_before), _event_handle(done_after))
     _check(st, "zpp_quantize_blockwise_i8")
 
@@ -326,17 +373,13 @@ def refresh_quantize_i8(secondary_bf16, src_bf16, codes, scales, *, block=256, n
                         stream=None, wait_before=None, done_after=None):
     """zpp_refresh_quantize_i8 over the first ``n`` elements of src: the
     secondary refresh and its quantization in one pass."""
-    _dev(secondary_bf16, _BF16, "secondary_bf16")
-    _dev(src_bf16, _BF16, "src_bf16")
-    _dev(codes, _I8, "codes")
-    _dev(scales, _F32, "scales")
     if n is None:
-        n = src_bf16.numel()
-    if (src_bf16.numel() < n or secondary_bf16.numel() < n or codes.numel() < n
-            or scales.numel() < num_blocks(n, block)):
-        raise ValueError("a buffer is too small for n = %d" % n)
-    st = _lib.zpp_refresh_quantize_i8(secondary_bf16.data_ptr(), src_bf16.data_ptr(), n, block,
-                                      codes.data_ptr(), scales.data_ptr(), stream_handle(stream),
+        n = _numel(src_bf16, _BF16, "src_bf16")
+    second, src, c, sc = _addresses(("secondary_bf16", "src_bf16", "codes", "scales"),
+                                    "a buffer is too small for n = %d" % n,
+                                    secondary_bf16, _BF16, n, src_bf16, _BF16, n, codes, _I8, n,
+                                    scales, _F32, num_blocks(n, block))
+    st = _lib.zpp_refresh_quantize_i8(second, src, n, block, c, sc, stream_handle(stream),
                                       _event_handle(wait_before), _event_handle(done_after))
     _check(st, "zpp_refresh_quantize_i8")
 
@@ -349,37 +392,28 @@ def dequant_gather_layer(shard_codes, shard_scales, shard_elems, layer_elems, ou
         raise ValueError("one scales tensor per codes tensor")
     if not 1 <= k <= MAX_SHARDS:
         raise ValueError("1..%d shards" % MAX_SHARDS)
-    for j in range(k):
-        _dev(shard_codes[j], _I8, "shard_codes[%d]" % j)
-        _dev(shard_scales[j], _F32, "shard_scales[%d]" % j)
-        if (shard_codes[j].numel() < shard_elems
-                or shard_scales[j].numel() < num_blocks(shard_elems, block)):
-            raise ValueError("shard %d buffers too small" % j)
-    _dev(out_bf16, _BF16, "out_bf16")
-    if out_bf16.numel() < layer_elems:
-        raise ValueError("out holds fewer than layer_elems elements")
-    cptrs = (_P * k)(*[c.data_ptr() for c in shard_codes])
-    sptrs = (_P * k)(*[s.data_ptr() for s in shard_scales])
-    waits = [_event_handle(e) for e in wait_events]
-    warr = (_P * max(1, len(waits)))(*waits) if waits else None
-    st = _lib.zpp_dequant_gather_layer(cptrs, sptrs, k, shard_elems, block, layer_elems,
-                                       out_bf16.data_ptr(), stream_handle(stream), warr,
-                                       len(waits), _event_handle(done_after))
+    small = "shard %d buffers too small"
+    cptrs = _address_array(shard_codes, _I8, shard_elems, "shard_codes", small)
+    sptrs = _address_array(shard_scales, _F32, num_blocks(shard_elems, block), "shard_scales",
+                           small)
+    out, = _addresses(("out_bf16",), "out holds fewer than layer_elems elements",
+                      out_bf16, _BF16, layer_elems)
+    warr, waits = _events(wait_events)
+    st = _lib.zpp_dequant_gather_layer(cptrs, sptrs, k, shard_elems, block, layer_elems, out,
+                                       stream_handle(stream), warr, waits,
+                                       _event_handle(done_after))
     _check(st, "zpp_dequant_gather_layer")
 
 
 def quantize_blockwise_i4(src, codes, scales, *, block=256, n=None, stream=None,
                           wait_before=None, done_after=None):
     """zpp_quantize_blockwise_i4 of the first ``n`` fp32 values of src."""
-    _dev(src, _F32, "src")
-    _dev(codes, _U8, "codes")
-    _dev(scales, _F32, "scales")
     if n is None:
-        n = src.numel()
-    if src.numel() < n or codes.numel() < (n + 1) // 2 or scales.numel() < num_blocks(n, block):
-        raise ValueError("a buffer is too small for n = %d" % n)
-    st = _lib.zpp_quantize_blockwise_i4(src.data_ptr(), n, block, codes.data_ptr(),
-                                        scales.data_ptr(), stream_handle(stream),
+        n = _numel(src, _F32, "src")
+    x, c, sc = _addresses(("src", "codes", "scales"), "a buffer is too small for n = %d" % n,
+                          src, _F32, n, codes, _U8, (n + 1) // 2,
+                          scales, _F32, num_blocks(n, block))
+    st = _lib.zpp_quantize_blockwise_i4(x, n, block, c, sc, stream_handle(stream),
                                         _event_handle(wait_before), _event_handle(done_after))
     _check(st, "zpp_quantize_blockwise_i4")
 
@@ -387,25 +421,28 @@ def quantize_blockwise_i4(src, codes, scales, *, block=256, n=None, stream=None,
 def dequant_reduce_i4(src_codes, src_scales, n, out, *, block=256, scale_out=1.0, stream=None,
                       wait_events=(), done_after=None):
     """zpp_dequant_reduce_i4 over len(src_codes) sources into out[:n]."""
-    k = len(src_codes)
-    if k != len(src_scales) or not 1 <= k <= MAX_SHARDS:
-        raise ValueError("1..%d sources, one scales tensor each" % MAX_SHARDS)
-    for q in range(k):
-        _dev(src_codes[q], _U8, "src_codes[%d]" % q)
-        _dev(src_scales[q], _F32, "src_scales[%d]" % q)
-        if src_codes[q].numel() < (n + 1) // 2 or src_scales[q].numel() < num_blocks(n, block):
-            raise ValueError("source %d buffers too small" % q)
-    _dev(out, _F32, "out")
-    if out.numel() < n:
-        raise ValueError("out holds fewer than n elements")
-    cptrs = (_P * k)(*[c.data_ptr() for c in src_codes])
-    sptrs = (_P * k)(*[x.data_ptr() for x in src_scales])
-    waits = [_event_handle(e) for e in wait_events]
-    warr = (_P * len(waits))(*waits) if waits else None
-    st = _lib.zpp_dequant_reduce_i4(cptrs, sptrs, k, n, block, scale_out, out.data_ptr(),
-                                    stream_handle(stream), warr, len(waits),
+    cptrs, sptrs, k = _sources(src_codes, src_scales, n, block)
+    o, = _addresses(("out",), "out holds fewer than n elements", out, _F32, n)
+    warr, waits = _events(wait_events)
+    st = _lib.zpp_dequant_reduce_i4(cptrs, sptrs, k, n, block, scale_out, o,
+                                    stream_handle(stream), warr, waits,
                                     _event_handle(done_after))
     _check(st, "zpp_dequant_reduce_i4")
+
+
+def _state(master, exp_avg, exp_avg_sq, primary_bf16, n):
+    return _addresses(("master", "exp_avg", "exp_avg_sq", "primary_bf16"),
+                      "a buffer holds fewer than n elements", master, _F32, n, exp_avg, _F32, n,
+                      exp_avg_sq, _F32, n, primary_bf16, _BF16, n)
+
+
+def _state_and_codes(master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16, codes, scales, n,
+                     block):
+    return _addresses(("master", "exp_avg", "exp_avg_sq", "primary_bf16", "secondary_bf16",
+                       "codes", "scales"), "a buffer is too small for n = %d" % n,
+                      master, _F32, n, exp_avg, _F32, n, exp_avg_sq, _F32, n,
+                      primary_bf16, _BF16, n, secondary_bf16, _BF16 | _OPTIONAL, n, codes, _I8, n,
+                      scales, _F32, num_blocks(n, block))
 
 
 def qgz_receive_adam_step(master, exp_avg, exp_avg_sq, src_codes, src_scales, primary_bf16, *,
@@ -413,30 +450,14 @@ def qgz_receive_adam_step(master, exp_avg, exp_avg_sq, src_codes, src_scales, pr
                           scale_out=1.0, n=None, stream=None, wait_events=(), done_after=None):
     """zpp_qgz_receive_adam_step: the partition step with its gradient taken
     from len(src_codes) int4 copies (the mean when scale_out = 1/len)."""
-    for t, name in ((master, "master"), (exp_avg, "exp_avg"), (exp_avg_sq, "exp_avg_sq")):
-        _dev(t, _F32, name)
-    _dev(primary_bf16, _BF16, "primary_bf16")
-    k = len(src_codes)
-    if k != len(src_scales) or not 1 <= k <= MAX_SHARDS:
-        raise ValueError("1..%d sources, one scales tensor each" % MAX_SHARDS)
     if n is None:
-        n = master.numel()
-    for q in range(k):
-        _dev(src_codes[q], _U8, "src_codes[%d]" % q)
-        _dev(src_scales[q], _F32, "src_scales[%d]" % q)
-        if src_codes[q].numel() < (n + 1) // 2 or src_scales[q].numel() < num_blocks(n, block):
-            raise ValueError("source %d buffers too small" % q)
-    if any(t.numel() < n for t in (master, exp_avg, exp_avg_sq, primary_bf16)):
-        raise ValueError("a buffer holds fewer than n elements")
-    cptrs = (_P * k)(*[c.data_ptr() for c in src_codes])
-    sptrs = (_P * k)(*[x.data_ptr() for x in src_scales])
-    waits = [_event_handle(e) for e in wait_events]
-    warr = (_P * len(waits))(*waits) if waits else None
+        n = _numel(master, _F32, "master")
+    p, m, v, o = _state(master, exp_avg, exp_avg_sq, primary_bf16, n)
+    cptrs, sptrs, k = _sources(src_codes, src_scales, n, block)
+    warr, waits = _events(wait_events)
     hp = AdamHParams(lr, beta1, beta2, eps, weight_decay, 1 if adamw else 0, int(step))
-    st = _lib.zpp_qgz_receive_adam_step(master.data_ptr(), exp_avg.data_ptr(),
-                                        exp_avg_sq.data_ptr(), cptrs, sptrs, k, block, scale_out,
-                                        primary_bf16.data_ptr(), n, ctypes.byref(hp),
-                                        stream_handle(stream), warr, len(waits),
+    st = _lib.zpp_qgz_receive_adam_step(p, m, v, cptrs, sptrs, k, block, scale_out, o, n,
+                                        ctypes.byref(hp), stream_handle(stream), warr, waits,
                                         _event_handle(done_after))
     _check(st, "zpp_qgz_receive_adam_step")
 
@@ -449,40 +470,16 @@ def qgz_receive_step_refresh_quantize(master, exp_avg, exp_avg_sq, src_codes, sr
     """zpp_qgz_receive_step_refresh_quantize: the receive step, the secondary
     copy (``secondary_bf16`` may be None) and its int8 quantization in one
     pass."""
-    for t, name in ((master, "master"), (exp_avg, "exp_avg"), (exp_avg_sq, "exp_avg_sq"),
-                    (scales, "scales")):
-        _dev(t, _F32, name)
-    _dev(primary_bf16, _BF16, "primary_bf16")
-    if secondary_bf16 is not None:
-        _dev(secondary_bf16, _BF16, "secondary_bf16")
-    _dev(codes, _I8, "codes")
-    k = len(src_codes)
-    if k != len(src_scales) or not 1 <= k <= MAX_SHARDS:
-        raise ValueError("1..%d sources, one scales tensor each" % MAX_SHARDS)
     if n is None:
-        n = master.numel()
-    for q in range(k):
-        _dev(src_codes[q], _U8, "src_codes[%d]" % q)
-        _dev(src_scales[q], _F32, "src_scales[%d]" % q)
-        if (src_codes[q].numel() < (n + 1) // 2
-                or src_scales[q].numel() < num_blocks(n, grad_block)):
-            raise ValueError("source %d buffers too small" % q)
-    bufs = [master, exp_avg, exp_avg_sq, primary_bf16, codes]
-    if secondary_bf16 is not None:
-        bufs.append(secondary_bf16)
-    if any(t.numel() < n for t in bufs) or scales.numel() < num_blocks(n, block):
-        raise ValueError("a buffer is too small for n = %d" % n)
-    cptrs = (_P * k)(*[c.data_ptr() for c in src_codes])
-    sptrs = (_P * k)(*[x.data_ptr() for x in src_scales])
-    waits = [_event_handle(e) for e in wait_events]
-    warr = (_P * len(waits))(*waits) if waits else None
+        n = _numel(master, _F32, "master")
+    p, m, v, *outs = _state_and_codes(master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16,
+                                      codes, scales, n, block)
+    cptrs, sptrs, k = _sources(src_codes, src_scales, n, grad_block)
+    warr, waits = _events(wait_events)
     hp = AdamHParams(lr, beta1, beta2, eps, weight_decay, 1 if adamw else 0, int(step))
     st = _lib.zpp_qgz_receive_step_refresh_quantize(
-        master.data_ptr(), exp_avg.data_ptr(), exp_avg_sq.data_ptr(), cptrs, sptrs, k, grad_block,
-        scale_out, primary_bf16.data_ptr(),
-        secondary_bf16.data_ptr() if secondary_bf16 is not None else None, codes.data_ptr(),
-        scales.data_ptr(), n, block, ctypes.byref(hp), stream_handle(stream), warr, len(waits),
-        _event_handle(done_after))
+        p, m, v, cptrs, sptrs, k, grad_block, scale_out, *outs, n, block, ctypes.byref(hp),
+        stream_handle(stream), warr, waits, _event_handle(done_after))
     _check(st, "zpp_qgz_receive_step_refresh_quantize")
 
 
@@ -497,27 +494,24 @@ def interleaved_sizes(n, block, num_src):
 
 
 def _interleaved_inputs(codes, scales, n, block, num_src):
-    _dev(codes, _U8, "codes")
-    _dev(scales, _F32, "scales")
     if not 1 <= num_src <= MAX_SHARDS:
         raise ValueError("1..%d sources" % MAX_SHARDS)
     nc, ns = interleaved_sizes(n, block, num_src)
-    if codes.numel() < nc or scales.numel() < ns:
-        raise ValueError("the interleaved buffer is too small for n = %d, %d sources" % (n, num_src))
+    return _addresses(("codes", "scales"),
+                      "the interleaved buffer is too small for n = %d, %d sources" % (n, num_src),
+                      codes, _U8, nc, scales, _F32, ns)
 
 
 def quantize_blockwise_i4_interleaved(src, codes, scales, *, source, num_src, block=256, n=None,
                                       stream=None, wait_before=None, done_after=None):
     """zpp_quantize_blockwise_i4_interleaved: source `source` of num_src."""
-    _dev(src, _F32, "src")
     if n is None:
-        n = src.numel()
-    if src.numel() < n:
-        raise ValueError("src holds fewer than n elements")
-    _interleaved_inputs(codes, scales, n, block, num_src)
+        n = _numel(src, _F32, "src")
+    x, = _addresses(("src",), "src holds fewer than n elements", src, _F32, n)
+    c, sc = _interleaved_inputs(codes, scales, n, block, num_src)
     st = _lib.zpp_quantize_blockwise_i4_interleaved(
-        src.data_ptr(), n, block, source, num_src, codes.data_ptr(), scales.data_ptr(),
-        stream_handle(stream), _event_handle(wait_before), _event_handle(done_after))
+        x, n, block, source, num_src, c, sc, stream_handle(stream), _event_handle(wait_before),
+        _event_handle(done_after))
     _check(st, "zpp_quantize_blockwise_i4_interleaved")
 
 
@@ -525,15 +519,12 @@ def dequant_reduce_i4_interleaved(codes, scales, num_src, n, out, *, block=256, 
                                   stream=None, wait_events=(), done_after=None):
     """zpp_dequant_reduce_i4_interleaved: the num_src int4 copies of one
     interleaved receive buffer reduced into out[:n]."""
-    _interleaved_inputs(codes, scales, n, block, num_src)
-    _dev(out, _F32, "out")
-    if out.numel() < n:
-        raise ValueError("out holds fewer than n elements")
-    waits = [_event_handle(e) for e in wait_events]
-    warr = (_P * len(waits))(*waits) if waits else None
-    st = _lib.zpp_dequant_reduce_i4_interleaved(
-        codes.data_ptr(), scales.data_ptr(), num_src, n, block, scale_out, out.data_ptr(),
-        stream_handle(stream), warr, len(waits), _event_handle(done_after))
+    c, sc = _interleaved_inputs(codes, scales, n, block, num_src)
+    o, = _addresses(("out",), "out holds fewer than n elements", out, _F32, n)
+    warr, waits = _events(wait_events)
+    st = _lib.zpp_dequant_reduce_i4_interleaved(c, sc, num_src, n, block, scale_out, o,
+                                                stream_handle(stream), warr, waits,
+                                                _event_handle(done_after))
     _check(st, "zpp_dequant_reduce_i4_interleaved")
 
 
@@ -543,21 +534,15 @@ def qgz_receive_adam_step_interleaved(master, exp_avg, exp_avg_sq, codes, scales
                                       stream=None, wait_events=(), done_after=None):
     """zpp_qgz_receive_adam_step_interleaved: the receive step from one
     interleaved buffer of num_src int4 copies."""
-    for t, name in ((master, "master"), (exp_avg, "exp_avg"), (exp_avg_sq, "exp_avg_sq")):
-        _dev(t, _F32, name)
-    _dev(primary_bf16, _BF16, "primary_bf16")
     if n is None:
-        n = master.numel()
-    if any(t.numel() < n for t in (master, exp_avg, exp_avg_sq, primary_bf16)):
-        raise ValueError("a buffer holds fewer than n elements")
-    _interleaved_inputs(codes, scales, n, block, num_src)
-    waits = [_event_handle(e) for e in wait_events]
-    warr = (_P * len(waits))(*waits) if waits else None
+        n = _numel(master, _F32, "master")
+    p, m, v, o = _state(master, exp_avg, exp_avg_sq, primary_bf16, n)
+    c, sc = _interleaved_inputs(codes, scales, n, block, num_src)
+    warr, waits = _events(wait_events)
     hp = AdamHParams(lr, beta1, beta2, eps, weight_decay, 1 if adamw else 0, int(step))
     st = _lib.zpp_qgz_receive_adam_step_interleaved(
-        master.data_ptr(), exp_avg.data_ptr(), exp_avg_sq.data_ptr(), codes.data_ptr(),
-        scales.data_ptr(), num_src, block, scale_out, primary_bf16.data_ptr(), n,
-        ctypes.byref(hp), stream_handle(stream), warr, len(waits), _event_handle(done_after))
+        p, m, v, c, sc, num_src, block, scale_out, o, n, ctypes.byref(hp), stream_handle(stream),
+        warr, waits, _event_handle(done_after))
     _check(st, "zpp_qgz_receive_adam_step_interleaved")
 
 
@@ -568,30 +553,16 @@ def qgz_receive_step_refresh_quantize_interleaved(
         done_after=None):
     """zpp_qgz_receive_step_refresh_quantize_interleaved: the single pass from
     one interleaved buffer of num_src int4 copies."""
-    for t, name in ((master, "master"), (exp_avg, "exp_avg"), (exp_avg_sq, "exp_avg_sq"),
-                    (scales, "scales")):
-        _dev(t, _F32, name)
-    _dev(primary_bf16, _BF16, "primary_bf16")
-    if secondary_bf16 is not None:
-        _dev(secondary_bf16, _BF16, "secondary_bf16")
-    _dev(codes, _I8, "codes")
     if n is None:
-        n = master.numel()
-    bufs = [master, exp_avg, exp_avg_sq, primary_bf16, codes]
-    if secondary_bf16 is not None:
-        bufs.append(secondary_bf16)
-    if any(t.numel() < n for t in bufs) or scales.numel() < num_blocks(n, block):
-        raise ValueError("a buffer is too small for n = %d" % n)
-    _interleaved_inputs(src_codes, src_scales, n, grad_block, num_src)
-    waits = [_event_handle(e) for e in wait_events]
-    warr = (_P * len(waits))(*waits) if waits else None
+        n = _numel(master, _F32, "master")
+    p, m, v, *outs = _state_and_codes(master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16,
+                                      codes, scales, n, block)
+    c, sc = _interleaved_inputs(src_codes, src_scales, n, grad_block, num_src)
+    warr, waits = _events(wait_events)
     hp = AdamHParams(lr, beta1, beta2, eps, weight_decay, 1 if adamw else 0, int(step))
     st = _lib.zpp_qgz_receive_step_refresh_quantize_interleaved(
-        master.data_ptr(), exp_avg.data_ptr(), exp_avg_sq.data_ptr(), src_codes.data_ptr(),
-        src_scales.data_ptr(), num_src, grad_block, scale_out, primary_bf16.data_ptr(),
-        secondary_bf16.data_ptr() if secondary_bf16 is not None else None, codes.data_ptr(),
-        scales.data_ptr(), n, block, ctypes.byref(hp), stream_handle(stream), warr, len(waits),
-        _event_handle(done_after))
+        p, m, v, c, sc, num_src, grad_block, scale_out, *outs, n, block, ctypes.byref(hp),
+        stream_handle(stream), warr, waits, _event_handle(done_after))
     _check(st, "zpp_qgz_receive_step_refresh_quantize_interleaved")
 
 

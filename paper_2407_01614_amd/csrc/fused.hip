@@ -15,11 +15,12 @@
 // the 4 elements [chunk + 256 w + 4 l, +4) for w < C / 256.  The bf16 of the
 // updated weights stays in registers (two per 4 elements) until the block's
 // absmax is known; a 256-block is exactly one wave, so its absmax is a
-// six-step cross-lane reduction.  Blocks of 64 to 512 take this kernel.  Any
-// other block (1024 and up, or not a power of two) takes two passes: the same
-// kernel with the 256-element chunks and no quantization (p, m, v, primary,
-// secondary: 32 B per element), then the int8 quantizer over the primary it
-// wrote (3 B + 4/B B), in stream order.  The 2 extra bytes per element cost
+// six-step cross-lane reduction.  Blocks of 64, 128, 256 and 512 take this
+// kernel.  Any other block takes a workgroup per block (fused_wide_kernel)
+// where that is faster, or two passes: the same kernel with the 256-element
+// chunks and no quantization (p, m, v, primary, secondary: 32 B per element),
+// then the int8 quantizer over the primary it wrote (3 B + 4/B B), in stream
+// order.  The 2 extra bytes per element cost
 // less than holding a larger block's values in a wave: at the Llama-2-13B
 // partition the two passes took 1094-1104 us at blocks of 192 to 4096, the
 // one-pass layouts 1127-1186 us (one wave per chunk of whole blocks, several
@@ -144,6 +145,126 @@ __global__ __launch_bounds__(kWave) void fused_kernel(FusedArgs a, GS gs, TileSp
         fused_chunk<ADAMW, B, QUANT, false, MANY>(a, gs, base, chunks.tail);
 }
 
+// The fused step with one quant block per workgroup, for blocks that are not
+// 64 to 512: ceil(B / 256) waves, one float4 group per lane (the lanes past a
+// block that is no multiple of 256 stay idle), the waves' maxima exchanged in
+// LDS.  The block's values stay in registers, so the primary is not read back
+// and there is one launch instead of two.
+template <bool ADAMW, bool WHOLE, bool MANY, class GS>
+__device__ __forceinline__ void fused_wide_block(const FusedArgs &a, const GS &gs, size_t base,
+                                                 uint32_t rest, size_t k) {
+    __shared__ uint32_t wave_mx[16];
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t waves = blockDim.x / kWave;
+    const uint32_t i = threadIdx.x * 4;
+    const size_t wb = base + wave * 256;
+    const bool some = WHOLE ? i < rest : wave * 256 < rest;
+    u32x2 pk = {0u, 0u};
+    if (some) {
+        f32x4 P = load4<WHOLE>(a.p + base, i, rest), M = load4<WHOLE>(a.m + base, i, rest),
+              V = load4<WHOLE>(a.v + base, i, rest), G[1];
+        grad_tile<WHOLE, MANY>(G, gs, wb, lane, rest - wave * 256);
+        adam_update4<ADAMW>(P, M, V, G[0], a.c);
+        pk = u32x2{pack_bf16x2(P.x, P.y), pack_bf16x2(P.z, P.w)};
+        if constexpr (!WHOLE) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (i + e >= rest)
+                    pk[e / 2] &= e % 2 ? 0x0000FFFFu : 0xFFFF0000u;
+        }
+        store4<WHOLE>(a.p + base, i, rest, P);
+        store4<WHOLE>(a.m + base, i, rest, M);
+        store4<WHOLE>(a.v + base, i, rest, V);
+        store4_bf16<WHOLE>(a.primary + base, i, rest, pk);
+        if (a.secondary)
+            store4_bf16<WHOLE>(a.secondary + base, i, rest, pk);
+    }
+    const u16x2 m2 = __builtin_elementwise_max(absbits2(pk.x), absbits2(pk.y));
+    uint32_t mx = max((uint32_t)m2.x, (uint32_t)m2.y);
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1)
+        mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
+    if (lane == 0)
+        wave_mx[wave] = mx;
+    // the waves meet once their maxima are in LDS; their stores to memory
+    // need not have finished, so this is no __syncthreads()
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    mx = lane < waves ? wave_mx[lane % 16] : 0u;
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1)
+        mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
+    mx = __builtin_amdgcn_readfirstlane(mx);
+    const BlockQuant q = block_params(mx);
+    if (some)
+        store4_i8<WHOLE>(a.codes + base, i, rest, quant_word(pk.x, pk.y, q));
+    if (threadIdx.x == 0)
+        a.scales[k] = q.scale;
+}
+
+template <bool ADAMW, bool MANY, class GS>
+__global__ __launch_bounds__(1024) void fused_wide_kernel(FusedArgs a, GS gs, uint32_t B, TileSpan blocks) {
+    const uint32_t t = tile_of(blockIdx.x, gridDim.x, blocks, fused_xcd_run<GS>() / 4);
+    const size_t k = blocks.first + t;
+    if (__builtin_expect(t < blocks.whole, 1))
+        fused_wide_block<ADAMW, true, MANY>(a, gs, k * B, B, k);
+    else
+        fused_wide_block<ADAMW, false, MANY>(a, gs, k * B, blocks.tail, k);
+}
+
+// Where the one-block-per-workgroup form runs in place of the two kernels.
+// What it costs is that a workgroup's waves start together and cover up to 16
+// neighbouring tiles on one XCD, which streams a few percent slower over long
+// arrays than one-wave workgroups dealt out over the XCDs; what it saves is
+// the second launch and 2 bytes read per element.  All blocks gain up to about
+// 12 M elements (192 / 320 / 2048 / 4096 at 6 M: 39.0 / 38.0 / 39.0 / 40.4 ->
+// 37.8 / 36.5 / 36.4 / 37.5 us, at 1 M 9.8 / 10.1 / 12.0 / 14.1 -> 7.6 / 7.7 /
+// 6.7 / 6.8), and these lose at 45 M (320: 253 -> 258, 2048: 252 -> 258).
+// Blocks of 832 to 1280 (4 or 5 waves) gain for longer: 1024 at 45 M 250 ->
+// 236, 100 M 548 -> 520, but 150 M 839 -> 849 and 210 M 1145 -> 1160; with the
+// gradient from int4 copies, whose two kernels cost more, at every length
+// (1024 and 8 copies, 200 M: 1161 -> 1077).
+constexpr size_t kWideMost = (size_t)8 << 20;
+template <class GS>
+bool wide_block(uint32_t block, size_t n) {
+    if (block > 768 && block <= 1280)
+        return !std::is_same_v<GS, F32Grad> || n <= 16 * kWideMost;
+    return n <= kWideMost;
+}
+
+// Workgroups per CU: the step's three or four times four waves (1024 at 45 M:
+// 236 us with 3, 249 with 4, 256 left to the hardware; the receive at 50 M 278
+// / 271 / 279), but short launches and many sources are left to the hardware
+// (1024 at 1 M elements: 6.9 us against 7.6 with 3).
+template <class GS>
+int wide_residency(const GS &gs, size_t n) {
+    if (n <= kWideMost / 2)
+        return 0;
+    if constexpr (std::is_same_v<GS, F32Grad>)
+        return 3;
+    else
+        return gs.num_src >= kManySources ? 0 : 4;
+}
+
+template <bool MANY, class GS>
+void launch_wide(const FusedArgs &a, const GS &gs, uint32_t block, bool on_lines,
+                 hipStream_t stream) {
+    const uint32_t threads = (block / 4 + kWave - 1) / kWave * kWave;
+    // beyond half of kWideMost a block of fewer waves would be capped too low
+    const int per_cu = threads / kWave >= 4 ? wide_residency(gs, a.n) : 0;
+    const size_t lds = residency_lds(per_cu) - (per_cu ? 1024 : 0);  // the maxima's own
+    for_tiles(a.n, block, 1, threads, on_lines, [&](const TileSpan &blocks, unsigned grid) {
+        if (a.c.adamw)
+            hipLaunchKernelGGL((fused_wide_kernel<true, MANY, GS>), dim3(grid), dim3(threads),
+                               lds, stream, a, gs, block, blocks);
+        else
+            hipLaunchKernelGGL((fused_wide_kernel<false, MANY, GS>), dim3(grid), dim3(threads),
+                               lds, stream, a, gs, block, blocks);
+    });
+}
+
 // Workgroups per CU for each gradient source.
 template <class GS> constexpr int fused_residency();
 template <> constexpr int fused_residency<F32Grad>() { return ZPP_FUSED_RESIDENCY; }
@@ -167,7 +288,12 @@ void launch_fused_chunks(const FusedArgs &a, const GS &gs, int residency, bool o
 
 template <int B, bool QUANT = true, class GS>
 void launch_fused_b(const FusedArgs &a, const GS &gs, bool on_lines, hipStream_t stream) {
-    int residency = fused_residency<GS>();
+    // the step with its copies alone, ahead of the quantizer, keeps fewer: 10
+    // (Llama-2-7B partition, both kernels: 1138 us with 9, 1138 with 10, 1146
+    // with 11, 1154 with 12, 1153 with 8; with 8 copies from the interleaved
+    // buffer at 50 M 305 with 10, 310 with 12, 315 with 8), from separate
+    // arrays as many as with the quantization (291 us with 13, 299 with 10)
+    int residency = QUANT || std::is_same_v<GS, I4Grad> ? fused_residency<GS>() : 10;
     if constexpr (!std::is_same_v<GS, F32Grad>) {
         if (gs.num_src >= kManySources)
             residency = 0;  // left to the hardware (zpp_i4grad.h)
@@ -186,6 +312,17 @@ hipError_t launch_fused_gs(const FusedArgs &a, const GS &gs, uint32_t block, boo
     case 256: launch_fused_b<256>(a, gs, on_lines, stream); break;
     case 512: launch_fused_b<512>(a, gs, on_lines, stream); break;
     default: {
+        if (wide_block<GS>(block, a.n)) {
+            if constexpr (!std::is_same_v<GS, F32Grad>) {
+                // a wave's 256 elements lie in one int4 block
+                if (block % 256 == 0 && many_sources(gs.num_src, gs.block)) {
+                    launch_wide<true>(a, gs, block, on_lines, stream);
+                    return hipGetLastError();
+                }
+            }
+            launch_wide<false>(a, gs, block, on_lines, stream);
+            return hipGetLastError();
+        }
         // the step and its copies in one pass, then the quantization of
         // the primary it wrote (stream order)
         launch_fused_b<256, false>(a, gs, on_lines, stream);

@@ -238,3 +238,42 @@ def test_alignments(zpp, n, block, interleaved):
         got = every_call(zpp, n, block, offset, interleaved)
         for name, r in ref.items():
             assert np.array_equal(got[name], r), (name, offset)
+
+
+@pytest.mark.parametrize("sources", [0, 16], ids=["gradient", "receive"])
+@pytest.mark.parametrize("block", [192, 320, 832, 1024, 1280, 1344, 2048, 4096])
+def test_fused_block_routes(zpp, block, sources):
+    """A block per workgroup against the step and the quantizer as separate
+    calls, at the lengths where the route changes and at ragged ones."""
+    limit = 8 << 20
+    for n in (1, block - 1, block, 5 * block + 3, limit, limit + 64 * block // 64 + 5):
+        names = ("master", "exp_avg", "exp_avg_sq", "primary", "secondary", "codes", "scales")
+        gen = torch.Generator(device="cuda").manual_seed(n)
+        p = torch.empty(n, device="cuda").normal_(0, 0.02, generator=gen)
+        g = torch.empty(n, device="cuda").normal_(0, 1e-3, generator=gen)
+        m, v = g * 0.5, g * g
+        if sources:
+            codes = torch.randint(0, 256, ((n + 1) // 2,), dtype=torch.uint8, device="cuda",
+                                  generator=gen)
+            src = [codes] * sources, [torch.full((-(-n // 256),), 1e-4, device="cuda")] * sources
+            kw = dict(scale_out=1.0 / sources)
+        got = [Buf(n, torch.float32) for _ in range(3)] + [
+            Buf(n, torch.int16), Buf(n, torch.int16), Buf(n, torch.int8),
+            Buf(-(-n // block), torch.float32)]
+        ref = [Buf(n, torch.float32) for _ in range(3)] + [
+            Buf(n, torch.int16), Buf(n, torch.int16), Buf(n, torch.int8),
+            Buf(-(-n // block), torch.float32)]
+        for bufs in (got, ref):
+            for b, x in zip(bufs, (p, m, v)):
+                b.t.copy_(x)
+        a, b = [x.t for x in got], [x.t for x in ref]
+        if sources:
+            zpp.qgz_receive_step_refresh_quantize(*a[:3], *src, *a[3:], block=block, step=3, **kw,
+                                                  **HP)
+            zpp.qgz_receive_adam_step(*b[:3], *src, b[3], step=3, **kw, **HP)
+        else:
+            zpp.adam_step_refresh_quantize(*a[:3], g, *a[3:], block=block, step=3, **HP)
+            zpp.adam_partition_step(*b[:3], g, b[3], step=3, **HP)
+        zpp.refresh_quantize_i8(b[4], b[3], b[5], b[6], block=block)
+        for x, y, name in zip(got, ref, names):
+            assert torch.equal(x.raw, y.raw), "%s, n = %d" % (name, n)

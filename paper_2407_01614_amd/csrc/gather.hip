@@ -55,13 +55,14 @@ struct GatherArgs {
     size_t shard_elems;
     size_t layer_elems;
     BlockDiv block;
-    uint32_t on_lines;  // every shard's part of the output starts on a line
 };
 
-// The workgroup's place along its shard: in runs per XCD where the shards'
-// parts of the output do not start on lines (kOffLineXcdRun, zpp_device.h).
-__device__ __forceinline__ size_t gather_place(bool on_lines) {
-    return on_lines ? blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x, kOffLineXcdRun);
+// The workgroup's place along its shard.  LINES: every shard's part of the
+// output starts at a multiple of 32 bytes; otherwise in runs per XCD (kOffLineXcdRun,
+// zpp_device.h).
+template <bool LINES>
+__device__ __forceinline__ size_t gather_place() {
+    return xcd_grouped(blockIdx.x, gridDim.x, LINES ? 0 : kOffLineXcdRun);
 }
 
 __device__ __forceinline__ float code_f32(uint32_t w, int byte) {
@@ -125,7 +126,7 @@ __device__ __forceinline__ void gather_tail(const int8_t *__restrict__ codes,
 // A row is one wave-wide pass: 64 lanes x 8 consecutive codes = 512 output
 // elements, read as one contiguous 512-byte load and written as one
 // contiguous 1 KiB store.  A tile is U rows per wave.
-template <int U>
+template <int U, bool LINES>
 __global__ __launch_bounds__(kGatherThreads) void gather_vec_kernel(GatherArgs a) {
     constexpr size_t kRow = (size_t)kGatherThreads * 8;  // elements per row of the workgroup
     constexpr size_t kTile = kRow * U;
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_vec_kernel(GatherArgs a
     const float *__restrict__ scales = a.shards.scales[j];
     uint16_t *__restrict__ out = a.out + lo;
     const size_t ntiles = (valid + kTile - 1) / kTile;
-    for (size_t t = gather_place(a.on_lines); t < ntiles; t += gridDim.x) {
+    for (size_t t = gather_place<LINES>(); t < ntiles; t += gridDim.x) {
         const size_t base = t * kTile + (size_t)threadIdx.x * 8;
         if ((t + 1) * kTile <= valid) {
             u32x2 c[U];
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_vec_kernel(GatherArgs a
 // one-shot grid: no loop, so the scale loads come before any store and the
 // compiler keeps them scalar).  B is a power of two: the row holds
 // kBlocks = max(1, 512 / B) whole blocks, or lies inside one.
-template <int B>
+template <int B, bool LINES>
 __global__ __launch_bounds__(kWave) void gather_row_kernel(GatherArgs a) {
     constexpr int kBlocks = B >= 512 ? 1 : 512 / B;
     constexpr int kLanesPerBlock = B >= 512 ? kWave : B / 8;
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(kWave) void gather_row_kernel(GatherArgs a) {
     const float *__restrict__ scales = a.shards.scales[j];
     uint16_t *__restrict__ out = a.out + lo;
     const uint32_t lane = threadIdx.x;
-    const size_t r = gather_place(a.on_lines);
+    const size_t r = gather_place<LINES>();
     const size_t i = r * 512 + (size_t)lane * 8;
     if ((r + 1) * 512 <= valid) {
         const u32x2 c = ld_nt_at<u32x2, 1>(codes + i);
@@ -216,13 +217,19 @@ __global__ __launch_bounds__(kWave) void gather_row_kernel(GatherArgs a) {
         }
         st_nt_at<u32x4, 2>(out + i, u32x4{r0.x, r0.y, r1.x, r1.y});
     } else {
-        gather_tail(codes, scales, out, a.block, i, valid);
+        gather_tail(codes, scales, out, BlockDiv{0, (uint32_t)__builtin_ctz(B), B}, i, valid);
     }
 }
 
 template <int B>
-void launch_rows(const GatherArgs &a, unsigned rows, unsigned shards, hipStream_t stream) {
-    hipLaunchKernelGGL((gather_row_kernel<B>), dim3(rows, shards), dim3(kWave), 0, stream, a);
+void launch_rows(const GatherArgs &a, unsigned rows, unsigned shards, bool on_lines,
+                 hipStream_t stream) {
+    if (on_lines)
+        hipLaunchKernelGGL((gather_row_kernel<B, true>), dim3(rows, shards), dim3(kWave), 0,
+                           stream, a);
+    else
+        hipLaunchKernelGGL((gather_row_kernel<B, false>), dim3(rows, shards), dim3(kWave), 0,
+                           stream, a);
 }
 
 }  // namespace
@@ -236,7 +243,6 @@ hipError_t launch_gather(const GatherShards &shards, uint32_t num_shards, size_t
     a.shard_elems = shard_elems;
     a.layer_elems = layer_elems;
     a.block = make_block_div(block);
-    a.on_lines = on_lines;
     const size_t per_shard = shard_elems < layer_elems ? shard_elems : layer_elems;
     const size_t nrows = (per_shard + 511) / 512;
     if ((block & (block - 1)) == 0 && nrows <= ZPP_GATHER_ROW_MAX_GRID_X) {
@@ -244,21 +250,27 @@ hipError_t launch_gather(const GatherShards &shards, uint32_t num_shards, size_t
         const unsigned gy = (unsigned)((layer_elems + shard_elems - 1) / shard_elems);
         const unsigned gx = (unsigned)nrows;
         switch (block) {
-        case 64: launch_rows<64>(a, gx, gy, stream); break;
-        case 128: launch_rows<128>(a, gx, gy, stream); break;
-        case 256: launch_rows<256>(a, gx, gy, stream); break;
-        case 512: launch_rows<512>(a, gx, gy, stream); break;
-        case 1024: launch_rows<1024>(a, gx, gy, stream); break;
-        case 2048: launch_rows<2048>(a, gx, gy, stream); break;
-        default: launch_rows<4096>(a, gx, gy, stream); break;
+        case 64: launch_rows<64>(a, gx, gy, on_lines, stream); break;
+        case 128: launch_rows<128>(a, gx, gy, on_lines, stream); break;
+        case 256: launch_rows<256>(a, gx, gy, on_lines, stream); break;
+        case 512: launch_rows<512>(a, gx, gy, on_lines, stream); break;
+        case 1024: launch_rows<1024>(a, gx, gy, on_lines, stream); break;
+        case 2048: launch_rows<2048>(a, gx, gy, on_lines, stream); break;
+        default: launch_rows<4096>(a, gx, gy, on_lines, stream); break;
         }
     } else {
         constexpr size_t kTile = (size_t)kGatherThreads * 8 * ZPP_GATHER_UNROLL;
         const size_t tiles = (per_shard + kTile - 1) / kTile;
         const unsigned gx =
             (unsigned)(tiles < ZPP_GATHER_MAX_GRID_X ? tiles : ZPP_GATHER_MAX_GRID_X);
-        hipLaunchKernelGGL((gather_vec_kernel<ZPP_GATHER_UNROLL>), dim3(gx, num_shards),
-                           dim3(kGatherThreads), residency_lds(ZPP_GATHER_RESIDENCY), stream, a);
+        const dim3 grid(gx, num_shards), threads(kGatherThreads);
+        constexpr size_t lds = residency_lds(ZPP_GATHER_RESIDENCY);
+        if (on_lines)
+            hipLaunchKernelGGL((gather_vec_kernel<ZPP_GATHER_UNROLL, true>), grid, threads, lds,
+                               stream, a);
+        else
+            hipLaunchKernelGGL((gather_vec_kernel<ZPP_GATHER_UNROLL, false>), grid, threads, lds,
+                               stream, a);
     }
     return hipGetLastError();
 }

@@ -78,7 +78,7 @@ hipError_t launch_adam(float *p, float *m, float *v, const float *g, uint16_t *o
                        const AdamConsts &c, bool on_lines, hipStream_t stream) {
     const AdamArgs a{p, m, v, g, out, n, c};
     constexpr uint32_t kTile = kAdamThreads * 4 * ZPP_ADAM_UNROLL;
-    constexpr size_t lds = residency_lds(ZPP_ADAM_RESIDENCY);
+    const size_t lds = launch_lds(ZPP_ADAM_RESIDENCY, n / kTile);
     for_tiles(n, kTile, 1, kAdamThreads, on_lines, [&](const TileSpan &tiles, unsigned grid) {
         if (c.adamw)
             hipLaunchKernelGGL((adam_vec_kernel<true, ZPP_ADAM_UNROLL>), dim3(grid),

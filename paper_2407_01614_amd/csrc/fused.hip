@@ -275,7 +275,7 @@ template <int B, bool QUANT, bool MANY, class GS>
 void launch_fused_chunks(const FusedArgs &a, const GS &gs, int residency, bool on_lines,
                          hipStream_t stream) {
     constexpr uint32_t C = B > 256 ? B : 256;
-    const size_t lds = residency_lds(residency);
+    const size_t lds = launch_lds(residency, a.n / C);
     for_tiles(a.n, C, 1, kWave, on_lines, [&](const TileSpan &chunks, unsigned grid) {
         if (a.c.adamw)
             hipLaunchKernelGGL((fused_kernel<true, B, GS, QUANT, MANY>), dim3(grid), dim3(kWave),

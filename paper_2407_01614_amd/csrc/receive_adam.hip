@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kWave) void recv_adam_kernel(RecvArgs<GS> a, TileSp
 
 template <bool MANY, class GS>
 void launch_recv_tiles(const RecvArgs<GS> &a, int residency, bool on_lines, hipStream_t stream) {
-    const size_t lds = residency_lds(residency);
+    const size_t lds = launch_lds(residency, a.n / 256);
     for_tiles(a.n, 256, 1, kWave, on_lines, [&](const TileSpan &tiles, unsigned grid) {
         if (a.c.adamw)
             hipLaunchKernelGGL((recv_adam_kernel<true, MANY, GS>), dim3(grid), dim3(kWave), lds,

@@ -59,6 +59,16 @@ constexpr size_t kLdsPerCU = 160 * 1024;  // LDS of one gfx950 CU
 constexpr size_t residency_lds(int workgroups_per_cu) {
     return workgroups_per_cu <= 0 ? 0 : (kLdsPerCU / workgroups_per_cu) / 1024 * 1024;
 }
+// The reservation of a launch of `wgs` one-wave workgroups.  A grid that fits
+// the CUs' 32 wave slots at once has no workgroups left to hand out, so a cap
+// only holds part of it back for a second round: it is left uncapped.  Capped
+// -> uncapped at 1 M elements (4096 workgroups): Adam 6.5 -> 6.0 us, the fused
+// step 7.7 -> 6.9, the receive step of 8 interleaved copies 7.6 -> 6.7; at 2 M
+// (8192, the line) Adam 12.0 -> 12.1, fused 13.3 -> 13.5, the receive step
+// 13.2 -> 12.6; at 4 M Adam 20.6 -> 21.4, the fused step 23.3 -> 24.4.
+inline size_t launch_lds(int workgroups_per_cu, size_t wgs) {
+    return wgs <= 32 * kCUs ? 0 : residency_lds(workgroups_per_cu);
+}
 static_assert(kLdsPerCU / residency_lds(11) == 11 && kLdsPerCU / residency_lds(12) == 12 &&
                   kLdsPerCU / residency_lds(13) == 13 && kLdsPerCU / residency_lds(14) == 14,
               "a reservation caps residency at exactly the requested count");

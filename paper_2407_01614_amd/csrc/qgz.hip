@@ -37,9 +37,6 @@
 #ifndef ZPP_QGZ_THREADS
 #define ZPP_QGZ_THREADS 256
 #endif
-#ifndef ZPP_QGZ_QUANT_UNROLL
-#define ZPP_QGZ_QUANT_UNROLL 4
-#endif
 // Shape of the quantizer for blocks that are not powers of two
 // (zpp_chunk.h): at least three slots per lane, and the widest lane group
 // whose slots the block fills to this percentage.  Swept at the Llama-2-13B
@@ -125,67 +122,82 @@ __device__ __forceinline__ size_t i4_out_byte_any(size_t i, size_t k, uint32_t B
     return (k * P + q) * (B / 2) + ((i - k * B) >> 1);
 }
 
-template <int B, int U>
-__global__ __launch_bounds__(kQgzThreads) void quant_i4_kernel(
-    const float *__restrict__ src, size_t n, uint8_t *__restrict__ codes,
-    float *__restrict__ scales, uint32_t q_src, uint32_t num_src) {
+// One wave's U tiles from element `base` on, `rest` elements of them inside the
+// array (WHOLE: all of them).
+template <int B, int U, bool WHOLE>
+__device__ __forceinline__ void quant_i4_tiles(const float *__restrict__ src, size_t base,
+                                               uint32_t rest, uint8_t *__restrict__ codes,
+                                               float *__restrict__ scales, uint32_t q_src,
+                                               uint32_t num_src) {
     constexpr uint32_t kShift = __builtin_ctz(B);
     constexpr int C = B > 256 ? B : 256;
     constexpr int G = C / 256;
     constexpr int L = B < 256 ? B / 4 : kWave;
-    constexpr int kWaves = kQgzThreads / kWave;
-    const size_t ntiles = (n + C - 1) / C;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    for (size_t t0 = ((size_t)blockIdx.x * kWaves + wave) * U; t0 < ntiles;
-         t0 += (size_t)gridDim.x * kWaves * U) {
-        f32x4 x[U][G];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    src += base;
+    f32x4 x[U][G];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const size_t i = (t0 + u) * C + (size_t)g * 256 + (size_t)lane * 4;
-                if (t0 + u < ntiles && i + 4 <= n) {
-                    x[u][g] = ld_nt_at<f32x4, 4>(src + i);
-                } else {
-                    float h[4];
+        for (int g = 0; g < G; ++g) {
+            const uint32_t i = u * C + g * 256 + lane * 4;
+            if (WHOLE || i + 4 <= rest) {
+                x[u][g] = ld_nt_at<f32x4, 4>(src + i);
+            } else {
+                float h[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        h[e] = (t0 + u < ntiles && i + e < n) ? src[i + e] : 0.0f;
-                    x[u][g] = f32x4{h[0], h[1], h[2], h[3]};
-                }
+                for (int e = 0; e < 4; ++e)
+                    h[e] = i + e < rest ? src[i + e] : 0.0f;
+                x[u][g] = f32x4{h[0], h[1], h[2], h[3]};
             }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const size_t tile = t0 + u;
-            uint32_t mx = 0;
+    for (int u = 0; u < U; ++u) {
+        uint32_t mx = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            mx = max(mx, abs_bits_max4(x[u][g]));
+#pragma unroll
+        for (int off = L / 2; off >= 1; off >>= 1)
+            mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
+        const I4Quant q = i4_params(mx);
+        const auto store = [&](int g) {
+            const uint32_t i = u * C + g * 256 + lane * 4;
+            const uint32_t h = i4_half(x[u][g], q);
+            const size_t byte0 = i4_out_byte(base + i, kShift, q_src, num_src);
+            // the second byte holds elements i + 2 and i + 3
+            if (WHOLE || i + 2 < rest)
+                st_nt_at<uint16_t, 1>(codes + byte0, (uint16_t)h);
+            else if (i < rest)
+                codes[byte0] = (uint8_t)h;
+        };
+        // no loop over a single group: its store would be hoisted out of it as
+        // a plain, temporal one
+        if constexpr (G == 1) {
+            store(0);
+        } else {
 #pragma unroll
             for (int g = 0; g < G; ++g)
-                mx = max(mx, abs_bits_max4(x[u][g]));
-#pragma unroll
-            for (int off = L / 2; off >= 1; off >>= 1)
-                mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
-            const I4Quant q = i4_params(mx);
-            if (tile < ntiles) {
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const size_t i = tile * C + (size_t)g * 256 + (size_t)lane * 4;
-                    const uint32_t h = i4_half(x[u][g], q);
-                    const size_t byte0 = i4_out_byte(i, kShift, q_src, num_src);
-                    // the second byte holds elements i + 2 and i + 3
-                    if (i + 2 < n) {
-                        st_nt_at<uint16_t, 1>(codes + byte0, (uint16_t)h);
-                    } else if (i < n) {
-                        codes[byte0] = (uint8_t)h;
-                    }
-                }
-                const size_t k = (tile * C + (size_t)lane * 4) / B;
-                if (lane % L == 0 && k * B < n)
-                    scales[k * num_src + q_src] = q.scale;
-            }
+                store(g);
         }
+        if (lane % L == 0 && (WHOLE || u * C + lane * 4 < rest))
+            scales[((base + u * C + lane * 4) / B) * num_src + q_src] = q.scale;
     }
+}
+
+template <int B, int U>
+__global__ __launch_bounds__(kQgzThreads) void quant_i4_kernel(
+    const float *__restrict__ src, uint8_t *__restrict__ codes, float *__restrict__ scales,
+    uint32_t q_src, uint32_t num_src, TileSpan tiles) {
+    constexpr uint32_t C = (B > 256 ? B : 256) * U;
+    constexpr int kWaves = kQgzThreads / kWave;
+    const uint32_t t =
+        blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const size_t base = (tiles.first + t) * C;
+    if (__builtin_expect(t < tiles.whole, 1))
+        quant_i4_tiles<B, U, true>(src, base, C, codes, scales, q_src, num_src);
+    else if (t == tiles.whole && tiles.tail)
+        quant_i4_tiles<B, U, false>(src, base, tiles.tail, codes, scales, q_src, num_src);
 }
 
 // Vector path for a block B = 64 b that is not a power of two, lane-group
@@ -325,16 +337,53 @@ hipError_t launch_reduce(const GS &gs, size_t n, float *out, bool on_lines, hipS
     return hipGetLastError();
 }
 
+// Workgroups per CU.  One tile of a large block per wave into a sender's slots,
+// whose scales land between the other senders', streams better with fewer
+// resident once the array is long (8 senders, uncapped -> capped: 1024 at 60 M
+// / 100 M / 203 M elements 50.6 -> 48.1, 86.9 -> 79.8, 182 -> 166 us; 4096, at
+// 3, 53.6 -> 50.8, 88.8 -> 83.1, 180 -> 167; 2048, at 3 and with two tiles per
+// wave, 48.4 -> 48.4, 81.6 -> 77.6, 170 -> 156; with one at 5, 166); blocks up
+// to 512 gain nothing.
+template <int B>
+int quant_i4_residency(size_t n, uint32_t num_src) {
+    if (B < 1024 || num_src == 1 || n < (size_t)48 << 20)
+        return 0;
+    return B == 1024 ? 5 : 3;
+}
+
+template <int B, int U>
+void launch_quant_i4_u(const float *src, size_t n, uint8_t *codes, float *scales, uint32_t q_src,
+                       uint32_t num_src, hipStream_t stream) {
+    const size_t lds = residency_lds(quant_i4_residency<B>(n, num_src));
+    for_tiles(n, (B > 256 ? B : 256) * U, kQgzThreads / kWave, kQgzThreads, true,
+              [&](const TileSpan &tiles, unsigned grid) {
+                  hipLaunchKernelGGL((quant_i4_kernel<B, U>), dim3(grid), dim3(kQgzThreads), lds,
+                                     stream, src, codes, scales, q_src, num_src, tiles);
+              });
+}
+
+// Tiles of max(B, 256) elements a wave keeps in flight.  Blocks of 512 and
+// more fill a lane's registers with one (four took 24.1 / 24.2 / 36.7 us at
+// blocks of 512 / 1024 / 4096 and 25.9 M elements, one 19.9 / 20.2 / 21.4;
+// 203 M: 151 / 152 / 219, and 143 / 148 / 162).  Up to 256 four stream best
+// over long arrays (203 M: 147 us, 160 with two), two put a short one on more
+// waves (1 M: 3.3 us, 3.9 with four; 8 M 9.0, 13 M 12.9 and 12.4).  Blocks of
+// 64 and 128 in a sender's slots, whose codes are runs of 32 and 64 bytes, take
+// two at every length (203 M: 64 286 -> 251 us, 128 187 -> 169).
+constexpr size_t kTwoTilesMost = (size_t)8 << 20;
 template <int B>
 void launch_quant_i4_b(const float *src, size_t n, uint8_t *codes, float *scales,
                        uint32_t q_src, uint32_t num_src, hipStream_t stream) {
-    constexpr size_t C = B > 256 ? B : 256;
-    constexpr size_t kTilesPerBlock = (kQgzThreads / kWave) * ZPP_QGZ_QUANT_UNROLL;
-    const size_t ntiles = (n + C - 1) / C;
-    const size_t need = (ntiles + kTilesPerBlock - 1) / kTilesPerBlock;
-    const unsigned grid = (unsigned)(need < ZPP_QGZ_MAX_GRID ? need : ZPP_QGZ_MAX_GRID);
-    hipLaunchKernelGGL((quant_i4_kernel<B, ZPP_QGZ_QUANT_UNROLL>), dim3(grid), dim3(kQgzThreads),
-                       0, stream, src, n, codes, scales, q_src, num_src);
+    if constexpr (B == 2048) {
+        if (quant_i4_residency<B>(n, num_src) != 0)
+            return launch_quant_i4_u<B, 2>(src, n, codes, scales, q_src, num_src, stream);
+    }
+    if constexpr (B > 256)
+        launch_quant_i4_u<B, 1>(src, n, codes, scales, q_src, num_src, stream);
+    else if (n <= kTwoTilesMost || (B <= 128 && num_src > 1))
+        launch_quant_i4_u<B, 2>(src, n, codes, scales, q_src, num_src, stream);
+    else
+        launch_quant_i4_u<B, 4>(src, n, codes, scales, q_src, num_src, stream);
 }
 
 template <int G, int S>

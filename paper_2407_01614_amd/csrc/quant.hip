@@ -61,18 +61,17 @@ constexpr int kQuantThreads = ZPP_QUANT_THREADS;
 // The workgroup's place in the array.  The pass with the copy takes runs of
 // workgroups per XCD where its outputs do not start on lines (zpp_device.h):
 // 131 M elements off by one 123 us without, 116 with.  The quantizer alone
-// gains nothing from them (10.0 us at 13.1 M without, 10.2 with).
-template <bool COPY>
-__device__ __forceinline__ size_t group_of(bool on_lines) {
-    return COPY && !on_lines ? xcd_grouped(blockIdx.x, gridDim.x, kOffLineXcdRun) : blockIdx.x;
+// gains nothing from them (10.0 us at 13.1 M without, 10.2 with).  RUNS is a
+// template argument: chosen at run time it cost the pass on lines 0.7%.
+template <bool RUNS>
+__device__ __forceinline__ uint32_t group_of() {
+    return RUNS ? (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, kOffLineXcdRun) : blockIdx.x;
 }
 
-// With COPY the loaded bf16 are also stored to `copy`, bit for bit (the
-// secondary refresh taken into the quantization's pass).
-template <int B, int U, bool COPY>
+template <int B, int U>
 __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
     const uint16_t *__restrict__ src, size_t n, int8_t *__restrict__ codes,
-    float *__restrict__ scales, uint16_t *__restrict__ copy, bool on_lines) {
+    float *__restrict__ scales) {
     constexpr int L = (B / 8 < kWave) ? B / 8 : kWave;  // lanes per quant block
     constexpr int V = (B / 8 > kWave) ? B / (8 * kWave) : 1;
     constexpr int kGroupsPerWave = kWave / L;
@@ -84,7 +83,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
     const int li = lane % L;
     const int wave = threadIdx.x / kWave;
 
-    for (size_t g0 = group_of<COPY>(on_lines) * kGroupsPerBlock; g0 < nblocks;
+    for (size_t g0 = (size_t)blockIdx.x * kGroupsPerBlock; g0 < nblocks;
          g0 += (size_t)gridDim.x * kGroupsPerBlock) {
         // all U rows of loads first, then the reductions and stores
         u32x4 x[U][V];
@@ -131,21 +130,121 @@ __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
                 c.y = quant_word(x[u][v].z, x[u][v].w, q);
                 if (valid && i + 8 <= n) {
                     st_nt_at<u32x2, 1>(codes + i, c);
-                    if (COPY)
-                        st_nt_at<u32x4, 2>(copy + i, x[u][v]);
                 } else if (valid) {
-                    for (int e = 0; e < 8 && i + e < n; ++e) {
+                    for (int e = 0; e < 8 && i + e < n; ++e)
                         codes[i + e] =
                             (int8_t)((e < 4 ? c.x >> (8 * e) : c.y >> (8 * (e - 4))) & 0xFFu);
-                        if (COPY)
-                            copy[i + e] = src[i + e];
-                    }
                 }
             }
             if (valid && li == 0)
                 scales[k] = q.scale;
         }
     }
+}
+
+// The quantization with the copy: the workgroup's U rows of blocks, `rest` elements of them inside the arrays
+// (WHOLE: all of them).
+template <int B, int U, bool WHOLE>
+__device__ __forceinline__ void quant_copy_rows(const uint16_t *__restrict__ src,
+                                                int8_t *__restrict__ codes,
+                                                float *__restrict__ scales,
+                                                uint16_t *__restrict__ copy, uint32_t rest) {
+    constexpr int L = (B / 8 < kWave) ? B / 8 : kWave;  // lanes per quant block
+    constexpr int V = (B / 8 > kWave) ? B / (8 * kWave) : 1;
+    constexpr int kGroupsPerWave = kWave / L;
+    constexpr int kGroupsPerRow = kGroupsPerWave * (kQuantThreads / kWave);
+    const uint32_t li = threadIdx.x % L;
+    const uint32_t k0 = threadIdx.x / L;
+    // all U rows of loads first, then the reductions and stores
+    u32x4 x[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const uint32_t i = (u * kGroupsPerRow + k0) * B + (v * L + li) * 8;
+            if (WHOLE || i + 8 <= rest) {
+                x[u][v] = ld_nt_at<u32x4, 2>(src + i);
+            } else {
+                uint32_t h[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    h[e] = i + e < rest ? (uint32_t)src[i + e] : 0u;
+                x[u][v] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
+                                h[6] | (h[7] << 16)};
+            }
+        }
+    const auto row = [&](int u) {
+        const uint32_t k = u * kGroupsPerRow + k0;
+        u16x2 m2 = {0, 0};
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            m2 = __builtin_elementwise_max(m2, __builtin_elementwise_max(
+                     __builtin_elementwise_max(absbits2(x[u][v].x), absbits2(x[u][v].y)),
+                     __builtin_elementwise_max(absbits2(x[u][v].z), absbits2(x[u][v].w))));
+        uint32_t mx = max((uint32_t)m2.x, (uint32_t)m2.y);
+#pragma unroll
+        for (int off = L / 2; off >= 1; off >>= 1)
+            mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
+
+        const BlockQuant q = block_params(mx);
+        const auto store = [&](int v) {
+            const uint32_t i = k * B + (v * L + li) * 8;
+            u32x2 c;
+            c.x = quant_word(x[u][v].x, x[u][v].y, q);
+            c.y = quant_word(x[u][v].z, x[u][v].w, q);
+            if (WHOLE || i + 8 <= rest) {
+                st_nt_at<u32x2, 1>(codes + i, c);
+                st_nt_at<u32x4, 2>(copy + i, x[u][v]);
+            } else {
+                for (int e = 0; e < 8 && i + e < rest; ++e) {
+                    codes[i + e] =
+                        (int8_t)((e < 4 ? c.x >> (8 * e) : c.y >> (8 * (e - 4))) & 0xFFu);
+                    copy[i + e] = src[i + e];
+                }
+            }
+        };
+        // no loop over a single vector (nor, below, over a single row): its
+        // store would be hoisted out of it as a plain, temporal one (203 M
+        // elements 164 us, 158 non-temporal)
+        if constexpr (V == 1) {
+            store(0);
+        } else {
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                store(v);
+        }
+        if (li == 0 && (WHOLE || k * B < rest))
+            scales[k] = q.scale;
+    };
+    if constexpr (U == 1) {
+        row(0);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            row(u);
+    }
+}
+
+// The loaded bf16 are also stored to `copy`, bit for bit (the secondary
+// refresh taken into the quantization's pass).  Straight code for whole
+// workgroups: 25.9 M elements 22.5 -> 22.1 us, 203 M 161.6 -> 158.4, blocks of
+// 4096 177 -> 171.  (The quantizer alone written so is 5-15% faster up to 4 M
+// elements and 4-7% slower from 13 M on, so it keeps its own form.)
+template <int B, int U, bool RUNS>
+__global__ __launch_bounds__(kQuantThreads) void quant_copy_kernel(
+    const uint16_t *__restrict__ src, int8_t *__restrict__ codes, float *__restrict__ scales,
+    uint16_t *__restrict__ copy, TileSpan tiles) {
+    constexpr uint32_t C = (B < 512 ? 512 : B) * (kQuantThreads / kWave) * U;
+    const uint32_t t = group_of<RUNS>();
+    const size_t base = (tiles.first + t) * C;
+    src += base;
+    codes += base;
+    scales += base / B;
+    copy += base;
+    if (__builtin_expect(t < tiles.whole, 1))
+        quant_copy_rows<B, U, true>(src, codes, scales, copy, C);
+    else
+        quant_copy_rows<B, U, false>(src, codes, scales, copy, tiles.tail);
 }
 
 // Vector path for a block B = 64 b that is not a power of two, lane-group
@@ -157,10 +256,10 @@ __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
 // parameters itself, as in the power-of-two kernel: no LDS, no atomics and
 // no barrier.  Workgroups whose blocks all lie inside the array load each
 // vector with one predicated load; only the last one checks every element.
-template <int G, int S, bool COPY>
+template <int G, int S, bool COPY, bool RUNS>
 __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
     const uint16_t *__restrict__ src, size_t n, uint32_t B, int8_t *__restrict__ codes,
-    float *__restrict__ scales, uint16_t *__restrict__ copy, bool on_lines) {
+    float *__restrict__ scales, uint16_t *__restrict__ copy) {
     constexpr int kGroupsPerWave = kWave / G;
     constexpr int kGroupsPerBlock = kGroupsPerWave * (kQuantThreads / kWave);
     const uint32_t vpb = B / 8;
@@ -168,7 +267,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
     const int lane = threadIdx.x & (kWave - 1);
     const int li = lane % G;
     const size_t kw = (size_t)(threadIdx.x / kWave) * kGroupsPerWave + lane / G;
-    for (size_t g0 = group_of<COPY>(on_lines) * kGroupsPerBlock; g0 < nblocks;
+    for (size_t g0 = (size_t)group_of<RUNS>() * kGroupsPerBlock; g0 < nblocks;
          g0 += (size_t)gridDim.x * kGroupsPerBlock) {
         const size_t k = g0 + kw;
         const bool valid = k < nblocks;
@@ -243,14 +342,25 @@ __global__ __launch_bounds__(kQuantThreads) void quant_grp_kernel(
 template <int B, bool COPY>
 void launch_vec(const uint16_t *src, size_t n, int8_t *codes, float *scales, uint16_t *copy,
                 bool on_lines, hipStream_t stream) {
-    constexpr int L = (B / 8 < kWave) ? B / 8 : kWave;
     constexpr int U = COPY ? ZPP_QUANT_COPY_UNROLL : ZPP_QUANT_UNROLL;
-    constexpr size_t kGroupsPerBlock = (kWave / L) * (kQuantThreads / kWave) * U;
-    const size_t nblocks = (n + B - 1) / B;
-    const size_t need = (nblocks + kGroupsPerBlock - 1) / kGroupsPerBlock;
-    const unsigned grid = (unsigned)(need < ZPP_QUANT_MAX_GRID ? need : ZPP_QUANT_MAX_GRID);
-    hipLaunchKernelGGL((quant_vec_kernel<B, U, COPY>), dim3(grid), dim3(kQuantThreads), 0,
-                       stream, src, n, codes, scales, copy, on_lines);
+    constexpr uint32_t C = (B < 512 ? 512 : B) * (kQuantThreads / kWave) * U;
+    if constexpr (COPY) {
+        for_tiles(n, C, 1, kQuantThreads, on_lines, [&](const TileSpan &tiles, unsigned grid) {
+            if (on_lines)
+                hipLaunchKernelGGL((quant_copy_kernel<B, U, false>), dim3(grid),
+                                   dim3(kQuantThreads), 0, stream, src, codes, scales, copy,
+                                   tiles);
+            else
+                hipLaunchKernelGGL((quant_copy_kernel<B, U, true>), dim3(grid),
+                                   dim3(kQuantThreads), 0, stream, src, codes, scales, copy,
+                                   tiles);
+        });
+    } else {
+        const size_t need = (n + C - 1) / C;
+        const unsigned grid = (unsigned)(need < ZPP_QUANT_MAX_GRID ? need : ZPP_QUANT_MAX_GRID);
+        hipLaunchKernelGGL((quant_vec_kernel<B, U>), dim3(grid), dim3(kQuantThreads), 0, stream,
+                           src, n, codes, scales);
+    }
 }
 
 template <int G, int S, bool COPY>
@@ -260,8 +370,12 @@ void launch_grp(const uint16_t *src, size_t n, uint32_t block, int8_t *codes, fl
     const size_t nblocks = (n + block - 1) / block;
     const size_t need = (nblocks + kGroupsPerBlock - 1) / kGroupsPerBlock;
     const unsigned grid = (unsigned)(need < ZPP_QUANT_MAX_GRID ? need : ZPP_QUANT_MAX_GRID);
-    hipLaunchKernelGGL((quant_grp_kernel<G, S, COPY>), dim3(grid), dim3(kQuantThreads), 0,
-                       stream, src, n, block, codes, scales, copy, on_lines);
+    if (COPY && !on_lines)
+        hipLaunchKernelGGL((quant_grp_kernel<G, S, COPY, COPY>), dim3(grid), dim3(kQuantThreads),
+                           0, stream, src, n, block, codes, scales, copy);
+    else
+        hipLaunchKernelGGL((quant_grp_kernel<G, S, COPY, false>), dim3(grid), dim3(kQuantThreads),
+                           0, stream, src, n, block, codes, scales, copy);
 }
 
 template <int S, bool COPY>

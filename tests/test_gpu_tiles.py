@@ -277,3 +277,32 @@ def test_fused_block_routes(zpp, block, sources):
         zpp.refresh_quantize_i8(b[4], b[3], b[5], b[6], block=block)
         for x, y, name in zip(got, ref, names):
             assert torch.equal(x.raw, y.raw), "%s, n = %d" % (name, n)
+
+
+@pytest.mark.parametrize("block", [64, 256, 512, 4096])
+def test_quantizer_edges(zpp, block):
+    """The quantizers at lengths around their whole tiles (rows of 512 elements
+    or of one block per wave): what a longer call over whole tiles gives, its
+    elements past the end zero, which no absmax sees."""
+    tile = max(512, block) * 8
+    full = 4 * tile
+    rnd = synth.rng(305, block)
+    bf16 = (rnd.standard_normal(full).astype(np.float32).view(np.uint32) >> 16).astype(np.int16)
+    f32 = rnd.standard_normal(full).astype(np.float32)
+    for n in (tile // 2, tile - 1, tile, tile + 1, tile + block + 3, 2 * tile - 8, 2 * tile + 2):
+        got = []
+        for m in (n, full):
+            h, x = bf16.copy(), f32.copy()
+            h[n:], x[n:] = 0, 0
+            src16, src32 = Buf(m, torch.int16, 0, h), Buf(m, torch.float32, 0, x)
+            nb = -(-m // block)
+            second = Buf(m, torch.int16)
+            c, s, c2, s2 = (Buf(m, torch.int8), Buf(nb, torch.float32),
+                            Buf(m, torch.int8), Buf(nb, torch.float32))
+            zpp.quantize_blockwise_i8(src16.t, c.t, s.t, block=block)
+            zpp.refresh_quantize_i8(second.t, src16.t, c2.t, s2.t, block=block)
+            c4, s4 = Buf((m + 1) // 2, torch.uint8), Buf(nb, torch.float32)
+            zpp.quantize_blockwise_i4(src32.t, c4.t, s4.t, block=block)
+            got.append([b.bits() for b in (c, s, second, c2, s2, c4, s4)])
+        same_start(*got, n, ("codes", "scales", "secondary", "codes with the copy",
+                             "scales with the copy", "int4 codes", "int4 scales"))

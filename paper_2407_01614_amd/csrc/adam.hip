@@ -9,8 +9,8 @@
 // reused).  The grid is one-shot (one tile per workgroup): on this GPU a
 // persistent grid of a few thousand workgroups streams about 20% slower.
 // Residency is capped at ZPP_ADAM_RESIDENCY one-wave workgroups per CU: at
-// the Llama-2-13B partition the step takes 923-931 us with 11 resident
-// (931-944 with 9, 10 or 12), 1003-1016 us uncapped.
+// the Llama-2-13B partition the step takes 923-931 us with 10 resident
+// (928-944 with 9 or 11), 1003-1016 us uncapped.
 #include "zpp_adam.h"
 #include "zpp_device.h"
 #include "zpp_launch.h"
@@ -22,7 +22,7 @@
 #define ZPP_ADAM_THREADS 64
 #endif
 #ifndef ZPP_ADAM_RESIDENCY
-#define ZPP_ADAM_RESIDENCY 11
+#define ZPP_ADAM_RESIDENCY 10
 #endif
 
 namespace zpp {

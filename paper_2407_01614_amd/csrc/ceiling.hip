@@ -60,8 +60,8 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(u32x4 *__restrict__ 
 
 // The Adam step (adam.hip): one-wave workgroups, one 256-element tile each;
 // a lane loads one float4 of p, m, v and g, stores float4 p, m, v in place
-// and 4 bf16 (8 bytes); at most 11 workgroups per CU (the step's own cap).
-constexpr int kAdamPatternResidency = 11;
+// and 4 bf16 (8 bytes); at most 10 workgroups per CU (the step's own cap).
+constexpr int kAdamPatternResidency = 10;
 
 __global__ __launch_bounds__(64) void adam_pattern_kernel(float *__restrict__ p,
                                                           float *__restrict__ m,

@@ -29,12 +29,12 @@
 // (1073 against 1095 us one pass); the single pass of the qgZ receive took
 // 1112-1117 against 1245-1460 us.
 // Residency is capped at ZPP_FUSED_RESIDENCY
-// workgroups per CU, as for the optimizer step: 1031-1046 us with 12 resident
-// at the Llama-2-13B partition (9-20 within 1%), 1127-1145 us uncapped.  With
+// workgroups per CU, as for the optimizer step: 1031-1046 us with 11 resident
+// at the Llama-2-13B partition (9-18 within 1%), 1127-1145 us uncapped.  With
 // the qgZ receive in place of the fp32 gradient (8 int4 sources) the cap is
-// ZPP_FUSED_RECV_RESIDENCY: 1111 us with 13, 1118 with 14, 1150 with 12, 1216
-// with 11, 1142 uncapped.  From one interleaved receive buffer
-// (ZPP_FUSED_RECV_IL_RESIDENCY): 1054 us with 14, 1062 with 16, 1075 with 12,
+// ZPP_FUSED_RECV_RESIDENCY: 1111 us with 12, 1118 with 14, 1150 with 11, 1216
+// with 10, 1142 uncapped.  From one interleaved receive buffer
+// (ZPP_FUSED_RECV_IL_RESIDENCY): 1054 us with 14, 1062 with 16, 1075 with 11,
 // 1097 uncapped, against 1096 us from separate arrays in the same run.
 #include <type_traits>
 
@@ -46,10 +46,10 @@
 #include "zpp_quant.h"
 
 #ifndef ZPP_FUSED_RESIDENCY
-#define ZPP_FUSED_RESIDENCY 12
+#define ZPP_FUSED_RESIDENCY 11
 #endif
 #ifndef ZPP_FUSED_RECV_RESIDENCY
-#define ZPP_FUSED_RECV_RESIDENCY 13
+#define ZPP_FUSED_RECV_RESIDENCY 12
 #endif
 #ifndef ZPP_FUSED_RECV_IL_RESIDENCY
 #define ZPP_FUSED_RECV_IL_RESIDENCY 14
@@ -254,7 +254,8 @@ void launch_wide(const FusedArgs &a, const GS &gs, uint32_t block, bool on_lines
     const uint32_t threads = (block / 4 + kWave - 1) / kWave * kWave;
     // beyond half of kWideMost a block of fewer waves would be capped too low
     const int per_cu = threads / kWave >= 4 ? wide_residency(gs, a.n) : 0;
-    const size_t lds = residency_lds(per_cu) - (per_cu ? 1024 : 0);  // the maxima's own
+    // the maxima have a granule of their own
+    const size_t lds = per_cu ? residency_lds(per_cu) - kLdsGranule : 0;
     for_tiles(a.n, block, 1, threads, on_lines, [&](const TileSpan &blocks, unsigned grid) {
         if (a.c.adamw)
             hipLaunchKernelGGL((fused_wide_kernel<true, MANY, GS>), dim3(grid), dim3(threads),
@@ -288,12 +289,12 @@ void launch_fused_chunks(const FusedArgs &a, const GS &gs, int residency, bool o
 
 template <int B, bool QUANT = true, class GS>
 void launch_fused_b(const FusedArgs &a, const GS &gs, bool on_lines, hipStream_t stream) {
-    // the step with its copies alone, ahead of the quantizer, keeps fewer: 10
-    // (Llama-2-7B partition, both kernels: 1138 us with 9, 1138 with 10, 1146
-    // with 11, 1154 with 12, 1153 with 8; with 8 copies from the interleaved
-    // buffer at 50 M 305 with 10, 310 with 12, 315 with 8), from separate
-    // arrays as many as with the quantization (291 us with 13, 299 with 10)
-    int residency = QUANT || std::is_same_v<GS, I4Grad> ? fused_residency<GS>() : 10;
+    // the step with its copies alone, ahead of the quantizer, keeps fewer: 9
+    // (Llama-2-7B partition, both kernels: 1138 us with 9, 1146 with 10, 1154
+    // with 11, 1153 with 8; with 8 copies from the interleaved buffer at 50 M
+    // 305 with 9, 310 with 11, 315 with 8), from separate arrays as many as
+    // with the quantization (291 us with 12, 299 with 9)
+    int residency = QUANT || std::is_same_v<GS, I4Grad> ? fused_residency<GS>() : 9;
     if constexpr (!std::is_same_v<GS, F32Grad>) {
         if (gs.num_src >= kManySources)
             residency = 0;  // left to the hardware (zpp_i4grad.h)

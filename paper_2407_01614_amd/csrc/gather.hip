@@ -21,7 +21,7 @@
 //
 // Vector kernel (any other multiple of 64 as the block): a lane's scale is
 // a vector load at its own block index (shared by the lanes of a block,
-// served from cache); two-wave workgroups with two rows per wave, at most 12
+// served from cache); two-wave workgroups with two rows per wave, at most 11
 // workgroups per CU.
 #include "zpp_device.h"
 #include "zpp_launch.h"
@@ -33,7 +33,7 @@
 #define ZPP_GATHER_THREADS 128
 #endif
 #ifndef ZPP_GATHER_RESIDENCY
-#define ZPP_GATHER_RESIDENCY 12
+#define ZPP_GATHER_RESIDENCY 11
 #endif
 #ifndef ZPP_GATHER_MAX_GRID_X
 #define ZPP_GATHER_MAX_GRID_X (1u << 20)

@@ -341,14 +341,14 @@ hipError_t launch_reduce(const GS &gs, size_t n, float *out, bool on_lines, hipS
 // whose scales land between the other senders', streams better with fewer
 // resident once the array is long (8 senders, uncapped -> capped: 1024 at 60 M
 // / 100 M / 203 M elements 50.6 -> 48.1, 86.9 -> 79.8, 182 -> 166 us; 4096, at
-// 3, 53.6 -> 50.8, 88.8 -> 83.1, 180 -> 167; 2048, at 3 and with two tiles per
-// wave, 48.4 -> 48.4, 81.6 -> 77.6, 170 -> 156; with one at 5, 166); blocks up
+// 2, 53.6 -> 50.8, 88.8 -> 83.1, 180 -> 167; 2048, at 2 and with two tiles per
+// wave, 48.4 -> 48.4, 81.6 -> 77.6, 170 -> 156; with one at 4, 166); blocks up
 // to 512 gain nothing.
 template <int B>
 int quant_i4_residency(size_t n, uint32_t num_src) {
     if (B < 1024 || num_src == 1 || n < (size_t)48 << 20)
         return 0;
-    return B == 1024 ? 5 : 3;
+    return B == 1024 ? 4 : 2;
 }
 
 template <int B, int U>

@@ -19,14 +19,14 @@
 // source) and one scale per source (zpp_i4grad.h: sources taken eight at a
 // time, all eight in flight before their fma passes).  Residency is capped at
 // ZPP_RECV_RESIDENCY workgroups per CU: at the Llama-2-13B partition with 8
-// sources 994-1001 us with 12 (13: 995-999, 11: 1001-1008, 14: 1003-1011),
+// sources 994-1001 us with 11 (12: 995-999, 10: 1001-1008, 14: 1003-1011),
 // 1027 us uncapped.  Scales loaded as wave-uniform scalar loads (possible for
 // blocks of 256 or more) took 1112-1251 us: the scalar cache's latency is not
 // hidden the way the vector loads' is.
 //
 // The same kernel reads the P copies from one interleaved receive buffer
 // (I4GradIl, zpp_i4grad.h: a wave's codes of all sources within one
-// contiguous run): 938 us with ZPP_RECV_IL_RESIDENCY = 12 (14: 949, 16: 955,
+// contiguous run): 938 us with ZPP_RECV_IL_RESIDENCY = 11 (14: 949, 16: 955,
 // uncapped 978) against 981 us from separate arrays in the same run.
 #include "zpp_adam.h"
 #include "zpp_chunk.h"
@@ -35,10 +35,10 @@
 #include "zpp_launch.h"
 
 #ifndef ZPP_RECV_RESIDENCY
-#define ZPP_RECV_RESIDENCY 12
+#define ZPP_RECV_RESIDENCY 11
 #endif
 #ifndef ZPP_RECV_IL_RESIDENCY
-#define ZPP_RECV_IL_RESIDENCY 12
+#define ZPP_RECV_IL_RESIDENCY 11
 #endif
 namespace zpp {
 namespace {

@@ -1,6 +1,7 @@
 // Work distribution shared by the kernels and the host checks: the lane
 // layout of the quantizers for blocks that are not powers of two (any
-// multiple of 64 up to 4096), and the renumbering of workgroups per XCD.
+// multiple of 64 up to 4096), the renumbering of workgroups per XCD, and the
+// cap on workgroups resident per CU.
 #pragma once
 
 #include <stddef.h>
@@ -55,6 +56,36 @@ constexpr size_t xcd_grouped(size_t w, size_t grid, size_t R) {
         return w;
     const size_t run = w / (8 * R), r = w % (8 * R);
     return (run + 1) * 8 * R <= grid ? run * 8 * R + (r % 8) * R + r / 8 : w;
+}
+
+// Residency cap.  The streaming kernels that keep many HBM streams open at
+// once (the optimizer step: four arrays read, four written) run faster with
+// fewer workgroups resident per CU than the hardware would otherwise place:
+// too many waves in flight oversubscribe the memory channels.  A launch caps
+// residency by reserving dynamic LDS that its kernel never touches, and the
+// dispatcher still hands out the one-shot grid as workgroups retire.  A CU
+// allocates LDS in granules (measured with a kernel that counts the
+// workgroups alive at once: 128 granules of 1280 bytes), so residency_lds(k)
+// is the fewest whole granules that k workgroups fit in and k + 1 do not.
+// residency_lds(0) = 0 leaves residency to the hardware.
+constexpr size_t kCUs = 256;          // CUs of an MI355X
+constexpr size_t kLdsGranule = 1280;  // bytes
+constexpr size_t kLdsGranules = 128;  // of one gfx950 CU: 160 KiB
+constexpr size_t workgroups_per_cu(size_t lds) {
+    return kLdsGranules / ((lds + kLdsGranule - 1) / kLdsGranule);
+}
+constexpr size_t residency_lds(int workgroups) {
+    return workgroups <= 0 ? 0 : (kLdsGranules / (workgroups + 1) + 1) * kLdsGranule;
+}
+// The reservation of a launch of `wgs` one-wave workgroups.  A grid that fits
+// the CUs' 32 wave slots at once has no workgroups left to hand out, so a cap
+// only holds part of it back for a second round: it is left uncapped.  Capped
+// -> uncapped at 1 M elements (4096 workgroups): Adam 6.5 -> 6.0 us, the fused
+// step 7.7 -> 6.9, the receive step of 8 interleaved copies 7.6 -> 6.7; at 2 M
+// (8192, the line) Adam 12.0 -> 12.1, fused 13.3 -> 13.5, the receive step
+// 13.2 -> 12.6; at 4 M Adam 20.6 -> 21.4, the fused step 23.3 -> 24.4.
+inline size_t launch_lds(int workgroups, size_t wgs) {
+    return wgs <= 32 * kCUs ? 0 : residency_lds(workgroups);
 }
 
 }  // namespace zpp

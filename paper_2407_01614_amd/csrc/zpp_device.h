@@ -45,34 +45,6 @@ __device__ __forceinline__ size_t block_of(const BlockDiv &d, size_t i) {
     return d.magic ? (size_t)__umul64hi((unsigned long long)(i >> 6), d.magic) : i >> d.shift;
 }
 
-// Residency cap.  The streaming kernels that keep many HBM streams open at
-// once (the optimizer step: four arrays read, four written) run faster with
-// fewer workgroups resident per CU than the hardware would otherwise place:
-// too many waves in flight oversubscribe the memory channels.  The optimizer
-// step, the fused steps, the step with the qgZ receive and the gather use it.  A launch caps
-// residency by reserving dynamic LDS that its kernel never touches: a CU then
-// holds at most kLdsPerCU / residency_lds(k) = k such workgroups, and the
-// dispatcher still hands out the one-shot grid as workgroups retire.
-// residency_lds(0) = 0 leaves residency to the hardware.
-constexpr size_t kCUs = 256;              // CUs of an MI355X
-constexpr size_t kLdsPerCU = 160 * 1024;  // LDS of one gfx950 CU
-constexpr size_t residency_lds(int workgroups_per_cu) {
-    return workgroups_per_cu <= 0 ? 0 : (kLdsPerCU / workgroups_per_cu) / 1024 * 1024;
-}
-// The reservation of a launch of `wgs` one-wave workgroups.  A grid that fits
-// the CUs' 32 wave slots at once has no workgroups left to hand out, so a cap
-// only holds part of it back for a second round: it is left uncapped.  Capped
-// -> uncapped at 1 M elements (4096 workgroups): Adam 6.5 -> 6.0 us, the fused
-// step 7.7 -> 6.9, the receive step of 8 interleaved copies 7.6 -> 6.7; at 2 M
-// (8192, the line) Adam 12.0 -> 12.1, fused 13.3 -> 13.5, the receive step
-// 13.2 -> 12.6; at 4 M Adam 20.6 -> 21.4, the fused step 23.3 -> 24.4.
-inline size_t launch_lds(int workgroups_per_cu, size_t wgs) {
-    return wgs <= 32 * kCUs ? 0 : residency_lds(workgroups_per_cu);
-}
-static_assert(kLdsPerCU / residency_lds(11) == 11 && kLdsPerCU / residency_lds(12) == 12 &&
-                  kLdsPerCU / residency_lds(13) == 13 && kLdsPerCU / residency_lds(14) == 14,
-              "a reservation caps residency at exactly the requested count");
-
 // The tiles of one launch: `whole` tiles of C elements from tile `first` on,
 // then, where the array does not end with them, one of `tail` elements.  The
 // host counts them, so that a kernel decides by one 32-bit comparison which

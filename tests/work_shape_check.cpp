@@ -15,6 +15,10 @@
 // workgroups the ones that XCD x receives (positions x, x + 8, ...) take R
 // consecutive numbers.
 //
+// Residency caps (residency_lds): for every count in use the reservation is
+// whole LDS granules of the CU and holds exactly that many workgroups, with the
+// wide kernel's own granule of LDS beside the rest too.
+//
 // Prints the worst fills and "work shapes ok".
 #include <stdint.h>
 #include <stdio.h>
@@ -126,6 +130,26 @@ static long check_xcd_grouped() {
     return bad;
 }
 
+static long check_residency() {
+    long bad = 0;
+    for (int k : {2, 3, 4, 9, 10, 11, 12, 14, 16}) {
+        const size_t lds = zpp::residency_lds(k);
+        // 128 granules of 1280 bytes per CU
+        const size_t held = 128 / ((lds + 1279) / 1280);
+        if (lds % 1280 || lds > 64 * 1024 || held != (size_t)k ||
+            zpp::workgroups_per_cu(lds) != held || zpp::workgroups_per_cu(lds - 1280 + 128) != held) {
+            printf("residency: %zu bytes for %d hold %zu\n", lds, k, held);
+            ++bad;
+        }
+    }
+    if (zpp::residency_lds(0) != 0 || zpp::launch_lds(9, 32 * 256) != 0 ||
+        zpp::launch_lds(9, 32 * 256 + 1) != zpp::residency_lds(9)) {
+        printf("residency: launches left to the hardware\n");
+        ++bad;
+    }
+    return bad;
+}
+
 int main() {
     double worst_i8 = 1.0, worst_i8c = 1.0, worst_i4 = 1.0;
     long bad = 0;
@@ -136,6 +160,7 @@ int main() {
     bad += check_groups(8, 55, 2, 2, "int8+copy", worst_i8c);
     bad += check_groups(4, 75, 3, 4, "int4", worst_i4);
     bad += check_xcd_grouped();
+    bad += check_residency();
     printf("worst fill: int8 %.4f, int8+copy %.4f, int4 %.4f\n", worst_i8, worst_i8c, worst_i4);
     if (bad) {
         printf("%ld failures\n", bad);

@@ -19,13 +19,33 @@ zpp_status hip_fail(hipError_t e) {
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
-// Whether every output (NULL: not asked for) starts on a 128-byte line, which
-// decides the order a launch's workgroups take (zpp_launch.h).
-bool on_lines(std::initializer_list<const void *> outputs) {
-    for (const void *p : outputs)
-        if (!aligned(p, 128))
+// Whether every array (NULL: not asked for) starts at a multiple of `line`
+// bytes.  Which outputs have to, for a launch's workgroups to keep the plain
+// order rather than runs per XCD (kOffLineXcdRun, zpp_device.h), was measured
+// with ranges that start a number of elements into lines; plain order against
+// runs, in us:
+//   the step's bf16 at 64 bytes: Adam 13 M 62.9 / 64.6, 52 M 251 / 256; the
+//     receive step of 8 interleaved copies 52 M 252 / 258, 210 M 978 / 1014
+//     (at 32 bytes, its state at 64: Adam 52 M 290 / 264), but that receive
+//     step at 1 M, whose grid fits the GPU at once, 7.5 / 7.0;
+//   int8 codes at 64 bytes: the fused step 13 M 71.5 / 73.8, the refresh with
+//     its quantization 4 M 4.49 / 4.82 (at 32 bytes, bf16 at 64: the fused
+//     step 210 M 1225 / 1155);
+//   the reduced fp32 gradient at 64 bytes: 52 M 69.2 / 71.1, at 32 70.4 / 71.2;
+//   a bf16 copy alone at 64 bytes is the other way: 52 M 35.5 / 34.1.
+bool start_at(size_t line, std::initializer_list<const void *> arrays) {
+    for (const void *p : arrays)
+        if (!aligned(p, line))
             return false;
     return true;
+}
+bool step_on_lines(const float *p, const float *m, const float *v, const uint16_t *out,
+                   size_t bf16_line = 64) {
+    return start_at(128, {p, m, v}) && start_at(bf16_line, {out});
+}
+bool fused_on_lines(const float *p, const float *m, const float *v, const uint16_t *primary,
+                    const uint16_t *secondary, const int8_t *codes) {
+    return start_at(128, {p, m, v, primary, secondary}) && start_at(64, {codes});
 }
 
 // Do [a, a + abytes) and [b, b + bbytes) share a byte?
@@ -128,7 +148,7 @@ ZPP_API zpp_status zpp_adam_partition_step(float *master, float *exp_avg, float 
     const size_t bytes[5] = {4 * n, 4 * n, 4 * n, 4 * n, 2 * n};
     if (any_overlap(ptrs, bytes, 5))
         return ZPP_EOVERLAP;
-    const bool lines = on_lines({master, exp_avg, exp_avg_sq, primary_bf16});
+    const bool lines = step_on_lines(master, exp_avg, exp_avg_sq, primary_bf16);
     const hipError_t e = zpp::launch_adam(master, exp_avg, exp_avg_sq, grad, primary_bf16, n,
                                           adam_consts(*hp), lines, stream);
     return e == hipSuccess ? ZPP_OK : hip_fail(e);
@@ -164,8 +184,8 @@ ZPP_API zpp_status zpp_adam_step_refresh_quantize(float *master, float *exp_avg,
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines =
-            on_lines({master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16, codes});
+        const bool lines = fused_on_lines(master, exp_avg, exp_avg_sq, primary_bf16,
+                                          secondary_bf16, codes);
         const hipError_t e =
             zpp::launch_fused(master, exp_avg, exp_avg_sq, grad, primary_bf16, secondary_bf16,
                               codes, scales, n, block, adam_consts(*hp), lines, stream);
@@ -192,7 +212,7 @@ ZPP_API zpp_status zpp_refresh_secondary(uint16_t *secondary_bf16, const uint16_
     if (st != ZPP_OK)
         return st;
     if (count) {
-        const bool lines = on_lines({secondary_bf16});
+        const bool lines = start_at(128, {secondary_bf16});
         const hipError_t e = zpp::launch_refresh(secondary_bf16, src_bf16, count, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
@@ -219,7 +239,7 @@ ZPP_API zpp_status zpp_quantize_blockwise_i8(const uint16_t *src_bf16, size_t n,
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines = on_lines({codes});
+        const bool lines = start_at(128, {codes});
         const hipError_t e = zpp::launch_quantize(src_bf16, n, block, codes, scales, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
@@ -248,7 +268,7 @@ ZPP_API zpp_status zpp_refresh_quantize_i8(uint16_t *secondary_bf16, const uint1
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines = on_lines({secondary_bf16, codes});
+        const bool lines = start_at(128, {secondary_bf16}) && start_at(64, {codes});
         const hipError_t e =
             zpp::launch_quantize_copy(src_bf16, n, block, codes, scales, secondary_bf16, lines,
                                       stream);
@@ -336,7 +356,7 @@ ZPP_API zpp_status zpp_quantize_blockwise_i4(const float *src, size_t n, uint32_
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines = on_lines({codes});
+        const bool lines = start_at(128, {codes});
         const hipError_t e = zpp::launch_quantize_i4(src, n, block, codes, scales, lines, stream);
         if (e != hipSuccess)
             return hip_fail(e);
@@ -384,7 +404,7 @@ ZPP_API zpp_status zpp_dequant_reduce_i4(const uint8_t *const *src_codes,
             return st;
     }
     if (n) {
-        const bool lines = on_lines({out});
+        const bool lines = start_at(32, {out});
         const hipError_t e = zpp::launch_dequant_reduce_i4(src_codes, src_scales, num_src, n,
                                                            block, scale_out, out, lines, stream);
         if (e != hipSuccess)
@@ -445,7 +465,7 @@ ZPP_API zpp_status zpp_qgz_receive_adam_step(float *master, float *exp_avg, floa
             return st;
     }
     if (n) {
-        const bool lines = on_lines({master, exp_avg, exp_avg_sq, primary_bf16});
+        const bool lines = step_on_lines(master, exp_avg, exp_avg_sq, primary_bf16);
         const hipError_t e = zpp::launch_receive_adam(master, exp_avg, exp_avg_sq, src_codes,
                                                       src_scales, num_src, block, scale_out,
                                                       primary_bf16, n, adam_consts(*hp), lines,
@@ -510,8 +530,8 @@ ZPP_API zpp_status zpp_qgz_receive_step_refresh_quantize(
             return st;
     }
     if (n) {
-        const bool lines =
-            on_lines({master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16, codes});
+        const bool lines = fused_on_lines(master, exp_avg, exp_avg_sq, primary_bf16,
+                                          secondary_bf16, codes);
         const hipError_t e = zpp::launch_fused_receive(
             master, exp_avg, exp_avg_sq, src_codes, src_scales, num_src, grad_block, scale_out,
             primary_bf16, secondary_bf16, codes, scales, n, block, adam_consts(*hp), lines, stream);
@@ -546,7 +566,7 @@ ZPP_API zpp_status zpp_quantize_blockwise_i4_interleaved(const float *src, size_
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines = on_lines({codes});
+        const bool lines = start_at(128, {codes});
         const hipError_t e = zpp::launch_quantize_i4_il(src, n, block, source, num_src, codes,
                                                         scales, lines, stream);
         if (e != hipSuccess)
@@ -589,7 +609,7 @@ ZPP_API zpp_status zpp_dequant_reduce_i4_interleaved(const uint8_t *codes, const
             return st;
     }
     if (n) {
-        const bool lines = on_lines({out});
+        const bool lines = start_at(32, {out});
         const hipError_t e = zpp::launch_dequant_reduce_i4_il(codes, scales, num_src, n, block,
                                                               scale_out, out, lines, stream);
         if (e != hipSuccess)
@@ -640,7 +660,8 @@ ZPP_API zpp_status zpp_qgz_receive_adam_step_interleaved(
             return st;
     }
     if (n) {
-        const bool lines = on_lines({master, exp_avg, exp_avg_sq, primary_bf16});
+        const bool lines = step_on_lines(master, exp_avg, exp_avg_sq, primary_bf16,
+                                         n <= (2u << 20) ? 128 : 64);
         const hipError_t e = zpp::launch_receive_adam_il(master, exp_avg, exp_avg_sq, codes,
                                                          scales, num_src, block, scale_out,
                                                          primary_bf16, n, adam_consts(*hp), lines,
@@ -699,8 +720,8 @@ ZPP_API zpp_status zpp_qgz_receive_step_refresh_quantize_interleaved(
             return st;
     }
     if (n) {
-        const bool lines =
-            on_lines({master, exp_avg, exp_avg_sq, primary_bf16, secondary_bf16, codes});
+        const bool lines = fused_on_lines(master, exp_avg, exp_avg_sq, primary_bf16,
+                                          secondary_bf16, codes);
         const hipError_t e = zpp::launch_fused_receive_il(
             master, exp_avg, exp_avg_sq, src_codes, src_scales, num_src, grad_block, scale_out,
             primary_bf16, secondary_bf16, codes, scales, n, block, adam_consts(*hp), lines, stream);

@@ -55,7 +55,7 @@ struct TileSpan {
     size_t first;
     uint32_t whole;
     uint32_t tail;
-    uint32_t on_lines;  // every output starts on a cache line
+    uint32_t on_lines;  // the outputs start on their lines (zpp_api.hip)
 };
 
 // Outputs that do not start on a 128-byte line: a wave's store then ends inside
@@ -65,7 +65,8 @@ struct TileSpan {
 // Adam step at 13.1 M elements off by one 81.3 us without, 70.2 / 69.6 /
 // 69.3 / 68.9 with runs of 16 / 32 / 64 / 128 (100 M: 618, 543 / 531 / 518 /
 // 511), the fused step 105 and 80, the receive step 82 and 72, the gather of
-// 200 M 121 and 102.  Stored as ordinary, temporal ones they were slower (73
+// 200 M 121 and 102.  (Outputs that start inside a line but far enough from its
+// ends lose by the runs: zpp_api.hip has the measured lines.)  Stored as ordinary, temporal ones they were slower (73
 // us for the Adam step, 95 without the runs).
 constexpr size_t kOffLineXcdRun = 128;
 

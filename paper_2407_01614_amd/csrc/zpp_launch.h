@@ -1,7 +1,8 @@
 // Internal launchers behind the C ABI.  Arguments are already validated; each
 // launcher only enqueues its kernel on `stream` and returns the launch error.
-// `on_lines`: every output array starts on a 128-byte line (kOffLineXcdRun in
-// zpp_device.h says what that decides); nothing else depends on alignment.
+// `on_lines`: the outputs start on the lines that the call asks of them
+// (zpp_api.hip), so its workgroups keep the plain order; otherwise they run as
+// kOffLineXcdRun in zpp_device.h says.  Nothing else depends on alignment.
 #pragma once
 
 #include <hip/hip_runtime_api.h>

@@ -59,10 +59,10 @@ namespace {
 constexpr int kQuantThreads = ZPP_QUANT_THREADS;
 
 // The workgroup's place in the array.  The pass with the copy takes runs of
-// workgroups per XCD where its outputs do not start on lines (zpp_device.h):
-// 131 M elements off by one 123 us without, 116 with.  The quantizer alone
-// gains nothing from them (10.0 us at 13.1 M without, 10.2 with).  RUNS is a
-// template argument: chosen at run time it cost the pass on lines 0.7%.
+// workgroups per XCD where its outputs do not start on lines, for the blocks
+// and lengths of quant_copy_runs (zpp_chunk.h).  The quantizer alone gains
+// nothing from them (10.0 us at 13.1 M without, 10.2 with).  RUNS is a template
+// argument: chosen at run time it cost the pass on lines 0.7%.
 template <bool RUNS>
 __device__ __forceinline__ uint32_t group_of() {
     return RUNS ? (uint32_t)xcd_grouped(blockIdx.x, gridDim.x, kOffLineXcdRun) : blockIdx.x;
@@ -345,13 +345,14 @@ void launch_vec(const uint16_t *src, size_t n, int8_t *codes, float *scales, uin
     constexpr int U = COPY ? ZPP_QUANT_COPY_UNROLL : ZPP_QUANT_UNROLL;
     constexpr uint32_t C = (B < 512 ? 512 : B) * (kQuantThreads / kWave) * U;
     if constexpr (COPY) {
+        constexpr bool kRuns = B <= 512;  // quant_copy_runs
         for_tiles(n, C, 1, kQuantThreads, on_lines, [&](const TileSpan &tiles, unsigned grid) {
-            if (on_lines)
-                hipLaunchKernelGGL((quant_copy_kernel<B, U, false>), dim3(grid),
+            if (kRuns && !on_lines)
+                hipLaunchKernelGGL((quant_copy_kernel<B, U, kRuns>), dim3(grid),
                                    dim3(kQuantThreads), 0, stream, src, codes, scales, copy,
                                    tiles);
             else
-                hipLaunchKernelGGL((quant_copy_kernel<B, U, true>), dim3(grid),
+                hipLaunchKernelGGL((quant_copy_kernel<B, U, false>), dim3(grid),
                                    dim3(kQuantThreads), 0, stream, src, codes, scales, copy,
                                    tiles);
         });
@@ -370,7 +371,7 @@ void launch_grp(const uint16_t *src, size_t n, uint32_t block, int8_t *codes, fl
     const size_t nblocks = (n + block - 1) / block;
     const size_t need = (nblocks + kGroupsPerBlock - 1) / kGroupsPerBlock;
     const unsigned grid = (unsigned)(need < ZPP_QUANT_MAX_GRID ? need : ZPP_QUANT_MAX_GRID);
-    if (COPY && !on_lines)
+    if (COPY && !on_lines && quant_copy_runs(block, n))
         hipLaunchKernelGGL((quant_grp_kernel<G, S, COPY, COPY>), dim3(grid), dim3(kQuantThreads),
                            0, stream, src, n, block, codes, scales, copy);
     else

@@ -29,8 +29,9 @@ bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 //     (at 32 bytes, its state at 64: Adam 52 M 290 / 264), but that receive
 //     step at 1 M, whose grid fits the GPU at once, 7.5 / 7.0;
 //   int8 codes at 64 bytes: the fused step 13 M 71.5 / 73.8, the refresh with
-//     its quantization 4 M 4.49 / 4.82 (at 32 bytes, bf16 at 64: the fused
-//     step 210 M 1225 / 1155);
+//     its quantization 4 M 4.49 / 4.82 (at 32 bytes, bf16 at 64: the fused step
+//     210 M 1225 / 1155); with blocks that are not powers of two the other way,
+//     576 at 210 M 183 / 172;
 //   the reduced fp32 gradient at 64 bytes: 52 M 69.2 / 71.1, at 32 70.4 / 71.2;
 //   a bf16 copy alone at 64 bytes is the other way: 52 M 35.5 / 34.1.
 bool start_at(size_t line, std::initializer_list<const void *> arrays) {
@@ -268,7 +269,8 @@ ZPP_API zpp_status zpp_refresh_quantize_i8(uint16_t *secondary_bf16, const uint1
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines = start_at(128, {secondary_bf16}) && start_at(64, {codes});
+        const bool pow2 = (block & (block - 1)) == 0;
+        const bool lines = start_at(128, {secondary_bf16}) && start_at(pow2 ? 64 : 128, {codes});
         const hipError_t e =
             zpp::launch_quantize_copy(src_bf16, n, block, codes, scales, secondary_bf16, lines,
                                       stream);

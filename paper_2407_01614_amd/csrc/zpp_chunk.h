@@ -58,6 +58,20 @@ constexpr size_t xcd_grouped(size_t w, size_t grid, size_t R) {
     return (run + 1) * 8 * R <= grid ? run * 8 * R + (r % 8) * R + r / 8 : w;
 }
 
+// Whether the refresh with its quantization, its outputs off their lines, runs
+// its workgroups per XCD.  With powers of two up to 512 it gains at every
+// length (256 at 4 M, 8 elements into lines: 4.8 us, 5.1 in plain order; 131 M
+// off by one 116, 123).  Larger blocks make tiles of 4096 elements and more,
+// whose few shared lines don't pay for holding whole arrays apart by XCD (4096
+// at 52 M: 56.5 us in runs, 52.3 plain).  Lane groups of other blocks gain over
+// long arrays alone (576 at 4 M / 52 M / 210 M: 6.4 / 47.1 / 173 us in runs,
+// 6.0 / 48.6 / 187 plain), and from 1024 on nothing (4032 at 52 M 55, 52.5).
+inline bool quant_copy_runs(uint32_t block, size_t n) {
+    if ((block & (block - 1)) == 0)
+        return block <= 512;
+    return block < 1024 && n >= ((size_t)32 << 20);
+}
+
 // Residency cap.  The streaming kernels that keep many HBM streams open at
 // once (the optimizer step: four arrays read, four written) run faster with
 // fewer workgroups resident per CU than the hardware would otherwise place:

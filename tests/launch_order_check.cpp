@@ -155,6 +155,10 @@ void check() {
            zpp_refresh_quantize_i8(se, (const uint16_t *)g, N, 256, c, sc, nullptr, nullptr,
                                    nullptr),
            on(kSecondary, 128) && on(kCodes, 64));
+    expect("refresh and quantize in blocks of 192",
+           zpp_refresh_quantize_i8(se, (const uint16_t *)g, N, 192, c, sc, nullptr, nullptr,
+                                   nullptr),
+           on(kSecondary, 128) && on(kCodes, 128));
     expect("reduce",
            zpp_dequant_reduce_i4(xl, xsl, 1, N, 256, 1.0f, out, nullptr, nullptr, 0, nullptr),
            on(kOut, 32));

@@ -240,6 +240,31 @@ def test_alignments(zpp, n, block, interleaved):
             assert np.array_equal(got[name], r), (name, offset)
 
 
+@pytest.mark.parametrize("block", [192, 576, 960, 1088])
+def test_refresh_quantize_long_ranges_off_lines(zpp, block):
+    """The refresh with its quantization over ranges off their lines, around
+    the length from which lane groups run per XCD (a run is 1024 workgroups of
+    4 to 16 blocks): what the call gives for arrays on lines."""
+    limit = 32 << 20
+    gen = torch.Generator(device="cuda").manual_seed(block)
+    src = torch.empty(limit + 2051, device="cuda").normal_(0, 0.02, generator=gen).bfloat16()
+    for n in (limit - 1, limit, limit + 2051):
+        nb = -(-n // block)
+        got = []
+        for offset in (0, 3, 8):
+            x = Buf(n, torch.bfloat16, offset)
+            x.t.copy_(src[:n])
+            out = [Buf(n, torch.bfloat16, offset), Buf(n, torch.int8, offset),
+                   Buf(nb, torch.float32)]
+            zpp.refresh_quantize_i8(out[0].t, x.t, out[1].t, out[2].t, block=block)
+            [b.bits() for b in out]
+            got.append([b.raw[b.lo:b.end] for b in out])
+        assert torch.equal(got[0][0], src[:n].view(torch.uint8)), n
+        for other in got[1:]:
+            for a, b in zip(got[0], other):
+                assert torch.equal(a, b), n
+
+
 @pytest.mark.parametrize("sources", [0, 16], ids=["gradient", "receive"])
 @pytest.mark.parametrize("block", [192, 320, 832, 1024, 1280, 1344, 2048, 4096])
 def test_fused_block_routes(zpp, block, sources):

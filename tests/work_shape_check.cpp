@@ -150,6 +150,25 @@ static long check_residency() {
     return bad;
 }
 
+// Runs per XCD of the refresh with its quantization: where they measure faster.
+static long check_quant_copy_runs() {
+    const struct {
+        uint32_t block;
+        size_t n;
+        bool runs;
+    } rule[] = {{64, 1, true},          {256, 4u << 20, true},   {512, 200u << 20, true},
+                {1024, 4u << 20, false}, {4096, 50u << 20, false}, {192, 4u << 20, false},
+                {576, 4u << 20, false},  {576, 32u << 20, true},  {960, (32u << 20) - 1, false},
+                {1088, 200u << 20, false}, {4032, 50u << 20, false}};
+    long bad = 0;
+    for (const auto &r : rule)
+        if (zpp::quant_copy_runs(r.block, r.n) != r.runs) {
+            printf("runs of the copy: block %u n %zu\n", r.block, r.n);
+            ++bad;
+        }
+    return bad;
+}
+
 int main() {
     double worst_i8 = 1.0, worst_i8c = 1.0, worst_i4 = 1.0;
     long bad = 0;
@@ -161,6 +180,7 @@ int main() {
     bad += check_groups(4, 75, 3, 4, "int4", worst_i4);
     bad += check_xcd_grouped();
     bad += check_residency();
+    bad += check_quant_copy_runs();
     printf("worst fill: int8 %.4f, int8+copy %.4f, int4 %.4f\n", worst_i8, worst_i8c, worst_i4);
     if (bad) {
         printf("%ld failures\n", bad);

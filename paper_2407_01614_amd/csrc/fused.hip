@@ -266,6 +266,13 @@ void launch_wide(const FusedArgs &a, const GS &gs, uint32_t block, bool on_lines
     });
 }
 
+template <class GS> constexpr Gradient gradient();
+template <> constexpr Gradient gradient<F32Grad>() { return Gradient::kF32; }
+template <> constexpr Gradient gradient<I4Grad>() { return Gradient::kCopies; }
+template <> constexpr Gradient gradient<I4GradIl>() { return Gradient::kInterleaved; }
+inline uint32_t num_sources(const F32Grad &) { return 0; }
+template <class GS> uint32_t num_sources(const GS &gs) { return gs.num_src; }
+
 // Workgroups per CU for each gradient source.
 template <class GS> constexpr int fused_residency();
 template <> constexpr int fused_residency<F32Grad>() { return ZPP_FUSED_RESIDENCY; }
@@ -289,12 +296,9 @@ void launch_fused_chunks(const FusedArgs &a, const GS &gs, int residency, bool o
 
 template <int B, bool QUANT = true, class GS>
 void launch_fused_b(const FusedArgs &a, const GS &gs, bool on_lines, hipStream_t stream) {
-    // the step with its copies alone, ahead of the quantizer, keeps fewer: 9
-    // (Llama-2-7B partition, both kernels: 1138 us with 9, 1146 with 10, 1154
-    // with 11, 1153 with 8; with 8 copies from the interleaved buffer at 50 M
-    // 305 with 9, 310 with 11, 315 with 8), from separate arrays as many as
-    // with the quantization (291 us with 12, 299 with 9)
-    int residency = QUANT || std::is_same_v<GS, I4Grad> ? fused_residency<GS>() : 9;
+    int residency = fused_residency<GS>();
+    if constexpr (!QUANT)
+        residency = copies_residency(gradient<GS>(), num_sources(gs), a.n, residency);
     if constexpr (!std::is_same_v<GS, F32Grad>) {
         if (gs.num_src >= kManySources)
             residency = 0;  // left to the hardware (zpp_i4grad.h)

@@ -169,6 +169,28 @@ static long check_quant_copy_runs() {
     return bad;
 }
 
+// Residency of the step with its copies ahead of the quantizer.
+static long check_copies_residency() {
+    using zpp::Gradient;
+    const size_t M = 1 << 20;
+    const struct {
+        Gradient from;
+        uint32_t num_src;
+        size_t n;
+        int want;
+    } rule[] = {{Gradient::kF32, 0, 20 * M, 9},          {Gradient::kCopies, 8, 200 * M, 14},
+                {Gradient::kInterleaved, 1, 20 * M, 14}, {Gradient::kInterleaved, 1, 100 * M, 14},
+                {Gradient::kInterleaved, 4, 50 * M, 14}, {Gradient::kInterleaved, 8, 20 * M, 14},
+                {Gradient::kInterleaved, 8, 32 * M, 9},  {Gradient::kInterleaved, 12, 50 * M, 9}};
+    long bad = 0;
+    for (const auto &r : rule)
+        if (zpp::copies_residency(r.from, r.num_src, r.n, 14) != r.want) {
+            printf("residency of the copies: %d %u %zu\n", (int)r.from, r.num_src, r.n);
+            ++bad;
+        }
+    return bad;
+}
+
 int main() {
     double worst_i8 = 1.0, worst_i8c = 1.0, worst_i4 = 1.0;
     long bad = 0;
@@ -181,6 +203,7 @@ int main() {
     bad += check_xcd_grouped();
     bad += check_residency();
     bad += check_quant_copy_runs();
+    bad += check_copies_residency();
     printf("worst fill: int8 %.4f, int8+copy %.4f, int4 %.4f\n", worst_i8, worst_i8c, worst_i4);
     if (bad) {
         printf("%ld failures\n", bad);

@@ -300,9 +300,9 @@ void launch_fused_b(const FusedArgs &a, const GS &gs, bool on_lines, hipStream_t
     if constexpr (!QUANT)
         residency = copies_residency(gradient<GS>(), num_sources(gs), a.n, residency);
     if constexpr (!std::is_same_v<GS, F32Grad>) {
-        if (gs.num_src >= kManySources)
-            residency = 0;  // left to the hardware (zpp_i4grad.h)
-        if (many_sources(gs.num_src, gs.block))
+        residency = receive_residency(gradient<GS>(), gs.num_src, gs.block.block, a.n, QUANT,
+                                      residency);
+        if (many_sources(gs.num_src, gs.block.block))
             return launch_fused_chunks<B, QUANT, true>(a, gs, residency, on_lines, stream);
     }
     launch_fused_chunks<B, QUANT, false>(a, gs, residency, on_lines, stream);
@@ -320,7 +320,7 @@ hipError_t launch_fused_gs(const FusedArgs &a, const GS &gs, uint32_t block, boo
         if (wide_block<GS>(block, a.n)) {
             if constexpr (!std::is_same_v<GS, F32Grad>) {
                 // a wave's 256 elements lie in one int4 block
-                if (block % 256 == 0 && many_sources(gs.num_src, gs.block)) {
+                if (block % 256 == 0 && many_sources(gs.num_src, gs.block.block)) {
                     launch_wide<true>(a, gs, block, on_lines, stream);
                     return hipGetLastError();
                 }

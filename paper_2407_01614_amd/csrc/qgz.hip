@@ -328,7 +328,7 @@ void launch_reduce_gs(const GS &gs, size_t n, float *out, bool on_lines, hipStre
 // the length that gives every CU its 32 waves.  Fewer sources keep two.
 template <class GS>
 hipError_t launch_reduce(const GS &gs, size_t n, float *out, bool on_lines, hipStream_t stream) {
-    if (!many_sources(gs.num_src, gs.block))
+    if (!many_sources(gs.num_src, gs.block.block))
         launch_reduce_gs<2, false>(gs, n, out, on_lines, stream);
     else if (n >= (size_t)512 * 32 * kCUs)
         launch_reduce_gs<2, true>(gs, n, out, on_lines, stream);

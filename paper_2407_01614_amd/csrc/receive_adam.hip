@@ -28,6 +28,8 @@
 // (I4GradIl, zpp_i4grad.h: a wave's codes of all sources within one
 // contiguous run): 938 us with ZPP_RECV_IL_RESIDENCY = 11 (14: 949, 16: 955,
 // uncapped 978) against 981 us from separate arrays in the same run.
+#include <type_traits>
+
 #include "zpp_adam.h"
 #include "zpp_chunk.h"
 #include "zpp_device.h"
@@ -100,9 +102,10 @@ void launch_recv_tiles(const RecvArgs<GS> &a, int residency, bool on_lines, hipS
 
 template <class GS>
 hipError_t launch_recv(const RecvArgs<GS> &a, int residency, bool on_lines, hipStream_t stream) {
-    if (a.src.num_src >= kManySources)
-        residency = 0;  // left to the hardware (zpp_i4grad.h)
-    if (many_sources(a.src.num_src, a.src.block))
+    constexpr Gradient from =
+        std::is_same_v<GS, I4Grad> ? Gradient::kCopies : Gradient::kInterleaved;
+    residency = receive_residency(from, a.src.num_src, a.src.block.block, a.n, true, residency);
+    if (many_sources(a.src.num_src, a.src.block.block))
         launch_recv_tiles<true>(a, residency, on_lines, stream);
     else
         launch_recv_tiles<false>(a, residency, on_lines, stream);

@@ -102,6 +102,20 @@ inline size_t launch_lds(int workgroups, size_t wgs) {
     return wgs <= 32 * kCUs ? 0 : residency_lds(workgroups);
 }
 
+// Where a step's gradient comes from: the fp32 array, the int4 copies as
+// separate arrays, or those in one interleaved buffer.
+enum class Gradient { kF32, kCopies, kInterleaved };
+
+// The many-source form (zpp_i4grad.h): from this many sources on, with int4
+// blocks that hold whole tiles.  With 12 it would gain at most 2% (receive step
+// 78.5 against 78.9 us at 13 M elements) and the dequant-reduce would lose (57
+// against 37.5 us at 20 M: its last, partial batch repeats loads); with 8 it
+// loses everywhere (67.2 against 66.0).
+constexpr uint32_t kManySources = 16;
+constexpr bool many_sources(uint32_t num_src, uint32_t grad_block) {
+    return num_src >= kManySources && grad_block % 256 == 0;
+}
+
 // Workgroups per CU of the step with its copies alone, ahead of the quantizer
 // over the primary it wrote; with_quant is the cap of the kernel that quantizes
 // too.  The fp32 gradient keeps 9 (Llama-2-7B partition, both kernels: 1138 us
@@ -110,13 +124,38 @@ inline size_t launch_lds(int workgroups, size_t wgs) {
 // buffer but for 8 copies or more over long arrays (14 / 9: 1 copy at 20 M 110.5
 // / 115, 50 M 273 / 280; 4 copies at 20 M 117 / 120; 8 at 20 M 123.5 / 125.5,
 // 50 M 310 / 304, 105 M 606 / 596).
-enum class Gradient { kF32, kCopies, kInterleaved };
 constexpr int copies_residency(Gradient from, uint32_t num_src, size_t n, int with_quant) {
     if (from == Gradient::kF32)
         return 9;
-    if (from == Gradient::kInterleaved && num_src >= 8 && n >= ((size_t)32 << 20))
+    if (from == Gradient::kInterleaved && num_src >= 8 && num_src < kManySources &&
+        n >= ((size_t)32 << 20))
         return 9;
     return with_quant;
+}
+
+// Workgroups per CU of a step that receives num_src int4 copies; few is the
+// kernel's cap for few of them.  With many sources a short array waits on the
+// latency of their loads and takes every wave the hardware holds (64
+// interleaved sources at 4.7 M, receive step: 51.3 us uncapped, 53.1 capped); a
+// long one streams, and from the interleaved buffer keeps the cap (uncapped /
+// capped, 16 sources at 50 M: blocks of 256 302.6 / 285, of 64 349 / 332, of
+// 320 359 / 343; 64 sources at 8 M, blocks of 64 and 320: capped better and
+// worse by 3%).  Separate arrays in the many-source form
+// stream best with 16 (16 sources, blocks of 1024 at 50 M: 319 uncapped, 308,
+// 325 with the cap of few sources); in other blocks every cap loses (32
+// sources, blocks of 64 at 50 M 391 / 435).  The step with its copies alone
+// (quant false) keeps 11 in the many-source form of the interleaved buffer (24
+// sources at 50 M, both kernels: 385 uncapped, 393 with 9, 365).
+constexpr int receive_residency(Gradient from, uint32_t num_src, uint32_t grad_block, size_t n,
+                                bool quant, int few) {
+    if (num_src < kManySources)
+        return few;
+    const bool many = many_sources(num_src, grad_block);
+    if (from == Gradient::kCopies)
+        return many && n >= ((size_t)12 << 20) ? 16 : 0;
+    if (n < ((size_t)(grad_block < 256 ? 8 : 12) << 20))
+        return 0;
+    return many && !quant ? 11 : few;
 }
 
 }  // namespace zpp

@@ -182,10 +182,11 @@ struct F32Grad {
 // streams.  So lane q holds source q's scale of the block (one load for up to
 // 64 sources in place of one per source), each source's turn reads it from
 // that lane into a scalar register, up to 32 sources' codes are in flight
-// together, and residency is left to the hardware.  64 sources at 4,956,160
-// elements, receive step: separate arrays 73.9 -> 60.6 us, interleaved 66.9 ->
-// 52.9 (43.6 at the copy rate); the dequant-reduce 80.5 -> 42.2 and 41.9 ->
-// 38.2; 16 sources at 13 M: receive pass 101 -> 87 (separate), 87.5 -> 83.
+// together, and short arrays leave residency to the hardware
+// (receive_residency in zpp_chunk.h).  64 sources at 4,956,160 elements, receive
+// step: separate arrays 73.9 -> 60.6 us, interleaved 66.9 -> 52.9 (43.6 at the
+// copy rate); the dequant-reduce 80.5 -> 42.2 and 41.9 -> 38.2; 16 sources at
+// 13 M: receive pass 101 -> 87 (separate), 87.5 -> 83.
 // Codes of two groups by one 4-byte load, halves swapped between lane pairs,
 // was no faster (62.8 and 59.1 us at 64 sources), nor was a cheaper decode
 // (v_cvt_off_f32_i4 with the scale times 16).
@@ -219,12 +220,6 @@ __device__ __forceinline__ TileCodesIl tile_codes(const I4GradIl &s, size_t base
                                                   uint32_t lane) {
     return {s.codes + il_code_byte(s, base, k, 0), s.block.block / 2, lane};
 }
-
-// From this many sources on.  With 12 the form below would gain at most 2%
-// (receive step 78.5 against 78.9 us at 13 M elements) and the dequant-reduce
-// would lose (57 against 37.5 us at 20 M: its last, partial batch repeats
-// loads); with 8 it loses everywhere (67.2 against 66.0).
-constexpr uint32_t kManySources = 16;
 
 // N sources from q on, all loads in flight before the sums.  Not ALL: the
 // first `count` of them; the loads past the last source repeat it.
@@ -308,11 +303,6 @@ __device__ __forceinline__ void grad_tile(f32x4 (&r)[G], const GS &s, size_t bas
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             r[g][e] = i4grad_scaled(r[g][e], s.scale_out);
-}
-
-// Whether a launch takes the many-source form.
-inline bool many_sources(uint32_t num_src, const BlockDiv &block) {
-    return num_src >= kManySources && block.block % 256 == 0;
 }
 
 }  // namespace zpp

@@ -169,6 +169,42 @@ static long check_quant_copy_runs() {
     return bad;
 }
 
+// Residency with many int4 sources.
+static long check_receive_residency() {
+    using zpp::Gradient;
+    const size_t M = 1 << 20;
+    const struct {
+        Gradient from;
+        uint32_t num_src, grad_block;
+        size_t n;
+        bool quant;
+        int want;
+    } rule[] = {
+        {Gradient::kInterleaved, 15, 256, 50 * M, true, 13},
+        {Gradient::kInterleaved, 16, 256, 4 * M, true, 0},
+        {Gradient::kInterleaved, 16, 256, 12 * M, true, 13},
+        {Gradient::kInterleaved, 64, 1024, 20 * M, true, 13},
+        {Gradient::kInterleaved, 24, 256, 50 * M, false, 11},
+        {Gradient::kInterleaved, 16, 64, 4 * M, true, 0},
+        {Gradient::kInterleaved, 16, 64, 8 * M, true, 13},
+        {Gradient::kInterleaved, 32, 320, 8 * M, true, 0},
+        {Gradient::kInterleaved, 32, 320, 50 * M, false, 13},
+        {Gradient::kCopies, 15, 256, 50 * M, true, 13},
+        {Gradient::kCopies, 16, 256, 12 * M - 1, true, 0},
+        {Gradient::kCopies, 16, 256, 12 * M, true, 16},
+        {Gradient::kCopies, 32, 64, 50 * M, true, 0},
+        {Gradient::kCopies, 32, 1024, 50 * M, false, 16},
+    };
+    long bad = 0;
+    for (const auto &r : rule)
+        if (zpp::receive_residency(r.from, r.num_src, r.grad_block, r.n, r.quant, 13) != r.want) {
+            printf("residency of a receive: %d %u %u %zu\n", (int)r.from, r.num_src, r.grad_block,
+                   r.n);
+            ++bad;
+        }
+    return bad;
+}
+
 // Residency of the step with its copies ahead of the quantizer.
 static long check_copies_residency() {
     using zpp::Gradient;
@@ -204,6 +240,7 @@ int main() {
     bad += check_residency();
     bad += check_quant_copy_runs();
     bad += check_copies_residency();
+    bad += check_receive_residency();
     printf("worst fill: int8 %.4f, int8+copy %.4f, int4 %.4f\n", worst_i8, worst_i8c, worst_i4);
     if (bad) {
         printf("%ld failures\n", bad);

@@ -154,11 +154,11 @@ ZPP_API zpp_status zpp_refresh_quantize_i8(uint16_t *secondary_bf16, const uint1
  * weights).  Results are bit for bit those of the three separate calls
  * (zpp_adam_partition_step into primary_bf16, zpp_refresh_secondary from it,
  * zpp_quantize_blockwise_i8 of it), at 33.016 instead of 37.016 bytes of HBM
- * traffic per element for block 256.  Blocks of 64, 128, 256, 512 and 832 to
- * 1280 take one pass, and so does any other up to 8 M elements; beyond, it
- * takes two kernels in stream order, the step with its copies and then the
- * quantization of primary_bf16 (2 more bytes read per element, which
- * measured faster than one pass for such blocks).
+ * traffic per element for block 256.  Blocks of 64, 128, 256 and 512 take one
+ * pass, blocks of 1024 to 1152 up to 104 M elements, of 832 to 1280 up to 24 M
+ * and any other up to 8 M; beyond, it takes two kernels in stream order, the
+ * step with its copies and then the quantization of primary_bf16 (2 more
+ * bytes read per element, which measured faster than one pass there).
  * master, exp_avg, exp_avg_sq: float[n] in place; grad: float[n];
  * primary_bf16: uint16_t[n] out; secondary_bf16: uint16_t[n] out, or NULL to
  * keep no bf16 secondary copy; codes: int8_t[n] out; scales:
@@ -288,8 +288,10 @@ ZPP_API zpp_status zpp_qgz_receive_adam_step(float *master, float *exp_avg, floa
  * zpp_qgz_receive_adam_step into primary_bf16, zpp_refresh_secondary from
  * it and zpp_quantize_blockwise_i8 of it, at 29 B + num_src * (0.5 B +
  * 4/grad_block B) + 4/block B of HBM traffic per element instead of
- * 33 B + num_src * (0.5 B + 4/grad_block B) + 4/block B.  Which int8 blocks
- * take one pass is as for zpp_adam_step_refresh_quantize.
+ * 33 B + num_src * (0.5 B + 4/grad_block B) + 4/block B.  Int8 blocks
+ * of 64, 128, 256, 512, 1024 and 1280 take one pass at any length, others up
+ * to a length that depends on the number of copies and their layout (8 M
+ * elements for most), two kernels beyond.
  * master, exp_avg, exp_avg_sq: float[n] in place.  src_codes, src_scales,
  * num_src, scale_out: as for zpp_qgz_receive_adam_step, with int4 blocks of
  * grad_block (a multiple of 64 in [64, 4096]).  primary_bf16: uint16_t[n] out;

@@ -67,6 +67,13 @@ struct FusedArgs {
     AdamConsts c;
 };
 
+template <class GS> constexpr Gradient gradient();
+template <> constexpr Gradient gradient<F32Grad>() { return Gradient::kF32; }
+template <> constexpr Gradient gradient<I4Grad>() { return Gradient::kCopies; }
+template <> constexpr Gradient gradient<I4GradIl>() { return Gradient::kInterleaved; }
+inline uint32_t num_sources(const F32Grad &) { return 0; }
+template <class GS> uint32_t num_sources(const GS &gs) { return gs.num_src; }
+
 // Runs of consecutive workgroups per XCD: grouped for the qgZ receive from
 // separate arrays (zpp_i4grad.h), plain otherwise.
 template <class GS> constexpr size_t fused_xcd_run() { return 0; }
@@ -214,33 +221,13 @@ __global__ __launch_bounds__(1024) void fused_wide_kernel(FusedArgs a, GS gs, ui
         fused_wide_block<ADAMW, false, MANY>(a, gs, k * B, blocks.tail, k);
 }
 
-// Where the one-block-per-workgroup form runs in place of the two kernels.
-// What it costs is that a workgroup's waves start together and cover up to 16
-// neighbouring tiles on one XCD, which streams a few percent slower over long
-// arrays than one-wave workgroups dealt out over the XCDs; what it saves is
-// the second launch and 2 bytes read per element.  All blocks gain up to about
-// 12 M elements (192 / 320 / 2048 / 4096 at 6 M: 39.0 / 38.0 / 39.0 / 40.4 ->
-// 37.8 / 36.5 / 36.4 / 37.5 us, at 1 M 9.8 / 10.1 / 12.0 / 14.1 -> 7.6 / 7.7 /
-// 6.7 / 6.8), and these lose at 45 M (320: 253 -> 258, 2048: 252 -> 258).
-// Blocks of 832 to 1280 (4 or 5 waves) gain for longer: 1024 at 45 M 250 ->
-// 236, 100 M 548 -> 520, but 150 M 839 -> 849 and 210 M 1145 -> 1160; with the
-// gradient from int4 copies, whose two kernels cost more, at every length
-// (1024 and 8 copies, 200 M: 1161 -> 1077).
-constexpr size_t kWideMost = (size_t)8 << 20;
-template <class GS>
-bool wide_block(uint32_t block, size_t n) {
-    if (block > 768 && block <= 1280)
-        return !std::is_same_v<GS, F32Grad> || n <= 16 * kWideMost;
-    return n <= kWideMost;
-}
-
 // Workgroups per CU: the step's three or four times four waves (1024 at 45 M:
 // 236 us with 3, 249 with 4, 256 left to the hardware; the receive at 50 M 278
 // / 271 / 279), but short launches and many sources are left to the hardware
 // (1024 at 1 M elements: 6.9 us against 7.6 with 3).
 template <class GS>
 int wide_residency(const GS &gs, size_t n) {
-    if (n <= kWideMost / 2)
+    if (n <= kWideShort / 2)
         return 0;
     if constexpr (std::is_same_v<GS, F32Grad>)
         return 3;
@@ -252,7 +239,7 @@ template <bool MANY, class GS>
 void launch_wide(const FusedArgs &a, const GS &gs, uint32_t block, bool on_lines,
                  hipStream_t stream) {
     const uint32_t threads = (block / 4 + kWave - 1) / kWave * kWave;
-    // beyond half of kWideMost a block of fewer waves would be capped too low
+    // beyond half of kWideShort a block of fewer waves would be capped too low
     const int per_cu = threads / kWave >= 4 ? wide_residency(gs, a.n) : 0;
     // the maxima have a granule of their own
     const size_t lds = per_cu ? residency_lds(per_cu) - kLdsGranule : 0;
@@ -265,13 +252,6 @@ void launch_wide(const FusedArgs &a, const GS &gs, uint32_t block, bool on_lines
                                lds, stream, a, gs, block, blocks);
     });
 }
-
-template <class GS> constexpr Gradient gradient();
-template <> constexpr Gradient gradient<F32Grad>() { return Gradient::kF32; }
-template <> constexpr Gradient gradient<I4Grad>() { return Gradient::kCopies; }
-template <> constexpr Gradient gradient<I4GradIl>() { return Gradient::kInterleaved; }
-inline uint32_t num_sources(const F32Grad &) { return 0; }
-template <class GS> uint32_t num_sources(const GS &gs) { return gs.num_src; }
 
 // Workgroups per CU for each gradient source.
 template <class GS> constexpr int fused_residency();
@@ -317,7 +297,7 @@ hipError_t launch_fused_gs(const FusedArgs &a, const GS &gs, uint32_t block, boo
     case 256: launch_fused_b<256>(a, gs, on_lines, stream); break;
     case 512: launch_fused_b<512>(a, gs, on_lines, stream); break;
     default: {
-        if (wide_block<GS>(block, a.n)) {
+        if (wide_block(gradient<GS>(), num_sources(gs), block, a.n)) {
             if constexpr (!std::is_same_v<GS, F32Grad>) {
                 // a wave's 256 elements lie in one int4 block
                 if (block % 256 == 0 && many_sources(gs.num_src, gs.block.block)) {

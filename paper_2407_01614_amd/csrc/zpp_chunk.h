@@ -116,6 +116,64 @@ constexpr bool many_sources(uint32_t num_src, uint32_t grad_block) {
     return num_src >= kManySources && grad_block % 256 == 0;
 }
 
+// Whether the fused step for a block other than 64, 128, 256 and 512 gives each
+// block a workgroup of its own (fused_wide_kernel) rather than two kernels, the
+// step with its copies and the quantizer.  What it costs is that a workgroup's
+// waves start together and cover up to 16 neighbouring tiles on one XCD, which
+// streams a few percent slower over long arrays than one-wave workgroups dealt
+// out over the XCDs; what it saves is the second launch and 2 bytes read per
+// element.  Measured against the two kernels, time over time:
+//   fp32 gradient: every block gains up to 12 M elements (192 / 320 / 2048 /
+//     4096 at 6 M .95 / .94 / .95 / .97, at 1 M .84 / .84 / .70 / .63) and
+//     these lose at 45 M (1.04 / 1.02 / 1.02 / 1.06).  Blocks of 4 or 5 waves
+//     gain for longer, by an amount that hangs on where the arrays lie and on
+//     the card (arrays allocated one by one, three layouts on two cards): 1024 /
+//     1088 / 1152 at 45 M .94 to 1.0 / .97 to 1.0 / .96 to .99, at 100 M .96 to
+//     .98 / .99 to 1.03 / 1.0 to 1.05, at 128 M up to 1.07; the others at 25 M
+//     832 1.0 to 1.03, 896 .98 to 1.01, 1280 .93 to .99, at 48 M up to 1.05 /
+//     1.02 / 1.04.
+//   int4 copies: a wave with idle lanes issues the loads of every source for
+//     them too, and in such blocks the form has no many-source variant.  Up to
+//     2 M elements it gains all the same below 32 sources (1 M, 16 interleaved
+//     sources, 192 / 832 / 1344: 1.01 / .94 / .99; 12: 1.00 / .92 / .95), and in
+//     blocks of 576 to 1344 from separate arrays with any number (32: .92 to
+//     1.0).  Beyond, from 16 sources, it loses (4 M, 16 interleaved sources 192
+//     / 832 / 1344: 1.13 / 1.01 / 1.01) but for those blocks from 16 to 31
+//     separate arrays (8 M: .96 to 1.0).  Blocks of one or two waves, with no
+//     neighbour to hide behind, lose sooner (8 M interleaved: 192 with 4 / 8
+//     sources 1.04 / 1.09, 320 and 448 with 8 1.04; separate: 192 with 8 1.02,
+//     320 .97).  Beyond 8 M, blocks of 832 to 1280: whole waves (1024 and 1280)
+//     gain at every length (.93 to 1.0), the others from separate arrays below 16
+//     sources too (.94 to 1.0), from the interleaved buffer with up to 4 sources
+//     up to 64 M (.95 to 1.01) and otherwise up to 16 M (.95 to 1.0; 8 sources
+//     at 52 M 1.03 to 1.05).  Blocks of 4096 and 16 sources lose from 8 M (1.0
+//     to 1.05).
+constexpr size_t kWideShort = (size_t)8 << 20;
+constexpr bool wide_block(Gradient from, uint32_t num_src, uint32_t block, size_t n) {
+    const bool four_waves = block > 768 && block <= 1280;
+    if (from == Gradient::kF32) {
+        if (!four_waves)
+            return n <= kWideShort;
+        return n <= (block >= 1024 && block <= 1152 ? 13 : 3) * kWideShort;
+    }
+    if (block % 256 == 0) {
+        if (block > 2048 && num_src >= kManySources)
+            return n <= kWideShort / 2;
+        return four_waves || n <= kWideShort;
+    }
+    const bool medium = block > 512 && block <= 1344;
+    if (n <= kWideShort / 4)
+        return num_src < 2 * kManySources || (from == Gradient::kCopies && medium);
+    if (num_src >= kManySources)
+        return from == Gradient::kCopies && medium && num_src < 2 * kManySources &&
+               n <= kWideShort;
+    if (from == Gradient::kCopies)
+        return four_waves || (n <= kWideShort && (block > 256 || num_src < 8));
+    if (four_waves)
+        return n <= (num_src <= 4 ? 8 : 2) * kWideShort;
+    return n <= kWideShort && num_src < (block > 512 ? kManySources : block > 256 ? 8u : 4u);
+}
+
 // Workgroups per CU of the step with its copies alone, ahead of the quantizer
 // over the primary it wrote; with_quant is the cap of the kernel that quantizes
 // too.  The fp32 gradient keeps 9 (Llama-2-7B partition, both kernels: 1138 us

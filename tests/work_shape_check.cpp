@@ -169,6 +169,50 @@ static long check_quant_copy_runs() {
     return bad;
 }
 
+// Which fused steps give each block a workgroup of its own.
+static long check_wide_block() {
+    using zpp::Gradient;
+    const size_t M = 1 << 20;
+    const Gradient f32 = Gradient::kF32, sep = Gradient::kCopies, il = Gradient::kInterleaved;
+    const struct {
+        Gradient from;
+        uint32_t num_src, block;
+        size_t n;
+        bool wide;
+    } rule[] = {
+        {f32, 0, 192, 8 * M, true},     {f32, 0, 192, 8 * M + 1, false},
+        {f32, 0, 4096, M, true},        {f32, 0, 2048, 45 * M, false},
+        {f32, 0, 832, 24 * M, true},    {f32, 0, 832, 32 * M, false},
+        {f32, 0, 1280, 45 * M, false},  {f32, 0, 1024, 100 * M, true},
+        {f32, 0, 1024, 128 * M, false}, {f32, 0, 1152, 100 * M, true},
+        {sep, 8, 1024, 200 * M, true},  {il, 8, 1024, 200 * M, true},
+        {il, 64, 1280, 20 * M, true},   {il, 32, 2048, 8 * M, true},
+        {il, 16, 4096, 8 * M, false},   {sep, 64, 4096, 4 * M, true},
+        {il, 15, 4096, 8 * M, true},    {il, 16, 192, M, true},
+        {il, 16, 192, 6 * M, false},    {il, 31, 4032, 2 * M, true},
+        {il, 32, 832, M, false},        {sep, 64, 832, M, true},
+        {sep, 64, 4032, M, false},      {sep, 16, 832, 8 * M, true},
+        {sep, 32, 832, 4 * M, false},   {sep, 16, 4032, 4 * M, false},
+        {il, 64, 320, M, false},        {sep, 15, 832, 100 * M, true},
+        {il, 8, 192, 2 * M, true},      {sep, 12, 192, 2 * M, true},
+        {sep, 7, 192, 8 * M, true},     {sep, 8, 192, 6 * M, false},
+        {sep, 15, 320, 8 * M, true},    {sep, 8, 320, 20 * M, false},
+        {il, 3, 192, 8 * M, true},      {il, 4, 192, 6 * M, false},
+        {il, 7, 320, 8 * M, true},      {il, 8, 448, 8 * M, false},
+        {il, 15, 576, 8 * M, true},     {il, 8, 832, 16 * M, true},
+        {il, 8, 832, 20 * M, false},    {il, 4, 1088, 52 * M, true},
+        {il, 4, 1088, 100 * M, false},
+    };
+    long bad = 0;
+    for (const auto &r : rule)
+        if (zpp::wide_block(r.from, r.num_src, r.block, r.n) != r.wide) {
+            printf("a workgroup per block: %d %u block %u n %zu\n", (int)r.from, r.num_src, r.block,
+                   r.n);
+            ++bad;
+        }
+    return bad;
+}
+
 // Residency with many int4 sources.
 static long check_receive_residency() {
     using zpp::Gradient;
@@ -240,6 +284,7 @@ int main() {
     bad += check_residency();
     bad += check_quant_copy_runs();
     bad += check_copies_residency();
+    bad += check_wide_block();
     bad += check_receive_residency();
     printf("worst fill: int8 %.4f, int8+copy %.4f, int4 %.4f\n", worst_i8, worst_i8c, worst_i4);
     if (bad) {

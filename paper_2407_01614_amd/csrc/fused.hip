@@ -278,7 +278,7 @@ template <int B, bool QUANT = true, class GS>
 void launch_fused_b(const FusedArgs &a, const GS &gs, bool on_lines, hipStream_t stream) {
     int residency = fused_residency<GS>();
     if constexpr (!QUANT)
-        residency = copies_residency(gradient<GS>(), num_sources(gs), a.n, residency);
+        residency = copies_residency(gradient<GS>(), residency);
     if constexpr (!std::is_same_v<GS, F32Grad>) {
         residency = receive_residency(gradient<GS>(), gs.num_src, gs.block.block, a.n, QUANT,
                                       residency);

@@ -177,18 +177,13 @@ constexpr bool wide_block(Gradient from, uint32_t num_src, uint32_t block, size_
 // Workgroups per CU of the step with its copies alone, ahead of the quantizer
 // over the primary it wrote; with_quant is the cap of the kernel that quantizes
 // too.  The fp32 gradient keeps 9 (Llama-2-7B partition, both kernels: 1138 us
-// with 9, 1146 with 10, 1154 with 11, 1153 with 8), separate copies as many as
-// with the quantization (291 us with 12, 299 with 9).  So does the interleaved
-// buffer but for 8 copies or more over long arrays (14 / 9: 1 copy at 20 M 110.5
-// / 115, 50 M 273 / 280; 4 copies at 20 M 117 / 120; 8 at 20 M 123.5 / 125.5,
-// 50 M 310 / 304, 105 M 606 / 596).
-constexpr int copies_residency(Gradient from, uint32_t num_src, size_t n, int with_quant) {
-    if (from == Gradient::kF32)
-        return 9;
-    if (from == Gradient::kInterleaved && num_src >= 8 && num_src < kManySources &&
-        n >= ((size_t)32 << 20))
-        return 9;
-    return with_quant;
+// with 9, 1146 with 10, 1154 with 11, 1153 with 8).  int4 copies keep as many as
+// with the quantization: separate ones 291 us with 12, 299 with 9; interleaved
+// ones, 14 against 9, 1 copy at 50 M 273 / 280, 4 at 20 M 117 / 120, 9 to 15 from
+// 33 M on 1.0 / 1.1 times (12 at 100 M 633 / 706).  Eight at 100 M went either way
+// by the card (572 / 597, 606 / 596).
+constexpr int copies_residency(Gradient from, int with_quant) {
+    return from == Gradient::kF32 ? 9 : with_quant;
 }
 
 // Workgroups per CU of a step that receives num_src int4 copies; few is the

@@ -252,23 +252,12 @@ static long check_receive_residency() {
 // Residency of the step with its copies ahead of the quantizer.
 static long check_copies_residency() {
     using zpp::Gradient;
-    const size_t M = 1 << 20;
-    const struct {
-        Gradient from;
-        uint32_t num_src;
-        size_t n;
-        int want;
-    } rule[] = {{Gradient::kF32, 0, 20 * M, 9},          {Gradient::kCopies, 8, 200 * M, 14},
-                {Gradient::kInterleaved, 1, 20 * M, 14}, {Gradient::kInterleaved, 1, 100 * M, 14},
-                {Gradient::kInterleaved, 4, 50 * M, 14}, {Gradient::kInterleaved, 8, 20 * M, 14},
-                {Gradient::kInterleaved, 8, 32 * M, 9},  {Gradient::kInterleaved, 12, 50 * M, 9}};
-    long bad = 0;
-    for (const auto &r : rule)
-        if (zpp::copies_residency(r.from, r.num_src, r.n, 14) != r.want) {
-            printf("residency of the copies: %d %u %zu\n", (int)r.from, r.num_src, r.n);
-            ++bad;
-        }
-    return bad;
+    if (zpp::copies_residency(Gradient::kF32, 11) == 9 &&
+        zpp::copies_residency(Gradient::kCopies, 12) == 12 &&
+        zpp::copies_residency(Gradient::kInterleaved, 14) == 14)
+        return 0;
+    printf("residency of the copies\n");
+    return 1;
 }
 
 int main() {

@@ -367,10 +367,7 @@ void launch_quant_i4_u(const float *src, size_t n, uint8_t *codes, float *scales
 // blocks of 512 / 1024 / 4096 and 25.9 M elements, one 19.9 / 20.2 / 21.4;
 // 203 M: 151 / 152 / 219, and 143 / 148 / 162).  Up to 256 four stream best
 // over long arrays (203 M: 147 us, 160 with two), two put a short one on more
-// waves (1 M: 3.3 us, 3.9 with four; 8 M 9.0, 13 M 12.9 and 12.4).  Blocks of
-// 64 and 128 in a sender's slots, whose codes are runs of 32 and 64 bytes, take
-// two at every length (203 M: 64 286 -> 251 us, 128 187 -> 169).
-constexpr size_t kTwoTilesMost = (size_t)8 << 20;
+// waves (i4_two_tiles, zpp_chunk.h).
 template <int B>
 void launch_quant_i4_b(const float *src, size_t n, uint8_t *codes, float *scales,
                        uint32_t q_src, uint32_t num_src, hipStream_t stream) {
@@ -380,7 +377,7 @@ void launch_quant_i4_b(const float *src, size_t n, uint8_t *codes, float *scales
     }
     if constexpr (B > 256)
         launch_quant_i4_u<B, 1>(src, n, codes, scales, q_src, num_src, stream);
-    else if (n <= kTwoTilesMost || (B <= 128 && num_src > 1))
+    else if (i4_two_tiles(B, num_src, n))
         launch_quant_i4_u<B, 2>(src, n, codes, scales, q_src, num_src, stream);
     else
         launch_quant_i4_u<B, 4>(src, n, codes, scales, q_src, num_src, stream);

@@ -72,6 +72,24 @@ inline bool quant_copy_runs(uint32_t block, size_t n) {
     return block < 1024 && n >= ((size_t)32 << 20);
 }
 
+// Whether a wave of the int4 quantizer keeps two tiles in flight rather than
+// four, for blocks up to 256.  Two put a short array on more waves (1 M: 3.3 us,
+// 3.9 with four; 8 M 9.0, 13 M 12.9 and 12.4).  Blocks of 64 and 128 in a
+// sender's slots, whose codes are runs of 32 and 64 bytes, take two over long
+// arrays again (203 M, 8 senders: 64 286 -> 251 us, 128 187 -> 169), blocks of
+// 128 the later the fewer senders share the buffer (two's time over four's: 64
+// with 2 senders at 13 M 1.03, with 8 at 20 M .94; 128 with 8 senders at 13 M
+// 1.03, 32 M .97; with 4 at 52 M 1.0; with 2 at 52 M 1.04, 90 M 1.04).
+constexpr bool i4_two_tiles(uint32_t block, uint32_t num_src, size_t n) {
+    if (n <= ((size_t)8 << 20))
+        return true;
+    if (block > 128 || num_src == 1)
+        return false;
+    if (block == 64)
+        return n > ((size_t)13 << 20);
+    return num_src > 2 && n > ((size_t)(num_src <= 4 ? 96 : 24) << 20);
+}
+
 // Residency cap.  The streaming kernels that keep many HBM streams open at
 // once (the optimizer step: four arrays read, four written) run faster with
 // fewer workgroups resident per CU than the hardware would otherwise place:

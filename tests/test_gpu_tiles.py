@@ -304,6 +304,34 @@ def test_fused_block_routes(zpp, block, sources):
             assert torch.equal(x.raw, y.raw), "%s, n = %d" % (name, n)
 
 
+@pytest.mark.parametrize("block", [64, 128, 256])
+def test_i4_slots_by_length(zpp, block):
+    """A sender's codes and scales in an interleaved buffer at the lengths where
+    the quantizer changes the tiles a wave keeps in flight: those of the plain
+    layout, at the slots' places, and the other senders' slots as they were."""
+    k, source = 3, 1
+    for n in ((8 << 20) + 771, (13 << 20) + 771, (97 << 20) + 771):
+        nb = -(-n // block)
+        gen = torch.Generator(device="cuda").manual_seed(n)
+        x = torch.empty(n, device="cuda").normal_(0, 1e-3, generator=gen)
+        c, s = (torch.zeros(nb * block // 2, dtype=torch.uint8, device="cuda"),
+                torch.zeros(nb, device="cuda"))
+        zpp.quantize_blockwise_i4(x, c, s, block=block)
+        nc, ns = zpp.interleaved_sizes(n, block, k)
+        ci = torch.full((nc,), 0x5A, dtype=torch.uint8, device="cuda")
+        si = torch.full((ns,), -1.0, device="cuda")
+        zpp.quantize_blockwise_i4_interleaved(x, ci, si, source=source, num_src=k, block=block)
+        ci, si = ci.view(nb, k, block // 2), si.view(nb, k)
+        used = (n + 1) // 2 - (nb - 1) * (block // 2)  # bytes of the last block that hold codes
+        assert torch.equal(ci[:-1, source], c.view(nb, -1)[:-1]), n
+        assert torch.equal(ci[-1, source, :used], c.view(nb, -1)[-1, :used]), n
+        assert torch.equal(si[:, source], s), n
+        for q in range(k):
+            if q != source:
+                assert (ci[:, q] == 0x5A).all() and (si[:, q] == -1.0).all(), (n, q)
+        assert (ci[-1, source, used:] == 0x5A).all(), n
+
+
 @pytest.mark.parametrize("block", [64, 256, 512, 4096])
 def test_quantizer_edges(zpp, block):
     """The quantizers at lengths around their whole tiles (rows of 512 elements

@@ -260,6 +260,26 @@ static long check_copies_residency() {
     return 1;
 }
 
+// Tiles in flight of the int4 quantizer.
+static long check_i4_tiles() {
+    const size_t M = 1 << 20;
+    const struct {
+        uint32_t block, num_src;
+        size_t n;
+        bool two;
+    } rule[] = {{256, 1, 8 * M, true},   {256, 8, 8 * M + 1, false}, {64, 1, 200 * M, false},
+                {64, 2, 13 * M, false},  {64, 8, 20 * M, true},      {128, 2, 200 * M, false},
+                {128, 4, 96 * M, false}, {128, 4, 128 * M, true},    {128, 8, 24 * M, false},
+                {128, 8, 32 * M, true},  {128, 64, M, true}};
+    long bad = 0;
+    for (const auto &r : rule)
+        if (zpp::i4_two_tiles(r.block, r.num_src, r.n) != r.two) {
+            printf("int4 tiles: block %u senders %u n %zu\n", r.block, r.num_src, r.n);
+            ++bad;
+        }
+    return bad;
+}
+
 int main() {
     double worst_i8 = 1.0, worst_i8c = 1.0, worst_i4 = 1.0;
     long bad = 0;
@@ -274,6 +294,7 @@ int main() {
     bad += check_quant_copy_runs();
     bad += check_copies_residency();
     bad += check_wide_block();
+    bad += check_i4_tiles();
     bad += check_receive_residency();
     printf("worst fill: int8 %.4f, int8+copy %.4f, int4 %.4f\n", worst_i8, worst_i8c, worst_i4);
     if (bad) {

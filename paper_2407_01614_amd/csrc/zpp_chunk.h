@@ -58,6 +58,37 @@ constexpr size_t xcd_grouped(size_t w, size_t grid, size_t R) {
     return (run + 1) * 8 * R <= grid ? run * 8 * R + (r % 8) * R + r / 8 : w;
 }
 
+// The tiles of one launch: `whole` tiles of C elements from tile `first` on,
+// then, where the array does not end with them, one of `tail` elements.  The
+// host counts them, so that a kernel decides by one 32-bit comparison which
+// kind its tile is.  (The remainder taken in the kernel as the smaller of two
+// 64-bit values was compiled, in one kernel, to a select on a stale condition
+// bit.)
+struct TileSpan {
+    size_t first;
+    uint32_t whole;
+    uint32_t tail;
+    uint32_t on_lines;  // the outputs start on their lines (zpp_api.hip)
+};
+
+// One-shot grids over the tiles of C elements of an array of n, `per_wg` of
+// them to a workgroup of `threads`, in as many launches as HIP's limit of
+// 2^32 - 1 work-items per grid asks for: launch(tiles, workgroups).  A launch
+// takes up to 2^31 work-items, so one-wave workgroups with a 256-element tile
+// (the step) reach 2^33 elements before a second launch, the refresh 2^34.
+// With no loop over tiles in the kernel the code of a whole tile is straight,
+// and the rare partial tile's lies behind it.
+template <class F>
+void for_tiles(size_t n, uint32_t C, uint32_t per_wg, uint32_t threads, bool on_lines, F &&launch) {
+    const size_t tiles = (n + C - 1) / C, most = (((size_t)1 << 31) / threads) * per_wg;
+    for (size_t t = 0; t < tiles; t += most) {
+        const size_t count = tiles - t < most ? tiles - t : most;
+        const size_t whole = n / C - t < count ? n / C - t : count;
+        launch(TileSpan{t, (uint32_t)whole, whole < count ? (uint32_t)(n % C) : 0u, on_lines},
+               (unsigned)((count + per_wg - 1) / per_wg));
+    }
+}
+
 // Whether the refresh with its quantization, its outputs off their lines, runs
 // its workgroups per XCD.  With powers of two up to 512 it gains at every
 // length (256 at 4 M, 8 elements into lines: 4.8 us, 5.1 in plain order; 131 M

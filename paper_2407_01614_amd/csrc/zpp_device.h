@@ -45,19 +45,6 @@ __device__ __forceinline__ size_t block_of(const BlockDiv &d, size_t i) {
     return d.magic ? (size_t)__umul64hi((unsigned long long)(i >> 6), d.magic) : i >> d.shift;
 }
 
-// The tiles of one launch: `whole` tiles of C elements from tile `first` on,
-// then, where the array does not end with them, one of `tail` elements.  The
-// host counts them, so that a kernel decides by one 32-bit comparison which
-// kind its tile is.  (The remainder taken in the kernel as the smaller of two
-// 64-bit values was compiled, in one kernel, to a select on a stale condition
-// bit.)
-struct TileSpan {
-    size_t first;
-    uint32_t whole;
-    uint32_t tail;
-    uint32_t on_lines;  // the outputs start on their lines (zpp_api.hip)
-};
-
 // Outputs that do not start on a 128-byte line: a wave's store then ends inside
 // a line that the next tile's wave goes on with, and two XCDs that each write
 // their part of it cost two partial writes of memory.  So neighbouring tiles
@@ -76,23 +63,6 @@ __device__ __forceinline__ uint32_t tile_of(uint32_t w, uint32_t grid, const Til
                                             size_t run) {
     return (uint32_t)(tiles.on_lines ? xcd_grouped(w, grid, run)
                                      : xcd_grouped(w, grid, kOffLineXcdRun));
-}
-
-// One-shot grids over the tiles of C elements of an array of n, `per_wg` of
-// them to a workgroup of `threads`, in as many launches as HIP's limit of
-// 2^32 - 1 work-items per grid asks for (one, for anything that fits this
-// GPU's memory): launch(tiles, workgroups).  With no loop over tiles in the
-// kernel the code of a whole tile is straight, and the rare partial tile's
-// lies behind it.
-template <class F>
-void for_tiles(size_t n, uint32_t C, uint32_t per_wg, uint32_t threads, bool on_lines, F &&launch) {
-    const size_t tiles = (n + C - 1) / C, most = (((size_t)1 << 31) / threads) * per_wg;
-    for (size_t t = 0; t < tiles; t += most) {
-        const size_t count = tiles - t < most ? tiles - t : most;
-        const size_t whole = n / C - t < count ? n / C - t : count;
-        launch(TileSpan{t, (uint32_t)whole, whole < count ? (uint32_t)(n % C) : 0u, on_lines},
-               (unsigned)((count + per_wg - 1) / per_wg));
-    }
 }
 
 // Streaming accesses: every byte is touched once, so loads and stores are

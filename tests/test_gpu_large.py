@@ -1,6 +1,7 @@
-"""Sizes past 2^32 elements: 64-bit indexing and the grid-stride loops that
-take over once a one-shot grid would exceed its cap.  Checked on sampled
-outputs against the oracle and by properties on everything."""
+"""Sizes past 2^32 elements: 64-bit indexing, the second launch of a one-shot
+grid that would exceed HIP's work-items (2^33 elements for the step, 2^34 for
+the refresh), and the grid-stride loops of the kernels that have one.  Checked
+on sampled outputs against the oracle and by properties on everything."""
 import numpy as np
 import pytest
 import torch
@@ -186,4 +187,53 @@ def test_receive_adam_past_4g(zpp, single_pass):
         assert torch.equal(sec, out)
         del sec, q8, s8
     del p, m, v, out, codes, scales
+    torch.cuda.empty_cache()
+
+
+def needs_free(gib):
+    torch.cuda.empty_cache()
+    free, _ = torch.cuda.mem_get_info()
+    if free < gib << 30:
+        pytest.skip("needs about %d GiB of free device memory" % gib)
+
+
+def test_refresh_in_two_launches(zpp):
+    """A copy of more than 2^34 elements takes a second launch of the one-shot
+    grid: every element copied, the ragged end included."""
+    needs_free(72)
+    n = (1 << 34) + 3 * 512 + 77
+    src = torch.empty(n, dtype=torch.int16, device="cuda")
+    for lo in range(0, n, 1 << 32):
+        src[lo:lo + (1 << 32)].random_(-32768, 32767)
+    dst = torch.zeros_like(src)
+    zpp.refresh_secondary(dst, src)
+    for lo in range(0, n, 1 << 32):
+        assert torch.equal(dst[lo:lo + (1 << 32)], src[lo:lo + (1 << 32)]), lo
+    del src, dst
+    torch.cuda.empty_cache()
+
+
+def test_adam_in_two_launches(zpp):
+    """A step over more than 2^33 elements takes a second launch: the elements
+    around the border and at the end equal, bit for bit, a step over those
+    alone, and all others, which hold one value, agree with each other."""
+    needs_free(160)
+    n, w = (1 << 33) + 4 * 256 + 3, 4096
+    lo = (1 << 33) - w  # the window to the end
+    hp = dict(lr=1e-4, beta1=0.9, beta2=0.95, eps=1e-8, weight_decay=0.1)
+    p, g = (torch.full((n,), x, device="cuda") for x in (0.02, 1e-3))
+    m, v = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+    out = torch.zeros(n, dtype=torch.int16, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    for t, std in ((p, 0.02), (g, 1e-3), (m, 1e-4)):
+        t[lo:].normal_(0, std, generator=gen)
+    v[lo:].uniform_(1e-8, 1e-6, generator=gen)
+    small = [t[lo:].clone() for t in (p, m, v, g, out)]
+    zpp.adam_partition_step(p, m, v, g, out, step=2, **hp)
+    zpp.adam_partition_step(*small, step=2, **hp)
+    for t, r in zip((p, m, v, g, out), small):
+        assert torch.equal(t[lo:], r)
+    for t in (p, m, v, out):
+        assert t[0] != 0 and t[:lo].min() == t[0] and t[:lo].max() == t[0]
+    del p, g, m, v, out
     torch.cuda.empty_cache()

@@ -280,6 +280,45 @@ static long check_i4_tiles() {
     return bad;
 }
 
+// One-shot grids (for_tiles): the launches' tiles follow one another, cover the
+// array with one partial tile at its very end, have workgroups enough for all of
+// them and none to spare, and stay below 2^32 work-items each.  Sizes up to
+// several launches (2^33 elements a launch for the step).
+static long check_for_tiles() {
+    const struct {
+        uint32_t C, per_wg, threads;
+    } shapes[] = {{256, 1, 64}, {512, 1, 64},  {512, 4, 256},  {2048, 1, 256}, {16384, 1, 256},
+                  {320, 1, 128}, {4096, 1, 1024}, {1024, 4, 256}};
+    long bad = 0;
+    for (const auto &sh : shapes) {
+        const size_t most = (((size_t)1 << 31) / sh.threads) * sh.per_wg * sh.C;
+        for (size_t n : {(size_t)0, (size_t)1, (size_t)sh.C - 1, (size_t)sh.C, (size_t)sh.C + 1,
+                         (size_t)sh.C * 7 + 5, most - 1, most, most + 1, most + sh.C,
+                         2 * most - sh.C, 2 * most, 3 * most + 17}) {
+            size_t next = 0, elems = 0, launches = 0;
+            bool ok = true, ended = false;
+            zpp::for_tiles(n, sh.C, sh.per_wg, sh.threads, true,
+                           [&](const zpp::TileSpan &t, unsigned grid) {
+                               const size_t count = (size_t)t.whole + (t.tail != 0);
+                               ok = ok && !ended && t.first == next && count > 0 &&
+                                    t.tail < sh.C && (size_t)grid * sh.threads < ((size_t)1 << 32) &&
+                                    (size_t)grid * sh.per_wg >= count &&
+                                    ((size_t)grid - 1) * sh.per_wg < count && t.on_lines == 1;
+                               next += count;
+                               elems += (size_t)t.whole * sh.C + t.tail;
+                               ended = t.tail != 0;
+                               ++launches;
+                           });
+            if (!ok || elems != n || launches != (n + most - 1) / most) {
+                printf("tiles of %u: n %zu: %zu elements in %zu launches\n", sh.C, n, elems,
+                       launches);
+                ++bad;
+            }
+        }
+    }
+    return bad;
+}
+
 int main() {
     double worst_i8 = 1.0, worst_i8c = 1.0, worst_i4 = 1.0;
     long bad = 0;
@@ -290,6 +329,7 @@ int main() {
     bad += check_groups(8, 55, 2, 2, "int8+copy", worst_i8c);
     bad += check_groups(4, 75, 3, 4, "int4", worst_i4);
     bad += check_xcd_grouped();
+    bad += check_for_tiles();
     bad += check_residency();
     bad += check_quant_copy_runs();
     bad += check_copies_residency();

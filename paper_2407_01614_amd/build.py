@@ -1,6 +1,7 @@
-"""Build ``libzpp.so`` (the HIP kernels and the C ABI) for gfx950 in-tree.
+"""Build ``libzpp.so`` (the HIP kernels and the C ABI) for gfx950 and the
+binding's ``_marshal.so`` in-tree.
 
-    python -m paper_2407_01614_amd.build          # builds paper_2407_01614_amd/libzpp.so
+    python -m paper_2407_01614_amd.build          # both, and libzpp_ceiling.so
 """
 import os
 import subprocess
@@ -48,7 +49,8 @@ def hipcc():
 
 
 def build(out=LIB, defines=(), verbose=False, sources=SOURCES):
-    """Compile the HIP sources of the path into one shared library."""
+    """Compile the HIP sources of the path into one shared library; with the
+    library itself, what its Python binding needs beside it (_marshal.so)."""
     tmp = out + ".tmp%d" % os.getpid()
     cmd = [hipcc(), *HIPCC_FLAGS, *["-D" + d for d in defines], "-I", INCLUDE, "-I", CSRC,
            *[os.path.join(CSRC, s) for s in sources], "-o", tmp]
@@ -64,6 +66,8 @@ def build(out=LIB, defines=(), verbose=False, sources=SOURCES):
     if err and verbose:
         print(err, file=sys.stderr)
     os.replace(tmp, out)
+    if out == LIB:
+        build_marshal(verbose=verbose)
     return out
 
 
@@ -99,4 +103,3 @@ def build_marshal(verbose=False):
 if __name__ == "__main__":
     print(build(verbose=True))
     print(build_ceiling(verbose=True))
-    print(build_marshal(verbose=True))

@@ -15,14 +15,16 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libzpp.so")
+MARSHAL_PATH = os.path.join(_PKG, "_marshal.so")
 
 ZPP_OK, ZPP_EINVAL, ZPP_EALIGN, ZPP_EOVERLAP, ZPP_EHIP = range(5)
 MAX_SHARDS = 64
 MAX_WAIT_EVENTS = 64
 
-if not os.path.exists(LIB_PATH):
-    raise ImportError("libzpp.so is not built (%s); run `python -m paper_2407_01614_amd.build`"
-                      % LIB_PATH)
+for _path in (LIB_PATH, MARSHAL_PATH):
+    if not os.path.exists(_path):
+        raise ImportError("%s is not built (%s); run `python -m paper_2407_01614_amd.build`"
+                          % (os.path.basename(_path), _path))
 
 from . import _marshal  # noqa: E402  (built beside the library)
 

@@ -26,6 +26,43 @@ def zpp():
     return mod
 
 
+def test_build_makes_all_the_binding_needs(monkeypatch):
+    """build() alone leaves an importable binding: the library and the
+    marshalling beside it.  Another output (the measurement streams) is its
+    library alone."""
+    from paper_2407_01614_amd import build
+    made = []
+
+    class Done:
+        returncode, stderr = 0, ""
+
+    monkeypatch.setattr(build.subprocess, "run", lambda *a, **k: Done())
+    monkeypatch.setattr(build.os, "replace", lambda src, dst: made.append(dst))
+    assert build.build() == build.LIB
+    assert made == [build.LIB, build.MARSHAL_LIB]
+    del made[:]
+    build.build_ceiling()
+    assert made == [build.CEILING_LIB]
+
+
+@pytest.mark.parametrize("there", [[], ["libzpp.so"], ["_marshal.so"]],
+                         ids=["neither", "library", "marshalling"])
+def test_import_says_what_is_not_built(tmp_path, there):
+    import shutil
+    import sys
+    pkg = tmp_path / "paper_2407_01614_amd"
+    pkg.mkdir()
+    for name in ("__init__.py", "zpp.py"):
+        shutil.copy(os.path.join(ROOT, "paper_2407_01614_amd", name), str(pkg))
+    for name in there:
+        (pkg / name).write_bytes(b"")
+    r = subprocess.run([sys.executable, "-c", "import paper_2407_01614_amd.zpp"],
+                       cwd=str(tmp_path), capture_output=True, text=True, timeout=120)
+    missing = "_marshal.so" if there == ["libzpp.so"] else "libzpp.so"
+    assert r.returncode != 0 and "ImportError: %s is not built" % missing in r.stderr, r.stderr
+    assert "python -m paper_2407_01614_amd.build" in r.stderr
+
+
 def declared_functions():
     text = open(HEADER).read()
     return sorted(set(re.findall(r"ZPP_API\s+[\w\s\*]*?\b(zpp_\w+)\s*\(", text)))

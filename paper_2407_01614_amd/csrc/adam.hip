@@ -32,7 +32,6 @@ struct AdamArgs {
     float *p, *m, *v;
     const float *g;
     uint16_t *out;
-    size_t n;
     AdamConsts c;
 };
 
@@ -76,7 +75,7 @@ __global__ __launch_bounds__(kAdamThreads) void adam_vec_kernel(AdamArgs a, Tile
 
 hipError_t launch_adam(float *p, float *m, float *v, const float *g, uint16_t *out, size_t n,
                        const AdamConsts &c, bool on_lines, hipStream_t stream) {
-    const AdamArgs a{p, m, v, g, out, n, c};
+    const AdamArgs a{p, m, v, g, out, c};
     constexpr uint32_t kTile = kAdamThreads * 4 * ZPP_ADAM_UNROLL;
     const size_t lds = launch_lds(ZPP_ADAM_RESIDENCY, n / kTile);
     for_tiles(n, kTile, 1, kAdamThreads, on_lines, [&](const TileSpan &tiles, unsigned grid) {

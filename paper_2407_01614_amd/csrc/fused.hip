@@ -314,7 +314,7 @@ hipError_t launch_fused_gs(const FusedArgs &a, const GS &gs, uint32_t block, boo
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
-        return launch_quantize(a.primary, a.n, block, a.codes, a.scales, on_lines, stream);
+        return launch_quantize(a.primary, a.n, block, a.codes, a.scales, stream);
     }
     }
     return hipGetLastError();

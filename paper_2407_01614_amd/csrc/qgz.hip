@@ -409,7 +409,7 @@ void launch_quant_i4_grp_g(uint32_t G, const float *src, size_t n, uint32_t bloc
 
 hipError_t launch_quantize_i4_il(const float *src, size_t n, uint32_t block, uint32_t source,
                                  uint32_t num_src, uint8_t *codes, float *scales,
-                                 bool, hipStream_t stream) {
+                                 hipStream_t stream) {
     switch (block) {
     case 64: launch_quant_i4_b<64>(src, n, codes, scales, source, num_src, stream); break;
     case 128: launch_quant_i4_b<128>(src, n, codes, scales, source, num_src, stream); break;
@@ -435,8 +435,8 @@ hipError_t launch_quantize_i4_il(const float *src, size_t n, uint32_t block, uin
 }
 
 hipError_t launch_quantize_i4(const float *src, size_t n, uint32_t block, uint8_t *codes,
-                              float *scales, bool on_lines, hipStream_t stream) {
-    return launch_quantize_i4_il(src, n, block, 0, 1, codes, scales, on_lines, stream);
+                              float *scales, hipStream_t stream) {
+    return launch_quantize_i4_il(src, n, block, 0, 1, codes, scales, stream);
 }
 
 hipError_t launch_dequant_reduce_i4(const uint8_t *const *src_codes,

@@ -421,16 +421,14 @@ void launch_vector(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
 hipError_t launch_quantize_copy(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
                                 float *scales, uint16_t *copy, bool on_lines,
                                 hipStream_t stream) {
-    if (copy)
-        launch_vector<true>(src, n, block, codes, scales, copy, on_lines, stream);
-    else
-        launch_vector<false>(src, n, block, codes, scales, nullptr, on_lines, stream);
+    launch_vector<true>(src, n, block, codes, scales, copy, on_lines, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_quantize(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
-                           float *scales, bool on_lines, hipStream_t stream) {
-    return launch_quantize_copy(src, n, block, codes, scales, nullptr, on_lines, stream);
+                           float *scales, hipStream_t stream) {
+    launch_vector<false>(src, n, block, codes, scales, nullptr, true, stream);
+    return hipGetLastError();
 }
 
 }  // namespace zpp

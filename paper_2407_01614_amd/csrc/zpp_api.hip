@@ -240,8 +240,7 @@ ZPP_API zpp_status zpp_quantize_blockwise_i8(const uint16_t *src_bf16, size_t n,
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines = start_at(128, {codes});
-        const hipError_t e = zpp::launch_quantize(src_bf16, n, block, codes, scales, lines, stream);
+        const hipError_t e = zpp::launch_quantize(src_bf16, n, block, codes, scales, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -358,8 +357,7 @@ ZPP_API zpp_status zpp_quantize_blockwise_i4(const float *src, size_t n, uint32_
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines = start_at(128, {codes});
-        const hipError_t e = zpp::launch_quantize_i4(src, n, block, codes, scales, lines, stream);
+        const hipError_t e = zpp::launch_quantize_i4(src, n, block, codes, scales, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }
@@ -568,9 +566,8 @@ ZPP_API zpp_status zpp_quantize_blockwise_i4_interleaved(const float *src, size_
     if (st != ZPP_OK)
         return st;
     if (n) {
-        const bool lines = start_at(128, {codes});
         const hipError_t e = zpp::launch_quantize_i4_il(src, n, block, source, num_src, codes,
-                                                        scales, lines, stream);
+                                                        scales, stream);
         if (e != hipSuccess)
             return hip_fail(e);
     }

@@ -9,10 +9,6 @@
 
 namespace zpp {
 
-#ifndef ZPP_THREADS
-#define ZPP_THREADS 256
-#endif
-constexpr int kThreads = ZPP_THREADS;  // workgroup size: 4 wave64 by default
 constexpr int kWave = 64;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));

@@ -57,7 +57,7 @@ hipError_t launch_refresh(uint16_t *dst, const uint16_t *src, size_t count, bool
                           hipStream_t stream);
 
 hipError_t launch_quantize(const uint16_t *src, size_t n, uint32_t block, int8_t *codes,
-                           float *scales, bool on_lines, hipStream_t stream);
+                           float *scales, hipStream_t stream);
 
 // The quantization that also stores the bf16 it reads to `copy`: the
 // secondary refresh and its quantization in one pass.
@@ -86,7 +86,7 @@ hipError_t launch_gather(const GatherShards &shards, uint32_t num_shards, size_t
 // qgZ: int4 quantization of fp32 gradients, and the dequantize-and-reduce
 // of num_src quantized copies of one partition.
 hipError_t launch_quantize_i4(const float *src, size_t n, uint32_t block, uint8_t *codes,
-                              float *scales, bool on_lines, hipStream_t stream);
+                              float *scales, hipStream_t stream);
 
 hipError_t launch_dequant_reduce_i4(const uint8_t *const *src_codes,
                                     const float *const *src_scales, uint32_t num_src, size_t n,
@@ -136,7 +136,7 @@ hipError_t launch_dequant_reduce_i4_il(const uint8_t *codes, const float *scales
 // layout of launch_quantize_i4).
 hipError_t launch_quantize_i4_il(const float *src, size_t n, uint32_t block, uint32_t source,
                                  uint32_t num_src, uint8_t *codes, float *scales,
-                                 bool on_lines, hipStream_t stream);
+                                 hipStream_t stream);
 
 // The qgZ receive fused into the partition step: the gradient of every
 // element is the dequantize-and-reduce of the num_src int4 sources (times

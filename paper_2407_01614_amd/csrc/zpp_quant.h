@@ -37,14 +37,10 @@ __device__ __forceinline__ BlockQuant block_params(uint32_t absbits) {
     return q;
 }
 
-// Scalar code of one value (used by the any-alignment kernel).  No clamp is
-// needed: |x| <= a and inv <= (127/a)(1 + 2^-24), so |x * inv| rounds to at
-// most 127 (1 + 2^-24)^2 < 127.5 and rint stays within [-127, 127].
-__device__ __forceinline__ int quant_one(float x, const BlockQuant &q) {
-    const float y = __builtin_rintf((x * q.pre) * q.inv);
-    return q.zero ? 0 : (int)y;
-}
-
+// No code needs a clamp: |x| <= a and inv <= (127/a)(1 + 2^-24), so |x * inv|
+// rounds to at most 127 (1 + 2^-24)^2 < 127.5 and stays within [-127, 127]
+// after rounding to an integer.
+//
 // Adding 1.5 * 2^23 to y (|y| < 2^22) leaves rint(y) in the low bits of the
 // sum's bit pattern: the sum's ulp is 1 and the addition rounds to nearest
 // even, exactly as rint does; the low byte is then the two's-complement code.

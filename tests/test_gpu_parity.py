@@ -2,7 +2,8 @@
 against the CPU oracle on identical seeded inputs.
 
 Sizes span several tiles with ragged tails; misaligned views drive the
-scalar kernels; special values cover the degenerate cases of the method.
+kernels' element-aligned accesses and the workgroup order of outputs off their
+lines; special values cover the degenerate cases of the method.
 Full-size cases at the Llama-2-13B shapes live in test_gpu_fullsize.py.
 """
 import numpy as np
@@ -87,7 +88,7 @@ def test_adam_multistep(zpp, adamw, hp):
 
 
 @pytest.mark.parametrize("n", [1, 3, 4, 5, 1023, 2047, 2048, 2049, 3 * 2048 + 7, 100003])
-@pytest.mark.parametrize("pad", [0, 1], ids=["vector", "scalar"])
+@pytest.mark.parametrize("pad", [0, 1], ids=["aligned", "off-by-one"])
 def test_adam_ragged(zpp, n, pad):
     hp = f32hp(HP_LOUD)
     p = synth.master_weights(n, 41, n)
@@ -183,7 +184,7 @@ def test_adam_checkpoint_resume_is_bitwise(zpp):
 # Secondary refresh
 # ===========================================================================
 @pytest.mark.parametrize("count", [0, 1, 7, 8, 9, 8191, 8192, 8193, 2 * 8192 * 4 + 5, 2097152])
-@pytest.mark.parametrize("pad", [0, 1], ids=["vector", "scalar"])
+@pytest.mark.parametrize("pad", [0, 1], ids=["aligned", "off-by-one"])
 def test_refresh_bitwise(zpp, count, pad):
     src = synth.random_bits16(count, 50, count)
     tsrc = to_dev(src, pad=pad)
@@ -239,7 +240,7 @@ def test_quant_blocks_and_ragged(zpp, block, n):
 
 
 @pytest.mark.parametrize("pads", [(1, 0), (0, 1), (8, 3)], ids=["src", "codes", "both"])
-def test_quant_misaligned_scalar_path(zpp, pads):
+def test_quant_misaligned(zpp, pads):
     n = 256 * 37 + 80
     x = synth.bf16_weights(n, 53)
     assert_quant_equal(run_quant_gpu(zpp, x, 256, *pads), oracle.quantize_blockwise_i8(x, 256),
@@ -270,7 +271,7 @@ def special_blocks(block):
 
 
 @pytest.mark.parametrize("block", [64, 192, 256, 4032, 4096])
-@pytest.mark.parametrize("pad", [0, 1], ids=["vector", "scalar"])
+@pytest.mark.parametrize("pad", [0, 1], ids=["aligned", "off-by-one"])
 def test_quant_special_blocks(zpp, block, pad):
     x = special_blocks(block)
     assert_quant_equal(run_quant_gpu(zpp, x, block, pad_src=pad),
@@ -308,8 +309,8 @@ def test_refresh_quantize_vs_oracle(zpp, block, n):
 @pytest.mark.parametrize("pads", [(1, 0, 0), (0, 1, 0), (0, 0, 3), (8, 0, 0)],
                          ids=["src", "secondary", "codes", "src-16"])
 def test_refresh_quantize_misaligned(zpp, pads):
-    """Misaligned views take the scalar kernel (or, for a 16-byte-aligned
-    offset, the vector one): the same bits."""
+    """Views off an output's line (workgroups in runs per XCD), or off the
+    vectors' alignment with the outputs on lines: the same bits."""
     n = 256 * 37 + 80
     x = synth.bf16_weights(n, 57)
     sec, codes, scales = run_refresh_quant_gpu(zpp, x, 256, *pads)
@@ -369,7 +370,7 @@ def test_gather_tiny_layer(zpp):
     (3, 3 * 5000 - 77, 320),
     (2, 2 * 4032 - 4031, 4032),
 ])
-@pytest.mark.parametrize("pad_out", [0, 1], ids=["vector", "scalar"])
+@pytest.mark.parametrize("pad_out", [0, 1], ids=["aligned", "off-by-one"])
 def test_gather_shapes(zpp, P2, N, block, pad_out):
     s, codes, scales = quantized_shards(N, P2, block, 60 + P2)
     got = run_gather_gpu(zpp, codes, scales, s, block, N, pad_out=pad_out)
@@ -379,8 +380,8 @@ def test_gather_shapes(zpp, P2, N, block, pad_out):
 
 @pytest.mark.parametrize("s", [1000, 256 * 3 + 8, 17])
 def test_gather_unaligned_shard_length(zpp, s):
-    """Shard lengths that are not a multiple of 16 take the scalar kernel;
-    the last block of every shard is then short."""
+    """Shard lengths that are not a multiple of 16 put the shards' parts of
+    the output off their lines, and the last block of every shard is short."""
     P2, block = 4, 256
     codes = [synth.random_codes(s, 61, j) for j in range(P2)]
     scales = [synth.random_scales((s + block - 1) // block, 61, j) for j in range(P2)]
@@ -493,11 +494,11 @@ def test_fused_vs_oracle(zpp, block, n):
 
 
 @pytest.mark.parametrize("block", [192, 320, 1024, 4032])
-def test_fused_two_kernel_blocks_misaligned_quantization(zpp, block):
-    """Blocks other than 64-512 run the step with its copies, then the int8
-    quantizer over the primary.  An 8-byte (not 16-byte) aligned primary and
-    4-byte (not 8-byte) aligned codes keep the step's vector kernel but put
-    the quantization on its scalar kernel: the same bits."""
+def test_fused_wide_blocks_misaligned(zpp, block):
+    """A workgroup per block (these short arrays) with an 8-byte (not 16-byte)
+    aligned primary and secondary and 4-byte aligned codes: the oracle's
+    results.  (The two kernels of longer arrays off alignment are
+    test_gpu_tiles.py's.)"""
     hp = f32hp(HP_TINY)
     n = block * 37 + 100
     p = synth.master_weights(n, 73, block)
@@ -508,11 +509,11 @@ def test_fused_two_kernel_blocks_misaligned_quantization(zpp, block):
 
 
 @pytest.mark.parametrize("secondary", [True, False], ids=["with-secondary", "no-secondary"])
-@pytest.mark.parametrize("pad", [0, 1], ids=["fused", "scalar"])
+@pytest.mark.parametrize("pad", [0, 1], ids=["aligned", "off-by-one"])
 @pytest.mark.parametrize("block", [256, 320])
 def test_fused_equals_separate_calls(zpp, secondary, pad, block):
     """The fused entry gives, bit for bit, what the three separate calls give
-    on the same inputs (both on the GPU), on both of its paths."""
+    on the same inputs (both on the GPU), aligned and off by one element."""
     hp = f32hp(HP_LOUD)
     n = 256 * 300 + 17
     p = synth.master_weights(n, 71)

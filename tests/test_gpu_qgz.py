@@ -85,7 +85,7 @@ def i4_special(block):
 
 
 @pytest.mark.parametrize("block", [64, 192, 256, 1024])
-@pytest.mark.parametrize("pad", [0, 1], ids=["vector", "scalar"])
+@pytest.mark.parametrize("pad", [0, 1], ids=["aligned", "off-by-one"])
 def test_quant_i4_special_blocks(zpp, block, pad):
     x = i4_special(block)
     got = run_quant_i4(zpp, x, block, pad_src=pad)
@@ -122,7 +122,7 @@ def test_dequant_reduce_i4_vs_oracle(zpp, P, n):
 
 @pytest.mark.parametrize("P,n,block", [(8, 192 * 37 + 5, 192), (3, 320 * 11 + 7, 320),
                                        (5, 4032 * 3 + 33, 4032)])
-@pytest.mark.parametrize("pad_out", [0, 1], ids=["vector", "scalar"])
+@pytest.mark.parametrize("pad_out", [0, 1], ids=["aligned", "off-by-one"])
 def test_dequant_reduce_i4_blocks_not_powers_of_two(zpp, P, n, block, pad_out):
     quants = oracle_sources(P, n, block, 85 + n)
     got = run_reduce_i4(zpp, quants, n, block, float(np.float32(1.0 / P)), pad_out=pad_out)
@@ -299,8 +299,7 @@ def test_receive_adam_equals_reduce_then_step(zpp, P, n, block, regime):
 
 @pytest.mark.parametrize("pads", [(1, 0), (0, 1), (3, 1)], ids=["state", "codes", "both"])
 def test_receive_adam_misaligned(zpp, pads):
-    """Misaligned state or codes take the any-alignment kernel: still the
-    two-kernel sequence bit for bit."""
+    """Misaligned state or codes: still the two-kernel sequence bit for bit."""
     n, block, P = 256 * 11 + 5, 128, 5
     quants = oracle_sources(P, n, block, 92)
     ref_state, _ = receive_state(n, 93)
@@ -440,7 +439,7 @@ def test_receive_pass_equals_three_calls(zpp, P, n, grad_block, block, secondary
 
 @pytest.mark.parametrize("pad", [1, 3])
 def test_receive_pass_misaligned(zpp, pad):
-    """Misaligned arrays take the three scalar kernels: the same results."""
+    """Misaligned arrays: the same results."""
     n, grad_block, block, P = 256 * 11 + 5, 128, 256, 5
     quants = oracle_sources(P, n, grad_block, 98)
     ref_state, _ = receive_state(n, 99)
@@ -553,7 +552,7 @@ def zeros_u8(n):
                                        (8, 65536 + 8, 1024), (64, 256 * 5 + 3, 128),
                                        (5, 4096 * 3 + 500, 4096), (8, 192 * 9 + 81, 192),
                                        (3, 320 * 5 + 3, 320)])
-@pytest.mark.parametrize("pad", [0, 1], ids=["vector", "scalar"])
+@pytest.mark.parametrize("pad", [0, 1], ids=["aligned", "off-by-one"])
 def test_quantize_i4_interleaved_equals_plain(zpp, P, n, block, pad):
     """Each source quantized into its slots of one interleaved buffer: taken
     back out, every source's codes and scales are the oracle's, bit for bit."""
@@ -604,9 +603,8 @@ def test_receive_interleaved_equals_separate(zpp, P, n, block, regime):
 @pytest.mark.parametrize("pads", [(1, 0), (0, 1), (0, 3), (0, 2)],
                          ids=["state", "codes-odd", "codes-odd-3", "codes-2"])
 def test_receive_interleaved_misaligned(zpp, pads):
-    """Misaligned state, or interleaved codes at an odd address, take the
-    any-alignment kernel; codes at a 2-byte address keep the vector kernel:
-    the same bits either way."""
+    """Misaligned state, or interleaved codes at an odd or a 2-byte address:
+    the same bits."""
     n, block, P = 256 * 11 + 5, 128, 5
     quants = oracle_sources(P, n, block, 162)
     ref_state, _ = receive_state(n, 163)
@@ -749,9 +747,8 @@ def test_dequant_reduce_interleaved_vs_oracle(zpp, P, n, block):
 
 @pytest.mark.parametrize("pads", [(1, 0), (0, 1), (0, 2)], ids=["out", "codes-odd", "codes-2"])
 def test_dequant_reduce_interleaved_misaligned(zpp, pads):
-    """A misaligned output or codes at an odd address take the any-alignment
-    kernel; codes at a 2-byte address keep the vector kernel: the oracle's
-    bits either way."""
+    """A misaligned output, or codes at an odd or a 2-byte address: the
+    oracle's bits."""
     n, block, P = 256 * 11 + 5, 128, 5
     quants = oracle_sources(P, n, block, 171)
     got = run_reduce_il(zpp, quants, n, block, 0.2, *pads)

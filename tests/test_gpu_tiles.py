@@ -265,52 +265,164 @@ def test_refresh_quantize_long_ranges_off_lines(zpp, block):
                 assert torch.equal(a, b), n
 
 
+def random_copies(n, k, grad_block, gen):
+    """k int4 copies of n elements, each with codes of its own and scales of
+    its own per block, and the gradient that they sum to.  The sum is the fma
+    chain of the method bit for bit: with scales within 1e-5 .. 2e-4 a partial
+    sum and a product together span fewer than 53 bits, so each sum in 64 bits
+    is exact and rounds to 32 once."""
+    codes, scales, acc = [], [], torch.zeros(n, device="cuda")
+    nb = -(-n // grad_block)
+    for _ in range(k):
+        c = torch.randint(0, 256, ((n + 1) // 2,), dtype=torch.uint8, device="cuda", generator=gen)
+        s = torch.empty(nb, device="cuda").uniform_(1e-5, 2e-4, generator=gen)
+        x = torch.stack((c & 0xF, c >> 4), 1).reshape(-1)[:n].to(torch.int8)
+        x = ((x ^ 8) - 8).double()
+        x *= s.repeat_interleave(grad_block)[:n].double()
+        acc = (acc.double() + x).float()
+        codes.append(c)
+        scales.append(s)
+    return codes, scales, acc * torch.tensor(1.0 / k, dtype=torch.float32, device="cuda")
+
+
+def interleaved(codes, scales, n, grad_block, offset):
+    """Those copies in one receive buffer, its codes `offset` bytes into it."""
+    k, nb, half = len(codes), -(-n // grad_block), grad_block // 2
+    c = torch.zeros(offset + nb * k * half, dtype=torch.uint8, device="cuda")
+    for q in range(k):
+        flat = torch.zeros(nb * half, dtype=torch.uint8, device="cuda")
+        flat[:codes[q].numel()] = codes[q]
+        c[offset:].view(nb, k, half)[:, q] = flat.view(nb, half)
+    return c[offset:], torch.stack(scales, 1).reshape(-1)
+
+
+NAMES7 = NAMES + ("codes", "scales")
+
+
+def check_pass(zpp, n, block, layout, k, grad_block, adamw=True, offset=0, secondary=True):
+    """The step with its copies and codes in one call, the receive step and the
+    reduction, against the gradient itself through the step and the refresh with
+    its quantization as calls of their own, bit for bit."""
+    gen = torch.Generator(device="cuda").manual_seed(n * 64 + k)
+    p = torch.empty(n, device="cuda").normal_(0, 0.02, generator=gen)
+    if layout == "gradient":
+        g = torch.empty(n, device="cuda").normal_(0, 1e-3, generator=gen)
+    else:
+        codes, scales, g = random_copies(n, k, grad_block, gen)
+    hp, kw = dict(HP, step=3, adamw=adamw), dict(scale_out=float(np.float32(1.0 / k)))
+
+    def state():
+        st = [Buf(n, torch.float32, offset) for _ in range(3)] + [Buf(n, torch.int16, offset)]
+        for b, x in zip(st, (p, g * 0.5, g * g)):
+            b.t.copy_(x)
+        return st
+
+    def outputs():
+        return [Buf(n, torch.int16, offset), Buf(n, torch.int8, offset),
+                Buf(-(-n // block), torch.float32)]
+
+    def same(got, ref, what):
+        for x, y, name in zip(got, ref, NAMES7):
+            assert x is None or torch.equal(x.raw, y.raw), (what, name)
+
+    ref, ref_out = state(), outputs()
+    gb = Buf(n, torch.float32, offset)
+    gb.t.copy_(g)
+    zpp.adam_partition_step(*[b.t for b in ref[:3]], gb.t, ref[3].t, **hp)
+    zpp.refresh_quantize_i8(ref_out[0].t, ref[3].t, ref_out[1].t, ref_out[2].t, block=block)
+    got, out = state(), outputs()
+    a, o = [b.t for b in got], [b.t for b in out]
+    if not secondary:
+        out[0] = o[0] = None
+    if layout == "gradient":
+        zpp.adam_step_refresh_quantize(*a[:3], gb.t, a[3], *o, block=block, **hp)
+        return same(got + out, ref + ref_out, "fused")
+    if layout == "interleaved":
+        src = interleaved(codes, scales, n, grad_block, offset) + (k,)
+        calls = (zpp.qgz_receive_step_refresh_quantize_interleaved,
+                 zpp.qgz_receive_adam_step_interleaved, zpp.dequant_reduce_i4_interleaved)
+    else:
+        src = ([torch.cat((c[:offset], c))[offset:] for c in codes], scales)
+        calls = (zpp.qgz_receive_step_refresh_quantize, zpp.qgz_receive_adam_step,
+                 zpp.dequant_reduce_i4)
+    calls[0](*a[:3], *src, a[3], *o, grad_block=grad_block, block=block, **kw, **hp)
+    same(got + out, ref + ref_out, "pass")
+    got = state()
+    a = [b.t for b in got]
+    calls[1](*a[:3], *src, a[3], block=grad_block, **kw, **hp)
+    same(got, ref, "step")
+    r = Buf(n, torch.float32, offset)
+    calls[2](*src, n, r.t, block=grad_block, **kw)
+    assert torch.equal(r.raw, gb.raw), "reduction"
+
+
 @pytest.mark.parametrize("sources", [0, 16], ids=["gradient", "receive"])
 @pytest.mark.parametrize("block", [192, 320, 832, 1024, 1280, 1344, 2048, 4096])
 def test_fused_block_routes(zpp, block, sources):
-    """A block per workgroup against the step and the quantizer as separate
-    calls, at the lengths where the route changes and at ragged ones."""
+    """The fused step for blocks other than 64, 128, 256 and 512 at ragged
+    lengths and around 8 M elements, where most blocks change from a workgroup
+    per block to two kernels; the receive with 16 separate copies."""
     limit = 8 << 20
-    for n in (1, block - 1, block, 5 * block + 3, limit, limit + 64 * block // 64 + 5):
-        names = ("master", "exp_avg", "exp_avg_sq", "primary", "secondary", "codes", "scales")
-        gen = torch.Generator(device="cuda").manual_seed(n)
-        p = torch.empty(n, device="cuda").normal_(0, 0.02, generator=gen)
-        g = torch.empty(n, device="cuda").normal_(0, 1e-3, generator=gen)
-        m, v = g * 0.5, g * g
-        if sources:
-            codes = torch.randint(0, 256, ((n + 1) // 2,), dtype=torch.uint8, device="cuda",
-                                  generator=gen)
-            src = [codes] * sources, [torch.full((-(-n // 256),), 1e-4, device="cuda")] * sources
-            kw = dict(scale_out=1.0 / sources)
-        got = [Buf(n, torch.float32) for _ in range(3)] + [
-            Buf(n, torch.int16), Buf(n, torch.int16), Buf(n, torch.int8),
-            Buf(-(-n // block), torch.float32)]
-        ref = [Buf(n, torch.float32) for _ in range(3)] + [
-            Buf(n, torch.int16), Buf(n, torch.int16), Buf(n, torch.int8),
-            Buf(-(-n // block), torch.float32)]
-        for bufs in (got, ref):
-            for b, x in zip(bufs, (p, m, v)):
-                b.t.copy_(x)
-        a, b = [x.t for x in got], [x.t for x in ref]
-        if sources:
-            zpp.qgz_receive_step_refresh_quantize(*a[:3], *src, *a[3:], block=block, step=3, **kw,
-                                                  **HP)
-            zpp.qgz_receive_adam_step(*b[:3], *src, b[3], step=3, **kw, **HP)
-        else:
-            zpp.adam_step_refresh_quantize(*a[:3], g, *a[3:], block=block, step=3, **HP)
-            zpp.adam_partition_step(*b[:3], g, b[3], step=3, **HP)
-        zpp.refresh_quantize_i8(b[4], b[3], b[5], b[6], block=block)
-        for x, y, name in zip(got, ref, names):
-            assert torch.equal(x.raw, y.raw), "%s, n = %d" % (name, n)
+    for n in (1, block - 1, block, 5 * block + 3, limit, limit + block + 5):
+        check_pass(zpp, n, block, "separate" if sources else "gradient", max(sources, 1), 256)
 
 
-@pytest.mark.parametrize("block", [64, 128, 256])
+@pytest.mark.parametrize("layout", ["separate", "interleaved"])
+@pytest.mark.parametrize("adamw", [True, False], ids=["adamw", "l2"])
+@pytest.mark.parametrize("k,grad_block,offset", [(16, 256, 0), (19, 512, 3), (33, 1024, 1),
+                                                 (64, 256, 4), (8, 256, 0), (12, 192, 1),
+                                                 (17, 320, 0), (24, 64, 5)])
+def test_receives(zpp, layout, adamw, k, grad_block, offset):
+    """Every int8 block's kernel with few and many int4 copies: whole tiles, a
+    partial one, on and off alignment, both forms of the decay.  (Many copies
+    take the many-source form with int4 blocks that are multiples of 256.)"""
+    for block in (64, 128, 256, 512, 192, 832, 1024, 4096):
+        check_pass(zpp, 5 * 4096 + 1029, block, layout, k, grad_block, adamw, offset,
+                   secondary=block != 512)
+
+
+@pytest.mark.parametrize("offset", [0, 1, 3, 4])
+@pytest.mark.parametrize("layout,k,block,adamw,secondary", [
+    ("gradient", 1, 192, True, True), ("gradient", 1, 2048, False, True),
+    ("gradient", 1, 4096, True, False),
+    ("separate", 3, 192, True, True), ("separate", 8, 2048, False, True),
+    ("separate", 19, 320, True, True), ("separate", 16, 4096, False, False),
+    ("interleaved", 1, 2048, False, True), ("interleaved", 8, 192, True, False),
+    ("interleaved", 12, 4096, True, True), ("interleaved", 17, 2048, True, True),
+    ("interleaved", 16, 320, False, True)])
+def test_two_kernels(zpp, layout, k, block, adamw, secondary, offset):
+    """Beyond 8 M elements, the step with its copies and then the quantizer over
+    the primary it wrote: each source of the gradient, few and many copies, on
+    and off alignment."""
+    check_pass(zpp, (8 << 20) + 2 * block + 5, block, layout, k, 256, adamw, offset, secondary)
+
+
+@pytest.mark.parametrize("layout,k,grad_block,block,limit", [
+    ("gradient", 1, 256, 832, 24 << 20), ("gradient", 1, 256, 1280, 24 << 20),
+    ("gradient", 1, 256, 1024, 104 << 20), ("gradient", 1, 256, 1152, 104 << 20),
+    ("separate", 8, 256, 1024, 4 << 20), ("separate", 3, 256, 832, 16 << 20),
+    ("separate", 64, 256, 1088, 2 << 20), ("interleaved", 8, 192, 1280, 4 << 20),
+    ("interleaved", 4, 256, 1088, 64 << 20), ("interleaved", 9, 256, 960, 16 << 20),
+    ("interleaved", 20, 256, 2048, 4 << 20), ("interleaved", 40, 512, 4096, 4 << 20),
+    ("separate", 16, 256, 256, 12 << 20), ("separate", 20, 512, 512, 12 << 20),
+    ("interleaved", 16, 256, 64, 12 << 20), ("interleaved", 16, 64, 256, 8 << 20),
+    ("separate", 20, 1024, 2048, 12 << 20)])
+def test_lengths_of_the_rules(zpp, layout, k, grad_block, block, limit):
+    """Around the lengths where the number of kernels or the workgroups per CU
+    change."""
+    for n in (limit, limit + block + 3):
+        check_pass(zpp, n, block, layout, k, grad_block)
+
+
+@pytest.mark.parametrize("block", [64, 128, 256, 1024, 2048, 4096])
 def test_i4_slots_by_length(zpp, block):
     """A sender's codes and scales in an interleaved buffer at the lengths where
-    the quantizer changes the tiles a wave keeps in flight: those of the plain
-    layout, at the slots' places, and the other senders' slots as they were."""
+    the quantizer changes the tiles a wave keeps in flight or caps residency:
+    those of the plain layout, at the slots' places, and the other senders' slots
+    as they were."""
     k, source = 3, 1
-    for n in ((8 << 20) + 771, (13 << 20) + 771, (97 << 20) + 771):
+    lengths = ((8, 13, 97) if block <= 256 else (8, 48))
+    for n in [(m << 20) + 771 for m in lengths]:
         nb = -(-n // block)
         gen = torch.Generator(device="cuda").manual_seed(n)
         x = torch.empty(n, device="cuda").normal_(0, 1e-3, generator=gen)

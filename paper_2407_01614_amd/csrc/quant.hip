@@ -371,8 +371,9 @@ void launch_grp(const uint16_t *src, size_t n, uint32_t block, int8_t *codes, fl
     const size_t nblocks = (n + block - 1) / block;
     const size_t need = (nblocks + kGroupsPerBlock - 1) / kGroupsPerBlock;
     const unsigned grid = (unsigned)(need < ZPP_QUANT_MAX_GRID ? need : ZPP_QUANT_MAX_GRID);
-    if (COPY && !on_lines && quant_copy_runs(block, n))
-        hipLaunchKernelGGL((quant_grp_kernel<G, S, COPY, COPY>), dim3(grid), dim3(kQuantThreads),
+    constexpr bool kRuns = COPY && S == 2;  // the blocks of quant_copy_runs
+    if (kRuns && !on_lines && quant_copy_runs(block, n))
+        hipLaunchKernelGGL((quant_grp_kernel<G, S, COPY, kRuns>), dim3(grid), dim3(kQuantThreads),
                            0, stream, src, n, block, codes, scales, copy);
     else
         hipLaunchKernelGGL((quant_grp_kernel<G, S, COPY, false>), dim3(grid), dim3(kQuantThreads),

@@ -240,7 +240,7 @@ def test_alignments(zpp, n, block, interleaved):
             assert np.array_equal(got[name], r), (name, offset)
 
 
-@pytest.mark.parametrize("block", [192, 576, 960, 1088])
+@pytest.mark.parametrize("block", [192, 320, 576, 960, 1088])
 def test_refresh_quantize_long_ranges_off_lines(zpp, block):
     """The refresh with its quantization over ranges off their lines, around
     the length from which lane groups run per XCD (a run is 1024 workgroups of
@@ -365,6 +365,12 @@ def test_fused_block_routes(zpp, block, sources):
     limit = 8 << 20
     for n in (1, block - 1, block, 5 * block + 3, limit, limit + block + 5):
         check_pass(zpp, n, block, "separate" if sources else "gradient", max(sources, 1), 256)
+
+
+@pytest.mark.parametrize("block", [64, 128, 192, 256, 512, 1024])
+def test_fused_with_l2_decay(zpp, block):
+    for offset in (0, 3):
+        check_pass(zpp, 5 * 4096 + 1029, block, "gradient", 1, 256, adamw=False, offset=offset)
 
 
 @pytest.mark.parametrize("layout", ["separate", "interleaved"])

@@ -161,6 +161,13 @@ static long check_quant_copy_runs() {
                 {576, 4u << 20, false},  {576, 32u << 20, true},  {960, (32u << 20) - 1, false},
                 {1088, 200u << 20, false}, {4032, 50u << 20, false}};
     long bad = 0;
+    // lane groups run per XCD in the instances of two slots alone
+    for (uint32_t block = 192; block < 4096; block += 64)
+        if ((block & (block - 1)) != 0 && zpp::quant_copy_runs(block, 200u << 20) &&
+            zpp::group_shape(block / 8, 16, 55, 2).S > 2) {
+            printf("runs of the copy: block %u has more than two slots\n", block);
+            ++bad;
+        }
     for (const auto &r : rule)
         if (zpp::quant_copy_runs(r.block, r.n) != r.runs) {
             printf("runs of the copy: block %u n %zu\n", r.block, r.n);

@@ -17,10 +17,10 @@
 // absmax is known; a 256-block is exactly one wave, so its absmax is a
 // six-step cross-lane reduction.  Blocks of 64, 128, 256 and 512 take this
 // kernel.  Any other block takes a workgroup per block (fused_wide_kernel)
-// where that is faster, or two passes: the same kernel with the 256-element
-// chunks and no quantization (p, m, v, primary, secondary: 32 B per element),
-// then the int8 quantizer over the primary it wrote (3 B + 4/B B), in stream
-// order.  The 2 extra bytes per element cost
+// where that is faster (wide_block, zpp_chunk.h), or two passes: the same kernel
+// with the 256-element chunks and no quantization (p, m, v, primary, secondary:
+// 32 B per element), then the int8 quantizer over the primary it wrote (3 B +
+// 4/B B), in stream order.  Over a long array the 2 extra bytes per element cost
 // less than holding a larger block's values in a wave: at the Llama-2-13B
 // partition the two passes took 1094-1104 us at blocks of 192 to 4096, the
 // one-pass layouts 1127-1186 us (one wave per chunk of whole blocks, several
@@ -28,8 +28,7 @@
 // with one float4 group per thread and a barrier per block), all but 512
 // (1073 against 1095 us one pass); the single pass of the qgZ receive took
 // 1112-1117 against 1245-1460 us.
-// Residency is capped at ZPP_FUSED_RESIDENCY
-// workgroups per CU, as for the optimizer step: 1031-1046 us with 11 resident
+// Residency is capped at ZPP_FUSED_RESIDENCY workgroups per CU, as for the optimizer step: 1031-1046 us with 11 resident
 // at the Llama-2-13B partition (9-18 within 1%), 1127-1145 us uncapped.  With
 // the qgZ receive in place of the fp32 gradient (8 int4 sources) the cap is
 // ZPP_FUSED_RECV_RESIDENCY: 1111 us with 12, 1118 with 14, 1150 with 11, 1216
@@ -152,8 +151,8 @@ __global__ __launch_bounds__(kWave) void fused_kernel(FusedArgs a, GS gs, TileSp
         fused_chunk<ADAMW, B, QUANT, false, MANY>(a, gs, base, chunks.tail);
 }
 
-// The fused step with one quant block per workgroup, for blocks that are not
-// 64 to 512: ceil(B / 256) waves, one float4 group per lane (the lanes past a
+// The fused step with one quant block per workgroup, for blocks other than 64,
+// 128, 256 and 512: ceil(B / 256) waves, one float4 group per lane (the lanes past a
 // block that is no multiple of 256 stay idle), the waves' maxima exchanged in
 // LDS.  The block's values stay in registers, so the primary is not read back
 // and there is one launch instead of two.
@@ -212,7 +211,8 @@ __device__ __forceinline__ void fused_wide_block(const FusedArgs &a, const GS &g
 }
 
 template <bool ADAMW, bool MANY, class GS>
-__global__ __launch_bounds__(1024) void fused_wide_kernel(FusedArgs a, GS gs, uint32_t B, TileSpan blocks) {
+__global__ __launch_bounds__(1024) void fused_wide_kernel(FusedArgs a, GS gs, uint32_t B,
+                                                          TileSpan blocks) {
     const uint32_t t = tile_of(blockIdx.x, gridDim.x, blocks, fused_xcd_run<GS>() / 4);
     const size_t k = blocks.first + t;
     if (__builtin_expect(t < blocks.whole, 1))

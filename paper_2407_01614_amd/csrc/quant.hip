@@ -142,8 +142,8 @@ __global__ __launch_bounds__(kQuantThreads) void quant_vec_kernel(
     }
 }
 
-// The quantization with the copy: the workgroup's U rows of blocks, `rest` elements of them inside the arrays
-// (WHOLE: all of them).
+// The quantization with the copy: the workgroup's U rows of blocks, `rest`
+// elements of them inside the arrays (WHOLE: all of them).
 template <int B, int U, bool WHOLE>
 __device__ __forceinline__ void quant_copy_rows(const uint16_t *__restrict__ src,
                                                 int8_t *__restrict__ codes,

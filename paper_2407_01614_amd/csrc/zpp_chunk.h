@@ -1,7 +1,8 @@
 // Work distribution shared by the kernels and the host checks: the lane
 // layout of the quantizers for blocks that are not powers of two (any
-// multiple of 64 up to 4096), the renumbering of workgroups per XCD, and the
-// cap on workgroups resident per CU.
+// multiple of 64 up to 4096), the renumbering of workgroups per XCD, the tiles
+// of a launch, the cap on workgroups resident per CU, and the rules by which a
+// launch takes one form or another.
 #pragma once
 
 #include <stddef.h>
@@ -242,10 +243,10 @@ constexpr int copies_residency(Gradient from, int with_quant) {
 // long one streams, and from the interleaved buffer keeps the cap (uncapped /
 // capped, 16 sources at 50 M: blocks of 256 302.6 / 285, of 64 349 / 332, of
 // 320 359 / 343; 64 sources at 8 M, blocks of 64 and 320: capped better and
-// worse by 3%).  Separate arrays in the many-source form
-// stream best with 16 (16 sources, blocks of 1024 at 50 M: 319 uncapped, 308,
-// 325 with the cap of few sources); in other blocks every cap loses (32
-// sources, blocks of 64 at 50 M 391 / 435).  The step with its copies alone
+// worse by 3%).  Separate arrays in the many-source form stream best with 16 (16
+// sources, blocks of 1024 at 50 M: 319 uncapped, 308, 325 with the cap of few
+// sources); in other blocks every cap loses (32 sources, blocks of 64 at 50 M
+// 391 / 435).  The step with its copies alone
 // (quant false) keeps 11 in the many-source form of the interleaved buffer (24
 // sources at 50 M, both kernels: 385 uncapped, 393 with 9, 365).
 constexpr int receive_residency(Gradient from, uint32_t num_src, uint32_t grad_block, size_t n,

@@ -189,7 +189,12 @@ struct F32Grad {
 // 13 M: receive pass 101 -> 87 (separate), 87.5 -> 83.
 // Codes of two groups by one 4-byte load, halves swapped between lane pairs,
 // was no faster (62.8 and 59.1 us at 64 sources), nor was a cheaper decode
-// (v_cvt_off_f32_i4 with the scale times 16).
+// (v_cvt_off_f32_i4 with the scale times 16).  The kernels hold 63 to 66
+// registers in this form, but 82 to 128 with L2 decay from the interleaved buffer
+// or two groups per lane (int8 blocks of 512), so 16 to 20 waves per CU where
+// nothing caps them, which at 50 M elements and 16 sources is no slower than the
+// form of few sources: the pass with L2 decay 318 us against 319.5, blocks of 512
+// from separate arrays 343 against 348.
 __device__ __forceinline__ float tile_scale(const I4Grad &s, size_t k, uint32_t lane) {
     return s.scales[lane < s.num_src ? lane : 0][k];
 }

@@ -143,11 +143,15 @@ def test_traffic_sources_cover_every_include(bench):
 
 
 def test_traffic_file_matches_current_sources(bench):
-    """The committed counter figures are those of the sources as they are."""
-    with open(os.path.join(ROOT, "profiles", "traffic.json")) as f:
+    """The committed counter figures are those of the sources as they are, of
+    every kernel that has a digest, and the bench line finds Adam's."""
+    path = os.path.join(ROOT, "profiles", "traffic.json")
+    with open(path) as f:
         t = json.load(f)
+    assert set(t["kernels"]) == set(bench.TRAFFIC_SOURCES)
     for kernel, v in t["kernels"].items():
         assert v["source_digest"] == bench.source_digest(bench.TRAFFIC_SOURCES[kernel]), kernel
+    assert bench.measured_traffic(path, "llama-2-13b", "adam", bench.TRAFFIC_SOURCES["adam"])
 
 
 def test_workloads_offered_fit_the_pipeline(bench):

@@ -41,16 +41,18 @@ __device__ __forceinline__ size_t block_of(const BlockDiv &d, size_t i) {
     return d.magic ? (size_t)__umul64hi((unsigned long long)(i >> 6), d.magic) : i >> d.shift;
 }
 
-// Outputs that do not start on a 128-byte line: a wave's store then ends inside
-// a line that the next tile's wave goes on with, and two XCDs that each write
-// their part of it cost two partial writes of memory.  So neighbouring tiles
-// run on one XCD, in runs of this many, and their parts meet in its L2: the
-// Adam step at 13.1 M elements off by one 81.3 us without, 70.2 / 69.6 /
+// Ranges that do not start on a 128-byte line: a tile's accesses end inside
+// lines that the next tile goes on with, and where two XCDs take the two, each
+// fetches the shared lines from memory.  So neighbouring tiles run on one XCD, in
+// runs of this many, and meet in its L2.  Counters at 13.1 M elements off by one,
+// read and written, plain order / runs (algorithmic): Adam 236 / 210 (210) and 190
+// / 191 (184) MB, the fused step 236 / 211 and 234 / 235 (223), a bf16 copy 29.5 /
+// 26.3 (26.2) and 27 / 27.  The Adam step there 81.3 us without, 70.2 / 69.6 /
 // 69.3 / 68.9 with runs of 16 / 32 / 64 / 128 (100 M: 618, 543 / 531 / 518 /
 // 511), the fused step 105 and 80, the receive step 82 and 72, the gather of
 // 200 M 121 and 102.  (Outputs that start inside a line but far enough from its
-// ends lose by the runs: zpp_api.hip has the measured lines.)  Stored as ordinary, temporal ones they were slower (73
-// us for the Adam step, 95 without the runs).
+// ends lose by the runs: zpp_api.hip has the measured lines.)  Stored as ordinary,
+// temporal ones they were slower (73 us for the Adam step, 95 without the runs).
 constexpr size_t kOffLineXcdRun = 128;
 
 // The tile of workgroup w of the launch: renumbered in runs of `run` per XCD
